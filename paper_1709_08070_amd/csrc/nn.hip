@@ -16,6 +16,7 @@
 //
 // Training target for a pair (v, u = A⁻¹v): T = (Λu − v)/s per node; the loss is
 // Σ|O − T|² / Σ|T|² over the band.
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -396,138 +397,237 @@ __global__ void __launch_bounds__(kBlock) k_loss(int n, const float* __restrict_
   if (threadIdx.x == 0) part[blockIdx.x] = red[0];
 }
 
-// dZ = dY ⊙ act'(Y) (hidden layers; Y the stored BF16 activation, whose sign is that of the
-// pre-activation) or dY (output layer), as an FP32 array.
-template <bool kAct>
-__global__ void __launch_bounds__(kBlock) k_dz(int64_t total, const float* __restrict__ dY,
-                                               const uint16_t* __restrict__ Y, float* __restrict__ dZ) {
-  for (int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x; e < total; e += (int64_t)gridDim.x * kBlock)
-    dZ[e] = kAct ? dY[e] * dact(bf16_to_f32(Y[e])) : dY[e];
+// The pre-activation gradients dZ reach the MFMA kernels in BF16 (rounded to nearest even once,
+// here) in two layouts: row-major dZr[node][j] for the input gradient and transposed
+// dZt[j][ld] for the weight gradient, whose inner dimension is the node (rows padded with
+// zeros to whole tiles of kGradNodes, so every 16-byte operand load is aligned and in bounds).
+constexpr int kGradNodes = 64;  // nodes per block of the kernels that write dZ
+
+// One tile of kGradNodes nodes: tile[nd][j] (FP32, zero beyond n) is in LDS; writes its
+// BF16 transpose and the tile's bias gradient dbp[block][j] = Σ_nodes dZ (FP32, fixed order).
+// Every thread of the 256-thread block calls it after a barrier.
+template <int C>
+__device__ __forceinline__ void write_dz_tile(const float (*tile)[C + 1], int node0, int64_t ld,
+                                              uint16_t* __restrict__ dZt, float* __restrict__ dbp) {
+  for (int e = threadIdx.x; e < C * kGradNodes / 8; e += 256) {
+    const int j = e / (kGradNodes / 8), q = (e % (kGradNodes / 8)) * 8;
+    float v[8];
+#pragma unroll
+    for (int r = 0; r < 8; ++r) v[r] = tile[q + r][j];
+    *reinterpret_cast<short8_t*>(dZt + (int64_t)j * ld + node0 + q) = __builtin_bit_cast(short8_t, pack8(v));
+  }
+  if (threadIdx.x < C) {
+    float b = 0.f;
+    for (int nd = 0; nd < kGradNodes; ++nd) b += tile[nd][threadIdx.x];
+    dbp[(int64_t)blockIdx.x * C + threadIdx.x] = b;
+  }
 }
 
-// Weight gradient partials over a chunk of nodes: dW_part[blk][k][j] = Σ_nodes A[node][k]·dZ[node][j],
-// db_part[blk][j] = Σ_nodes dZ[node][j]. MFMA with the nodes as the inner dimension: one
-// wave per 16×16 (k, j) tile, tiles strided over the block's waves.
-template <bool kDense, int CIN, int COUT>
-__global__ void __launch_bounds__(256) k_wgrad(int n, int chunk, const uint16_t* __restrict__ G1,
-                                               const uint16_t* __restrict__ X, const int* __restrict__ nbr,
-                                               const float* __restrict__ dZ, float* __restrict__ dWp,
-                                               float* __restrict__ dbp) {
-  constexpr int K = kSlots * CIN;
-  constexpr int KT = K / 16, JT = COUT / 16;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+// Output layer: dZ = dO (n × 16), no activation.
+__global__ void __launch_bounds__(256) k_dz_out(int n, int64_t ld, const float* __restrict__ dO,
+                                                uint16_t* __restrict__ dZr, uint16_t* __restrict__ dZt,
+                                                float* __restrict__ dbp) {
+  __shared__ float tile[kGradNodes][17];
+  const int node0 = blockIdx.x * kGradNodes;
+  for (int e = threadIdx.x; e < kGradNodes * 16; e += 256) {
+    const int nd = e / 16, j = e % 16;
+    const float v = node0 + nd < n ? dO[(int64_t)(node0 + nd) * 16 + j] : 0.f;
+    tile[nd][j] = v;
+    if (node0 + nd < n) dZr[(int64_t)(node0 + nd) * 16 + j] = bf16_bits(v);
+  }
+  __syncthreads();
+  write_dz_tile<16>(tile, node0, ld, dZt, dbp);
+}
+
+// 8×8 transpose of 16-bit elements in registers: x[r] holds 8 channels of node r, f[t] the 8
+// nodes of channel t. Two byte permutes per pair of dwords, 32 in all.
+__device__ __forceinline__ void transpose8(const short8_t (&x)[8], bf16x8_t (&f)[8]) {
+  typedef unsigned uint4_t __attribute__((ext_vector_type(4)));
+  uint4_t in[8];
+#pragma unroll
+  for (int r = 0; r < 8; ++r) in[r] = __builtin_bit_cast(uint4_t, x[r]);
+#pragma unroll
+  for (int t = 0; t < 8; ++t) {
+    uint4_t o;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      o[q] = __builtin_amdgcn_perm(in[2 * q + 1][t / 2], in[2 * q][t / 2], t & 1 ? 0x07060302u : 0x05040100u);
+    f[t] = __builtin_bit_cast(bf16x8_t, o);
+  }
+}
+
+// Weight gradient partials over a chunk of nodes (a multiple of 32):
+// dW_part[chunk][k][j] = Σ_nodes A[node][k]·dZ[node][j], an MFMA product with the nodes as the
+// inner dimension. A wave takes 128 rows k (two neighbour slots of 64 channels, or 128
+// columns of the dense first layer) against all COUT columns: per step of 32 nodes each lane
+// reads 8 consecutive channels of 8 nodes (16-byte loads, 8 lanes to a 128-byte activation
+// row) and transposes them in registers into the A fragments of 8 tiles; lane q of a 16-row tile
+// t then stands for row (q >> 3)·64 + 8(q & 7) + t. The B fragments are 16-byte loads of dZt.
+// Bound by the gathers' latency; 128 chunks (512 for the small products) give about one wave per SIMD
+// with the next step's rows in flight. One 16×16 tile per wave with scalar 2-byte gathers, 18
+// to 27 blocks of 2048 nodes, took 10.4 ms per 64 → 64 layer at 55,111 nodes; this takes 38 µs.
+template <bool kDense, int COUT>
+__global__ void __launch_bounds__(256) k_wgrad(int n, int chunk, int64_t ld, const uint16_t* __restrict__ X,
+                                               const int* __restrict__ nbr, const uint16_t* __restrict__ dZt,
+                                               float* __restrict__ dWp) {
+  constexpr int K = kDense ? 256 : 1024, NT = COUT / 16;
+  const int lane = threadIdx.x & 63;
+  const int kb = blockIdx.y * (blockDim.x >> 6) + (threadIdx.x >> 6);  // 128-row block of dW
   const int n0 = blockIdx.x * chunk, n1 = min(n, n0 + chunk);
-  const int nq = 8 * (lane >> 4);
-  for (int tile = wave; tile < KT * JT; tile += 4) {
-    const int kt = tile / JT, jt = tile % JT;
-    const int krow = kt * 16 + (lane & 15);
-    const int jcol = jt * 16 + (lane & 15);
-    const int slot = krow / CIN, c = krow % CIN;
-    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
-    for (int nb = n0; nb < n1; nb += 32) {
-      short8_t as;
-      float bv[8];
+  const int nq = 8 * (lane >> 4);                   // the lane's nodes within a step
+  const int half = (lane >> 3) & 1, c0 = 8 * (lane & 7);
+  f32x4_t acc[8][NT];
 #pragma unroll
-      for (int r = 0; r < 8; ++r) {
-        const int nd = nb + nq + r;
-        if (nd < n1) {
-          as[r] = (short)(kDense ? G1[(int64_t)nd * K + krow] : X[(int64_t)nbr[(int64_t)nd * kSlots + slot] * CIN + c]);
-          bv[r] = dZ[(int64_t)nd * COUT + jcol];
-        } else {
-          as[r] = 0;
-          bv[r] = 0.f;
-        }
-      }
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, as), pack8(bv), acc, 0, 0, 0);
-    }
-    // lane holds D[k = kt·16 + 4·(lane/16) + r][j = jt·16 + lane%16]
+  for (int t = 0; t < 8; ++t)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int k = kt * 16 + 4 * (lane >> 4) + r;
-      dWp[(int64_t)blockIdx.x * K * COUT + (int64_t)k * COUT + jcol] = acc[r];
-    }
-  }
-  // bias partials (FP32, fixed order)
-  for (int j = threadIdx.x; j < COUT; j += 256) {
-    float sacc = 0.f;
-    for (int nd = n0; nd < n1; ++nd) sacc += dZ[(int64_t)nd * COUT + j];
-    dbp[(int64_t)blockIdx.x * COUT + j] = sacc;
-  }
-}
-
-// grads[off + e] = Σ_blocks part[blk·count + e] (fixed order)
-__global__ void __launch_bounds__(kBlock) k_sum_parts(int64_t count, int nblk, const float* __restrict__ part,
-                                                      float* __restrict__ out) {
-  for (int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x; e < count; e += (int64_t)gridDim.x * kBlock) {
-    float s = 0.f;
-    for (int q = 0; q < nblk; ++q) s += part[(int64_t)q * count + e];
-    out[e] = s;
-  }
-}
-
-// dA = dZ · Wᵀ for 16-node wave tiles: dA[node][k] = Σ_j dZ[node][j]·W[k][j].
-template <int CIN, int COUT>
-__global__ void __launch_bounds__(256) k_dgrad(int n, const float* __restrict__ dZ, const uint16_t* __restrict__ Wk,
-                                               float* __restrict__ dA) {
-  constexpr int K = kSlots * CIN;
-  constexpr int JSTEPS = (COUT + 31) / 32;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int node0 = (blockIdx.x * 4 + wave) * 16;
-  const int node = node0 + (lane & 15);
-  const bool live = node < n;
-  const int jq = 8 * (lane >> 4);
-  bf16x8_t a[JSTEPS];
-#pragma unroll
-  for (int s = 0; s < JSTEPS; ++s) {
-    float vals[8];
+    for (int j = 0; j < NT; ++j) acc[t][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  const short8_t zero = {0, 0, 0, 0, 0, 0, 0, 0};
+  auto load = [&](int nb, short8_t (&x)[8]) {
+    int64_t at[8];
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
-      const int j = s * 32 + jq + r;
-      vals[r] = (live && j < COUT) ? dZ[(int64_t)node * COUT + j] : 0.f;
+      const int nd = min(nb + nq + r, n - 1);
+      at[r] = kDense ? (int64_t)nd * K + kb * 128 + half * 64 : (int64_t)nbr[(int64_t)nd * kSlots + 2 * kb + half] * 64;
     }
-    a[s] = pack8(vals);
+#pragma unroll
+    for (int r = 0; r < 8; ++r)
+      x[r] = nb + nq + r < n1 ? *reinterpret_cast<const short8_t*>(X + at[r] + c0) : zero;
+  };
+  short8_t x[8];
+  load(n0, x);
+  for (int nb = n0; nb < n1; nb += 32) {
+    bf16x8_t f[8], b[NT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) b[j] = load8_bf16(dZt + (int64_t)(j * 16 + (lane & 15)) * ld + nb + nq);
+    transpose8(x, f);
+    if (nb + 32 < n1) load(nb + 32, x);
+#pragma unroll
+    for (int t = 0; t < 8; ++t)
+#pragma unroll
+      for (int j = 0; j < NT; ++j) acc[t][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[t], b[j], acc[t][j], 0, 0, 0);
   }
-  for (int kt = 0; kt < K / 16; ++kt) {
-    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
-    const int kcol = kt * 16 + (lane & 15);
+  float* __restrict__ out = dWp + (int64_t)blockIdx.x * K * COUT;
 #pragma unroll
-    for (int s = 0; s < JSTEPS; ++s) {
-      float wv[8];
-#pragma unroll
-      for (int r = 0; r < 8; ++r) {
-        const int j = s * 32 + jq + r;
-        if (j < COUT) {
-          const uint32_t bits = (uint32_t)Wk[(int64_t)kcol * COUT + j] << 16;
-          memcpy(&wv[r], &bits, 4);
-        } else {
-          wv[r] = 0.f;
-        }
-      }
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[s], pack8(wv), acc, 0, 0, 0);
-    }
+  for (int t = 0; t < 8; ++t)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int nd = node0 + 4 * (lane >> 4) + r;
-      if (nd < n) dA[(int64_t)nd * K + kcol] = acc[r];
+      const int q = 4 * (lane >> 4) + r;
+      const int k = kb * 128 + (q >> 3) * 64 + 8 * (q & 7) + t;
+#pragma unroll
+      for (int j = 0; j < NT; ++j) out[(int64_t)k * COUT + j * 16 + (lane & 15)] = acc[t][j][r];
+    }
+}
+
+// grads[off + e] = Σ_blocks part[blk·count + e] (fixed order): 64 elements per block, the
+// partials split over its four waves and combined in wave order.
+__global__ void __launch_bounds__(kBlock) k_sum_parts(int64_t count, int nblk, const float* __restrict__ part,
+                                                      float* __restrict__ out) {
+  __shared__ float red[4][64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t e = (int64_t)blockIdx.x * 64 + lane;
+  const int q0 = (int)((int64_t)nblk * w / 4), q1 = (int)((int64_t)nblk * (w + 1) / 4);
+  float s = 0.f;
+  if (e < count) {
+#pragma unroll 8
+    for (int q = q0; q < q1; ++q) s += part[(int64_t)q * count + e];
+  }
+  red[w][lane] = s;
+  __syncthreads();
+  if (w == 0 && e < count) out[e] = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
+}
+
+// Bias gradient: out[j] = Σ_tiles part[tile·count + j], one block per j (fixed order).
+__global__ void __launch_bounds__(kBlock) k_sum_bias(int count, int ntile, const float* __restrict__ part,
+                                                     float* __restrict__ out) {
+  __shared__ float red[kBlock];
+  float s = 0.f;
+  for (int q = threadIdx.x; q < ntile; q += kBlock) s += part[(int64_t)q * count + blockIdx.x];
+  red[threadIdx.x] = s;
+  __syncthreads();
+  for (int off = kBlock / 2; off > 0; off >>= 1) {
+    if (threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) out[blockIdx.x] = red[0];
+}
+
+// dA[node][k] = Σ_j dZ[node][j]·W[k][j] as the MFMA product W·dZᵀ (W rows as A, nodes as columns),
+// so that a lane holds four consecutive k of one node: 16-byte stores. A block takes 64
+// nodes; each of its waves a quarter of the rows k, every W fragment serving four node tiles.
+// Bound by writing dA (4 KB per node): 64 µs per 64 → 64 layer at 55,111 nodes (3.5 TB/s), 104 µs
+// with 4-byte stores and one node tile per W fragment.
+template <int COUT>
+__global__ void __launch_bounds__(256) k_dgrad(int n, const uint16_t* __restrict__ dZr,
+                                               const uint16_t* __restrict__ Wk, float* __restrict__ dA) {
+  constexpr int K = kSlots * 64, JS = (COUT + 31) / 32;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int jq = 8 * (lane >> 4);
+  const bf16x8_t none = __builtin_bit_cast(bf16x8_t, short8_t{0, 0, 0, 0, 0, 0, 0, 0});
+  bf16x8_t b[4][JS];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int nd = blockIdx.x * 64 + u * 16 + (lane & 15);
+#pragma unroll
+    for (int s = 0; s < JS; ++s)
+      b[u][s] = nd < n && s * 32 + jq < COUT ? load8_bf16(dZr + (int64_t)nd * COUT + s * 32 + jq) : none;
+  }
+  for (int kt = wave * (K / 64); kt < (wave + 1) * (K / 64); ++kt) {
+    bf16x8_t a[JS];
+#pragma unroll
+    for (int s = 0; s < JS; ++s)
+      a[s] = s * 32 + jq < COUT ? load8_bf16(Wk + (int64_t)(kt * 16 + (lane & 15)) * COUT + s * 32 + jq) : none;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s = 0; s < JS; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[s], b[u][s], acc, 0, 0, 0);
+      const int nd = blockIdx.x * 64 + u * 16 + (lane & 15);
+      if (nd < n) *reinterpret_cast<f32x4_t*>(dA + (int64_t)nd * K + kt * 16 + 4 * (lane >> 4)) = acc;
     }
   }
 }
 
-// dX[j][c] = Σ_{(i, slot) with nbr[i][slot] = j} dA[i][slot·C + c], over the reverse lists
-// (sorted, so the sum order is fixed).
-template <int CIN>
-__global__ void __launch_bounds__(kBlock) k_scatter_back(int n, const int64_t* __restrict__ rrow,
-                                                         const int* __restrict__ rent, const float* __restrict__ dA,
-                                                         float* __restrict__ dX) {
-  const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (t >= (int64_t)n * CIN) return;
-  const int j = (int)(t / CIN), c = (int)(t % CIN);
-  float s = 0.f;
-  for (int64_t q = rrow[j]; q < rrow[j + 1]; ++q) {
-    const int e = rent[q];  // i·16 + slot
-    s += dA[(int64_t)(e / kSlots) * kSlots * CIN + (int64_t)(e % kSlots) * CIN + c];
+// dX[j][c] = Σ_{(i, slot) with nbr[i][slot] = j} dA[i][slot·64 + c] over the reverse lists (sorted,
+// so the sum order is fixed), then dZ = dX ⊙ act'(X) of the layer below (X its stored BF16
+// activation, whose sign is that of the pre-activation) in both layouts. 16 lanes read a
+// node's 256-byte rows of dA, four entries in flight; 16 nodes at a time, 64 per block. 58 µs at
+// 55,111 nodes (3.9 TB/s of dA), against 93 µs for the sum alone with one 4-byte channel per lane.
+__global__ void __launch_bounds__(256) k_scatter_back(int n, int64_t ld, const int64_t* __restrict__ rrow,
+                                                      const int* __restrict__ rent, const float* __restrict__ dA,
+                                                      const uint16_t* __restrict__ X, uint16_t* __restrict__ dZr,
+                                                      uint16_t* __restrict__ dZt, float* __restrict__ dbp) {
+  __shared__ float tile[kGradNodes][65];
+  typedef short short4_t __attribute__((ext_vector_type(4)));
+  const int node0 = blockIdx.x * kGradNodes, c = 4 * (threadIdx.x & 15);
+  for (int g = threadIdx.x >> 4; g < kGradNodes; g += 16) {
+    const int j = node0 + g;
+    f32x4_t s = {0.f, 0.f, 0.f, 0.f};
+    if (j < n) {
+      const int64_t e = rrow[j + 1];
+      int64_t q = rrow[j];
+      for (; q + 4 <= e; q += 4) {
+        f32x4_t v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)  // entry i·16 + slot is row i·16 + slot of dA's 64-channel rows
+          v[u] = *reinterpret_cast<const f32x4_t*>(dA + (int64_t)rent[q + u] * 64 + c);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) s += v[u];
+      }
+      for (; q < e; ++q) s += *reinterpret_cast<const f32x4_t*>(dA + (int64_t)rent[q] * 64 + c);
+      const short4_t y = *reinterpret_cast<const short4_t*>(X + (int64_t)j * 64 + c);
+      short4_t o;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        s[r] *= dact(bf16_to_f32((uint16_t)y[r]));
+        o[r] = (short)bf16_bits(s[r]);
+      }
+      *reinterpret_cast<short4_t*>(dZr + (int64_t)j * 64 + c) = o;
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) tile[g][c + r] = s[r];
   }
-  dX[t] = s;
+  __syncthreads();
+  write_dz_tile<64>(tile, node0, ld, dZt, dbp);
 }
 
 __global__ void __launch_bounds__(kBlock) k_rev_count(int64_t ne, const int* __restrict__ nbr,
@@ -604,15 +704,24 @@ struct NNBufs {
   uint16_t* G1;
   uint16_t* X[kLayers];  // BF16; X[0] unused (layer 0 reads G1); X[l] = input of layer l
   float* T;
-  float* dY;
-  float* dZ;
+  float* dO;
+  uint16_t* dZr;  // BF16 pre-activation gradients, row-major and transposed (see k_dz_out)
+  uint16_t* dZt;
+  int64_t ld;     // row length of dZt
   float* dA;
   float* dWp;
+  float* dbp;
   double* lpart;
 };
 
 constexpr int kRedBlocks = 256;
-constexpr int kWgradChunk = 2048;
+// Node chunks of a weight gradient with `rows` rows and COUT columns: at least 256 nodes each
+// (8 MFMA steps) and at most 32 MB of partial products in all.
+int wgrad_chunk(int n, int rows, int cout) {
+  const int most = (32 << 20) / (4 * rows * cout);
+  const int c = std::max(256, (n + most - 1) / most);
+  return (c + 31) / 32 * 32;
+}
 
 pb_status bufs(pb_ctx* ctx, int n, NNBufs& B) {
   auto ws = [&](const char* name, size_t bytes) { return workspace(ctx, name, bytes); };
@@ -628,14 +737,19 @@ pb_status bufs(pb_ctx* ctx, int n, NNBufs& B) {
   B.X[2] = (uint16_t*)ws("nn_X2", sizeof(uint16_t) * (size_t)n * 64);
   B.X[3] = (uint16_t*)ws("nn_X3", sizeof(uint16_t) * (size_t)n * 64);
   B.T = (float*)ws("nn_T", sizeof(float) * (size_t)n * 2);
-  B.dY = (float*)ws("nn_dY", sizeof(float) * (size_t)n * 64);
-  B.dZ = (float*)ws("nn_dZ", sizeof(float) * (size_t)n * 64);
+  B.dO = (float*)ws("nn_dO", sizeof(float) * (size_t)n * 16);
+  const int nt = (n + kGradNodes - 1) / kGradNodes;
+  B.ld = (int64_t)nt * kGradNodes;
+  B.dZr = (uint16_t*)ws("nn_dZr", sizeof(uint16_t) * (size_t)n * 64);
+  B.dZt = (uint16_t*)ws("nn_dZt", sizeof(uint16_t) * (size_t)B.ld * 64);
   B.dA = (float*)ws("nn_dA", sizeof(float) * (size_t)n * 1024);
-  const int nblk = (n + kWgradChunk - 1) / kWgradChunk;
-  B.dWp = (float*)ws("nn_dWp", sizeof(float) * (size_t)nblk * (1024 * 64 + 64));
+  const int cw = wgrad_chunk(n, 1024, 64), cs = wgrad_chunk(n, 256, 64);
+  B.dWp = (float*)ws("nn_dWp", sizeof(float) * std::max((size_t)((n + cw - 1) / cw) * 1024 * 64,
+                                                        (size_t)((n + cs - 1) / cs) * 256 * 64));
+  B.dbp = (float*)ws("nn_dbp", sizeof(float) * (size_t)nt * 64);
   B.lpart = (double*)ws("nn_lpart", sizeof(double) * 2 * kRedBlocks);
   if (!B.nbr || !B.feat || !B.rrow || !B.rent || !B.s || !B.spart || !B.G1 || !B.X[1] || !B.X[2] || !B.X[3] || !B.T ||
-      !B.dY || !B.dZ || !B.dA || !B.dWp || !B.lpart)
+      !B.dO || !B.dZr || !B.dZt || !B.dA || !B.dWp || !B.dbp || !B.lpart)
     return PB_ENOMEM;
   return PB_OK;
 }
@@ -721,41 +835,32 @@ pb_status nn_grads(pb_ctx* ctx, pb_nn* net, const pb_band* band, const Derived& 
   NNBufs B;
   PB_TRY(bufs(ctx, n, B));
   float* O = out_buf(ctx, n);
-  const unsigned nbl = (unsigned)((n + 63) / 64);
-  const unsigned ew = 2048;
+  const unsigned nt = (unsigned)((n + kGradNodes - 1) / kGradNodes);
   Scope t(ctx, "nn");
   k_target<<<kRedBlocks, kBlock, 0, ctx->stream>>>(n, v, u, B.s, d.lam1, d.lam2, B.T, B.lpart);
-  float* dO = B.dY;  // n × 16 fits in the n × 64 buffer
-  k_loss<<<kRedBlocks, kBlock, 0, ctx->stream>>>(n, O, B.T, B.lpart, kRedBlocks, dO, B.lpart + kRedBlocks);
-  const int nblk = (n + kWgradChunk - 1) / kWgradChunk;
+  k_loss<<<kRedBlocks, kBlock, 0, ctx->stream>>>(n, O, B.T, B.lpart, kRedBlocks, B.dO, B.lpart + kRedBlocks);
   float* g = net->grads;
-  const int64_t n64 = n;
-  // layer 3 (output): dZ = dO
-  k_dz<false><<<ew, kBlock, 0, ctx->stream>>>(n64 * 16, dO, nullptr, B.dZ);
-  k_wgrad<false, 64, 16><<<nblk, 256, 0, ctx->stream>>>(n, kWgradChunk, nullptr, B.X[3], B.nbr, B.dZ, B.dWp,
-                                                        B.dWp + (int64_t)nblk * 1024 * 16);
-  k_sum_parts<<<ew, kBlock, 0, ctx->stream>>>(1024 * 16, nblk, B.dWp, g + w_off(3));
-  k_sum_parts<<<1, kBlock, 0, ctx->stream>>>(16, nblk, B.dWp + (int64_t)nblk * 1024 * 16, g + b_off(3));
-  k_dgrad<64, 16><<<nbl, 256, 0, ctx->stream>>>(n, B.dZ, net->wk + wbf_off(3), B.dA);
-  k_scatter_back<64><<<(unsigned)((n64 * 64 + kBlock - 1) / kBlock), kBlock, 0, ctx->stream>>>(n, B.rrow, B.rent,
-                                                                                              B.dA, B.dY);
-  // layers 2, 1: dZ = dX_{l+1} ⊙ act'(X_{l+1}); input of layer l is X[l]
-  for (int l = 2; l >= 1; --l) {
-    k_dz<true><<<ew, kBlock, 0, ctx->stream>>>(n64 * 64, B.dY, B.X[l + 1], B.dZ);
-    k_wgrad<false, 64, 64><<<nblk, 256, 0, ctx->stream>>>(n, kWgradChunk, nullptr, B.X[l], B.nbr, B.dZ, B.dWp,
-                                                          B.dWp + (int64_t)nblk * 1024 * 64);
-    k_sum_parts<<<ew, kBlock, 0, ctx->stream>>>(1024 * 64, nblk, B.dWp, g + w_off(l));
-    k_sum_parts<<<1, kBlock, 0, ctx->stream>>>(64, nblk, B.dWp + (int64_t)nblk * 1024 * 64, g + b_off(l));
-    k_dgrad<64, 64><<<nbl, 256, 0, ctx->stream>>>(n, B.dZ, net->wk + wbf_off(l), B.dA);
-    k_scatter_back<64><<<(unsigned)((n64 * 64 + kBlock - 1) / kBlock), kBlock, 0, ctx->stream>>>(n, B.rrow, B.rent,
-                                                                                                B.dA, B.dY);
+  k_dz_out<<<nt, 256, 0, ctx->stream>>>(n, B.ld, B.dO, B.dZr, B.dZt, B.dbp);
+  // layers 3 to 1 gather X[l] (dX_l ⊙ act'(X_l) is the layer below's dZ); layer 0 reads G1 and
+  // has no input gradient
+  for (int l = kLayers - 1; l >= 0; --l) {
+    const int rows = kdim(l), cout = kCout[l];
+    const int chunk = wgrad_chunk(n, rows, cout), nc = (n + chunk - 1) / chunk;
+    if (l == 0)
+      k_wgrad<true, 64><<<dim3(nc, 1), 128, 0, ctx->stream>>>(n, chunk, B.ld, B.G1, B.nbr, B.dZt, B.dWp);
+    else if (l == kLayers - 1)
+      k_wgrad<false, 16><<<dim3(nc, 2), 256, 0, ctx->stream>>>(n, chunk, B.ld, B.X[l], B.nbr, B.dZt, B.dWp);
+    else
+      k_wgrad<false, 64><<<dim3(nc, 2), 256, 0, ctx->stream>>>(n, chunk, B.ld, B.X[l], B.nbr, B.dZt, B.dWp);
+    k_sum_parts<<<(unsigned)(rows * cout / 64), kBlock, 0, ctx->stream>>>((int64_t)rows * cout, nc, B.dWp, g + w_off(l));
+    k_sum_bias<<<(unsigned)cout, kBlock, 0, ctx->stream>>>(cout, (int)nt, B.dbp, g + b_off(l));
+    if (l == 0) break;
+    if (l == kLayers - 1)
+      k_dgrad<16><<<nt, 256, 0, ctx->stream>>>(n, B.dZr, net->wk + wbf_off(l), B.dA);
+    else
+      k_dgrad<64><<<nt, 256, 0, ctx->stream>>>(n, B.dZr, net->wk + wbf_off(l), B.dA);
+    k_scatter_back<<<nt, 256, 0, ctx->stream>>>(n, B.ld, B.rrow, B.rent, B.dA, B.X[l], B.dZr, B.dZt, B.dbp);
   }
-  // layer 0: input G1 (dense), no input gradient
-  k_dz<true><<<ew, kBlock, 0, ctx->stream>>>(n64 * 64, B.dY, B.X[1], B.dZ);
-  k_wgrad<true, 16, 64><<<nblk, 256, 0, ctx->stream>>>(n, kWgradChunk, B.G1, nullptr, B.nbr, B.dZ, B.dWp,
-                                                       B.dWp + (int64_t)nblk * 256 * 64);
-  k_sum_parts<<<ew, kBlock, 0, ctx->stream>>>(256 * 64, nblk, B.dWp, g + w_off(0));
-  k_sum_parts<<<1, kBlock, 0, ctx->stream>>>(64, nblk, B.dWp + (int64_t)nblk * 256 * 64, g + b_off(0));
   PB_TRY(launch_ok(ctx, "nn backward"));
   if (loss) {
     std::vector<double> lp(kRedBlocks);
