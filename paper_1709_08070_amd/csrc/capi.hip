@@ -187,56 +187,97 @@ pb_status check_band(pb_ctx* ctx, const pb_band* b) {
 
 // ---------------------------------------------------------------- scan
 
-constexpr int kScanBlock = 256;
+constexpr int kScanBlock = 256, kScanPer = 16;
+constexpr int kScanTile = kScanBlock * kScanPer;
 
-// Per-block inclusive scan of a segment; writes the block total to sums.
-__global__ void __launch_bounds__(kScanBlock) k_scan_blocks(int64_t* data, int64_t n, int64_t* sums) {
-  __shared__ int64_t s[kScanBlock];
-  int64_t i = (int64_t)blockIdx.x * kScanBlock + threadIdx.x;
-  int64_t v = i < n ? data[i] : 0;
-  s[threadIdx.x] = v;
+// Sum of each tile of kScanTile values.
+template <typename T>
+__global__ void __launch_bounds__(kScanBlock) k_scan_sums(const T* __restrict__ data, int64_t n, T* __restrict__ sums) {
+  __shared__ T s[kScanBlock];
+  T a = 0;
+#pragma unroll
+  for (int r = 0; r < kScanPer; ++r) {
+    const int64_t i = (int64_t)blockIdx.x * kScanTile + r * kScanBlock + threadIdx.x;
+    if (i < n) a += data[i];
+  }
+  s[threadIdx.x] = a;
+  __syncthreads();
+  for (int off = kScanBlock / 2; off > 0; off >>= 1) {
+    if (threadIdx.x < off) s[threadIdx.x] += s[threadIdx.x + off];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) sums[blockIdx.x] = s[0];
+}
+
+// Exclusive scan of one tile in place: its base is the sum of the earlier tiles' sums (re-added
+// by every block: two launches whatever n, against a recursion of scans over the sums); a
+// thread scans kScanPer consecutive values. The last block writes the total to total (may be null).
+template <typename T>
+__global__ void __launch_bounds__(kScanBlock) k_scan_apply(T* __restrict__ data, int64_t n, const T* __restrict__ sums,
+                                                           T* __restrict__ total) {
+  __shared__ T s[kScanBlock];
+  T b = 0;
+  for (int q = threadIdx.x; q < (int)blockIdx.x; q += kScanBlock) b += sums[q];
+  s[threadIdx.x] = b;
+  __syncthreads();
+  for (int off = kScanBlock / 2; off > 0; off >>= 1) {
+    if (threadIdx.x < off) s[threadIdx.x] += s[threadIdx.x + off];
+    __syncthreads();
+  }
+  const T base = s[0];
+  __syncthreads();
+  const int64_t i0 = (int64_t)blockIdx.x * kScanTile + threadIdx.x * kScanPer;
+  T v[kScanPer], t = 0;
+#pragma unroll
+  for (int r = 0; r < kScanPer; ++r) {
+    v[r] = i0 + r < n ? data[i0 + r] : 0;
+    t += v[r];
+  }
+  s[threadIdx.x] = t;
   __syncthreads();
   for (int off = 1; off < kScanBlock; off <<= 1) {
-    int64_t t = threadIdx.x >= off ? s[threadIdx.x - off] : 0;
+    const T u = threadIdx.x >= off ? s[threadIdx.x - off] : 0;
     __syncthreads();
-    s[threadIdx.x] += t;
+    s[threadIdx.x] += u;
     __syncthreads();
   }
-  if (i < n) data[i] = s[threadIdx.x] - v;  // exclusive within block
-  if (threadIdx.x == kScanBlock - 1) sums[blockIdx.x] = s[threadIdx.x];
+  T run = base + s[threadIdx.x] - t;
+#pragma unroll
+  for (int r = 0; r < kScanPer; ++r) {
+    if (i0 + r < n) data[i0 + r] = run;
+    run += v[r];
+  }
+  if (total && blockIdx.x == gridDim.x - 1 && threadIdx.x == kScanBlock - 1) *total = run;
 }
 
-__global__ void __launch_bounds__(kScanBlock) k_scan_add(int64_t* data, int64_t n, const int64_t* offs) {
-  int64_t i = (int64_t)blockIdx.x * kScanBlock + threadIdx.x;
-  if (i < n) data[i] += offs[blockIdx.x];
-}
-
-// Recursive exclusive scan; total = sum of all inputs.
-static pb_status scan_rec(pb_ctx* ctx, int64_t* data, int64_t n, int64_t* total_dev, int depth) {
-  int64_t nb = (n + kScanBlock - 1) / kScanBlock;
-  char name[32];
-  snprintf(name, sizeof(name), "scan_sums%d", depth);
-  int64_t* sums = (int64_t*)workspace(ctx, name, sizeof(int64_t) * (size_t)(nb + 1));
+template <typename T>
+static pb_status scan(pb_ctx* ctx, T* data, int64_t n, T* total_dev) {
+  const int64_t nb = (n + kScanTile - 1) / kScanTile;
+  T* sums = (T*)workspace(ctx, "scan_sums", sizeof(int64_t) * (size_t)nb);
   if (!sums) return PB_ENOMEM;
-  k_scan_blocks<<<(unsigned)nb, kScanBlock, 0, ctx->stream>>>(data, n, sums);
-  PB_TRY(launch_ok(ctx, "scan"));
-  if (nb == 1) {
-    PB_HIP(ctx, hipMemcpyAsync(total_dev, sums, sizeof(int64_t), hipMemcpyDeviceToDevice, ctx->stream));
-    return PB_OK;
-  }
-  PB_TRY(scan_rec(ctx, sums, nb, total_dev, depth + 1));
-  k_scan_add<<<(unsigned)nb, kScanBlock, 0, ctx->stream>>>(data, n, sums);
-  return launch_ok(ctx, "scan_add");
+  if (nb > 1) k_scan_sums<T><<<(unsigned)nb, kScanBlock, 0, ctx->stream>>>(data, n, sums);
+  k_scan_apply<T><<<(unsigned)nb, kScanBlock, 0, ctx->stream>>>(data, n, sums, total_dev);
+  return launch_ok(ctx, "scan");
 }
 
 pb_status exclusive_scan_i64(pb_ctx* ctx, int64_t* data, int64_t n, int64_t* total_host) {
-  int64_t* tot = (int64_t*)workspace(ctx, "scan_total", sizeof(int64_t));
-  if (!tot) return PB_ENOMEM;
-  PB_TRY(scan_rec(ctx, data, n, tot, 0));
-  if (total_host) {
-    PB_HIP(ctx, hipMemcpyAsync(total_host, tot, sizeof(int64_t), hipMemcpyDeviceToHost, ctx->stream));
-    PB_TRY(sync(ctx, "scan"));
-  }
+  if (!total_host) return scan<int64_t>(ctx, data, n, nullptr);
+  PB_TRY(host_pin(ctx));
+  PB_TRY(scan<int64_t>(ctx, data, n, (int64_t*)ctx->host_pin_dev));
+  PB_TRY(sync(ctx, "scan"));
+  *total_host = *(volatile int64_t*)ctx->host_pin;
+  return PB_OK;
+}
+
+pb_status exclusive_scan_i32(pb_ctx* ctx, int* data, int64_t n) { return scan<int>(ctx, data, n, nullptr); }
+
+pb_status host_pin(pb_ctx* ctx) {
+  if (ctx->host_pin) return PB_OK;
+  void *h = nullptr, *dev = nullptr;
+  PB_HIP(ctx, hipHostMalloc(&h, sizeof(double) * kHostPin, hipHostMallocCoherent | hipHostMallocMapped));
+  ctx->host_pin = (double*)h;
+  PB_HIP(ctx, hipHostGetDevicePointer(&dev, h, 0));
+  ctx->host_pin_dev = (double*)dev;
   return PB_OK;
 }
 
@@ -277,6 +318,7 @@ void pb_destroy(pb_ctx* ctx) {
   }
   for (auto e : ctx->event_pool) (void)hipEventDestroy(e);
   if (ctx->host_state) (void)hipHostFree(ctx->host_state);
+  if (ctx->host_pin) (void)hipHostFree(ctx->host_pin);
   if (ctx->batch_stream) {
     (void)hipStreamSynchronize(ctx->batch_stream);
     (void)hipStreamDestroy(ctx->batch_stream);

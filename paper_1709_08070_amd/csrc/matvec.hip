@@ -11,7 +11,8 @@
 // is counted exactly once. The near matrix depends only on the geometry and is built once per
 // band; each application is then an SpMV. The far kernel's tile shape (sources per LDS tile,
 // targets per lane) is chosen per band size by timing the candidates once (autotuner); the
-// symmetric kernel (each unordered pair once, both directions) is one of the candidates.
+// symmetric kernel (each unordered pair once, both directions) is one of the candidates. The
+// near-field matrix and its cell list are built in near.hip.
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
@@ -277,108 +278,17 @@ F32Params f32params(const Derived& d, double sigma) {
                    (float)(rcs * rcs * 1.001)};
 }
 
-// Geometry of the mixed operator for one band: centre and scale of the FP32 records, the
-// cell list and the FP64 near-field CSR matrix. Buffers are named `<pfx>...` in the context
-// workspace; the plan receives the sizes and pointers.
-pb_status near_build(pb_ctx* ctx, const pb_band* band, const Derived& d, const char* pfx, MixedPlan& P,
-                     bool cells_only) {
-  const int n = (int)band->n;
-  auto name = [&](const char* s) {
-    static thread_local char buf[64];
-    snprintf(buf, sizeof(buf), "%s%s", pfx, s);
-    return (const char*)buf;
-  };
-  const int nbb = 256;
-  double* bb = (double*)workspace(ctx, name("bbox"), sizeof(double) * 6 * nbb);
-  if (!bb) return PB_ENOMEM;
-  k_bbox<<<nbb, kBlock, 0, ctx->stream>>>(n, band_dev(band), bb);
-  PB_TRY(launch_ok(ctx, "bbox"));
-  std::vector<double> hb(6 * nbb);
-  PB_HIP(ctx, hipMemcpyAsync(hb.data(), bb, sizeof(double) * 6 * nbb, hipMemcpyDeviceToHost, ctx->stream));
-  PB_TRY(sync(ctx, "bbox"));
-  double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-  for (int q = 0; q < nbb; ++q)
-    for (int a = 0; a < 3; ++a) {
-      lo[a] = std::fmin(lo[a], hb[6 * q + a]);
-      hi[a] = std::fmax(hi[a], hb[6 * q + 3 + a]);
-    }
-  P.band_key = band->px;
-  P.n = n;
-  P.cx = 0.5 * (lo[0] + hi[0]);
-  P.cy = 0.5 * (lo[1] + hi[1]);
-  P.cz = 0.5 * (lo[2] + hi[2]);
-  P.sigma = d.kappa > 0.0 ? d.kappa : 1.0;
-  P.rc = d.rc;
-  P.rc2f = f32params(d, P.sigma).rc2;
-  // cells at least r_c wide (margin for the FP32 rounding of the coordinates), at most 2^26 cells
-  double cell = d.rc * 1.001 + 1e-4;
-  for (;;) {
-    double nc = 1.0;
-    for (int a = 0; a < 3; ++a) nc *= std::floor((hi[a] - lo[a]) / cell) + 1.0;
-    if (nc <= 67108864.0) break;
-    cell *= 1.25;
-  }
-  P.cell = cell;
-  P.ncx = (int)std::floor((hi[0] - lo[0]) / cell) + 1;
-  P.ncy = (int)std::floor((hi[1] - lo[1]) / cell) + 1;
-  P.ncz = (int)std::floor((hi[2] - lo[2]) / cell) + 1;
-  const int64_t ncell = (int64_t)P.ncx * P.ncy * P.ncz;
-  int64_t* start = (int64_t*)workspace(ctx, name("cell_start"), sizeof(int64_t) * (size_t)(ncell + 1));
-  int* cursor = (int*)workspace(ctx, name("cell_cursor"), sizeof(int) * (size_t)ncell);
-  int* nodes = (int*)workspace(ctx, name("cell_nodes"), sizeof(int) * (size_t)n);
-  int* cell_of = (int*)workspace(ctx, name("cell_of"), sizeof(int) * (size_t)n);
-  float4* A = (float4*)workspace(ctx, name("A"), sizeof(float4) * n);
-  float4* M = (float4*)workspace(ctx, name("M"), sizeof(float4) * n);
-  float4* N = (float4*)workspace(ctx, name("N"), sizeof(float4) * n);
-  const int ngroup = (n + kGroup - 1) / kGroup;
-  float4* box = (float4*)workspace(ctx, name("box"), sizeof(float4) * 2 * (size_t)ngroup);
-  int64_t* row = (int64_t*)workspace(ctx, name("near_row"), sizeof(int64_t) * (size_t)(n + 1));
-  if (!start || !cursor || !nodes || !cell_of || !A || !M || !N || !box || !row) return PB_ENOMEM;
-  PB_HIP(ctx, hipMemsetAsync(start, 0, sizeof(int64_t) * (size_t)(ncell + 1), ctx->stream));
-  PB_HIP(ctx, hipMemsetAsync(cursor, 0, sizeof(int) * (size_t)ncell, ctx->stream));
-  const unsigned nb = (unsigned)((n + kBlock - 1) / kBlock);
-  k_cell_count<<<nb, kBlock, 0, ctx->stream>>>(n, band_dev(band), lo[0], lo[1], lo[2], 1.0 / cell, P.ncx, P.ncy,
-                                               P.ncz, cell_of, start);
-  PB_TRY(launch_ok(ctx, "cell count"));
-  PB_TRY(exclusive_scan_i64(ctx, start, ncell + 1, nullptr));
-  k_cell_fill<<<nb, kBlock, 0, ctx->stream>>>(n, cell_of, start, cursor, nodes);
-  k_cell_sort<<<(unsigned)((ncell + kBlock - 1) / kBlock), kBlock, 0, ctx->stream>>>(ncell, start, nodes);
-  PB_TRY(launch_ok(ctx, "cell list"));
-  if (cells_only) return PB_OK;
-  // FP32 records (weights zero) for the near predicate, then the near-field block matrix
-  k_pack_f32<<<nb, kBlock, 0, ctx->stream>>>(n, band_dev(band), band->w, nullptr, 0.0, P.cx, P.cy, P.cz, P.sigma, A,
-                                             M, N);
-  k_group_box<<<(unsigned)ngroup, kGroup, 0, ctx->stream>>>(n, A, box);
-  const CellsDev cells{start, nodes, cell_of, P.ncx, P.ncy, P.ncz};
-  PB_HIP(ctx, hipMemsetAsync(row + n, 0, sizeof(int64_t), ctx->stream));
-  const unsigned nbw = (unsigned)((n + kNearWaves - 1) / kNearWaves);
-  k_near_count<<<nbw, kBlock, 0, ctx->stream>>>(n, A, cells, P.rc2f, row);
-  PB_TRY(launch_ok(ctx, "near count"));
-  int64_t nnz = 0;
-  PB_TRY(exclusive_scan_i64(ctx, row, n + 1, &nnz));
-  P.nnz = nnz;
-  int* col = (int*)workspace(ctx, name("near_col"), sizeof(int) * (size_t)std::max<int64_t>(nnz, 1));
-  double4* coef = (double4*)workspace(ctx, name("near_coef"), sizeof(double4) * (size_t)std::max<int64_t>(nnz, 1));
-  if (!col || !coef) return PB_ENOMEM;
-  k_near_fill<<<nbw, kBlock, 0, ctx->stream>>>(n, band_dev(band, d.curved), band->w, d.h3 / (4.0 * kPi), A, cells,
-                                               P.rc2f, kparams(d), row, col, coef);
-  PB_TRY(launch_ok(ctx, "near fill"));
-  P.A = A;
-  P.M = M;
-  P.N = N;
-  P.box = box;
-  P.row = row;
-  P.col = col;
-  P.coef = coef;
-  return PB_OK;
-}
-
 pb_status mixed_prepare(pb_ctx* ctx, const pb_band* band, const Derived& d) {
   PB_TRY(near_build(ctx, band, d, "mx_", ctx->mixed));
   const int n = (int)band->n;
   MixedPlan& P = ctx->mixed;
   double* partial = (double*)workspace(ctx, "mv_partial", sizeof(double) * 2 * (size_t)n * far_max_chunks(ctx, n));
   if (!partial) return PB_ENOMEM;
+  if (!ctx->far_cfg.count(n)) {  // records (weights zero) for the candidates' timing
+    k_pack_f32<<<(unsigned)((n + kBlock - 1) / kBlock), kBlock, 0, ctx->stream>>>(
+        n, band_dev(band), band->w, nullptr, 0.0, P.cx, P.cy, P.cz, P.sigma, P.A, P.M, P.N);
+    PB_TRY(launch_ok(ctx, "pack"));
+  }
   return far_autotune(ctx, n, d.kappa > 0.0, P.A, P.M, P.N, P.box, f32params(d, P.sigma), partial, &P.far_cfg);
 }
 

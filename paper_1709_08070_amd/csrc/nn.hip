@@ -100,39 +100,136 @@ __device__ __forceinline__ float dact(float x) { return x > 0.f ? 1.f : kSlope; 
 
 // ---------------------------------------------------------------- geometry
 
-// 16 nearest band nodes by projection distance (self first), from the near-field cell list.
-__global__ void __launch_bounds__(kBlock) k_knn(int n, BandDev b, CellsDev cells, int* __restrict__ nbr) {
-  const int i = blockIdx.x * kBlock + threadIdx.x;
-  if (i >= n) return;
+// 16 nearest band nodes by projection distance (ties by index; self first), from the cell list:
+// one wave per node.
+//  1. The lanes form the squared distances of the node's candidates (the nine ranges of its 27
+//     cells) and keep them in LDS (kKnnCand) and from there in registers.
+//  2. Bisection on a squared radius, by ballots, for one that holds 16 to 64 candidates (all
+//     of them where there are no more than 64).
+//  3. Those are compacted, and each ranks itself among them by (distance, index): rank s < 16 is
+//     slot s.
+// Where a node has more than kKnnCand candidates or no such radius exists (48 equal distances),
+// the wave's first lane keeps a sorted list of 16 over a scan of the ranges instead. 112 µs at
+// 55,111 nodes; one thread per node keeping such a list took 594 µs: its insertions are a serial
+// chain and the lanes' candidates are scattered.
+constexpr int kKnnCand = 512;
+constexpr int kKnnWaves = 4;
+
+__device__ __forceinline__ double dist2_rn(double dx, double dy, double dz) {
+  return __dadd_rn(__dadd_rn(__dmul_rn(dx, dx), __dmul_rn(dy, dy)), __dmul_rn(dz, dz));
+}
+
+__global__ void __launch_bounds__(64 * kKnnWaves) k_knn(int n, BandDev b, CellsDev cells, int* __restrict__ nbr) {
+  __shared__ double sd[kKnnWaves][kKnnCand];
+  __shared__ int sq[kKnnWaves][kKnnCand];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int i = blockIdx.x * kKnnWaves + w;
+  if (i >= n) return;  // whole waves; the kernel has no block barrier
+  auto lds_order = [] {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
+  const double xi = b.px[i], yi = b.py[i], zi = b.pz[i];
+  int lo, hi;
+  cell_ranges(cells, cells.cell_of[i], lo, hi);
+  int m = 0;
+  for (int r = 0; r < 9; ++r) m += __builtin_amdgcn_readlane(hi, r) - __builtin_amdgcn_readlane(lo, r);
+  int* __restrict__ out = nbr + (int64_t)i * kSlots;
+  bool done = false;
+  if (m <= kKnnCand) {
+    int at = 0;
+    for (int r = 0; r < 9; ++r) {
+      const int a = __builtin_amdgcn_readlane(lo, r), e = __builtin_amdgcn_readlane(hi, r);
+      for (int q = a + lane; q < e; q += 64) {
+        const double4 x = cells.pos[q];
+        sd[w][at + q - a] = dist2_rn(xi - x.x, yi - x.y, zi - x.z);
+        sq[w][at + q - a] = q;
+      }
+      at += e - a;
+    }
+    lds_order();
+    constexpr int kRows = kKnnCand / 64;
+    double d[kRows];
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) d[r] = r * 64 + lane < m ? sd[w][r * 64 + lane] : INFINITY;
+    // cells are at least r_c wide: (2 cells)² bounds what the bisection starts from
+    const double top = 12.0 / (cells.inv * cells.inv);
+    double t = m <= 64 ? INFINITY : top, tl = 0.0, th = INFINITY;
+    int cnt = m;
+    for (int it = 0; m > 64 && it < 48; ++it) {
+      t = th < INFINITY ? 0.5 * (tl + th) : (it == 0 ? top * 0.0625 : t * 4.0);
+      cnt = 0;
+#pragma unroll
+      for (int r = 0; r < kRows; ++r)
+        if (r * 64 < m) cnt += __popcll(__ballot(d[r] <= t));
+      if (cnt < kSlots) tl = t;
+      else if (cnt > 64) th = t;
+      else break;
+    }
+    if (cnt <= 64 && (cnt >= kSlots || m <= 64)) {
+      // compact the survivors into the first cnt LDS slots; a survivor's place is never beyond
+      // its own, and every lane holds its distances in registers, its q is read before any write
+      int q[kRows];
+#pragma unroll
+      for (int r = 0; r < kRows; ++r) q[r] = r * 64 + lane < m ? sq[w][r * 64 + lane] : 0;
+      lds_order();
+      int base = 0;
+#pragma unroll
+      for (int r = 0; r < kRows; ++r)
+        if (r * 64 < m) {
+          const bool in = r * 64 + lane < m && d[r] <= t;
+          const unsigned long long mask = __ballot(in);
+          if (in) {
+            const int at2 = base + __popcll(mask & ((1ull << lane) - 1ull));
+            sd[w][at2] = d[r];
+            sq[w][at2] = cells.nodes[q[r]];
+          }
+          base += __popcll(mask);
+        }
+      lds_order();
+      cnt = base;  // a NaN distance is in no radius
+      const double dm = lane < cnt ? sd[w][lane] : INFINITY;
+      const int jm = lane < cnt ? sq[w][lane] : 0;
+      int rank = 0;
+      for (int k = 0; k < cnt; ++k) {
+        const double dk = sd[w][k];
+        const int jk = sq[w][k];
+        rank += dk < dm || (dk == dm && jk < jm);
+      }
+      if (lane < cnt && rank < kSlots) out[rank] = jm;
+      if (lane >= cnt && lane < kSlots) out[lane] = i;  // fewer than 16 candidates
+      done = true;
+    }
+  }
+  if (done) return;
+  // the general case: lane r < 9's range bounds are needed by lane 0, so every lane takes part in
+  // the reads of them
   double bd[kSlots];
   int bi[kSlots];
   for (int s = 0; s < kSlots; ++s) {
     bd[s] = INFINITY;
     bi[s] = i;
   }
-  const double xi = b.px[i], yi = b.py[i], zi = b.pz[i];
-  const int c = cells.cell_of[i];
-  const int cz = c % cells.ncz, cy = (c / cells.ncz) % cells.ncy, cx = c / (cells.ncz * cells.ncy);
-  for (int ax = max(cx - 1, 0); ax <= min(cx + 1, cells.ncx - 1); ++ax)
-    for (int ay = max(cy - 1, 0); ay <= min(cy + 1, cells.ncy - 1); ++ay)
-      for (int az = max(cz - 1, 0); az <= min(cz + 1, cells.ncz - 1); ++az) {
-        const int cc = (ax * cells.ncy + ay) * cells.ncz + az;
-        for (int64_t q = cells.start[cc]; q < cells.start[cc + 1]; ++q) {
-          const int j = cells.nodes[q];
-          const double dx = xi - b.px[j], dy = yi - b.py[j], dz = zi - b.pz[j];
-          const double d2 = __dadd_rn(__dadd_rn(__dmul_rn(dx, dx), __dmul_rn(dy, dy)), __dmul_rn(dz, dz));
-          if (d2 > bd[kSlots - 1] || (d2 == bd[kSlots - 1] && j >= bi[kSlots - 1])) continue;
-          int s = kSlots - 1;
-          while (s > 0 && (bd[s - 1] > d2 || (bd[s - 1] == d2 && bi[s - 1] > j))) {
-            bd[s] = bd[s - 1];
-            bi[s] = bi[s - 1];
-            --s;
-          }
-          bd[s] = d2;
-          bi[s] = j;
-        }
+  for (int r = 0; r < 9; ++r) {
+    const int a = __builtin_amdgcn_readlane(lo, r), e = __builtin_amdgcn_readlane(hi, r);
+    for (int q = a; q < e; ++q) {
+      const double4 x = cells.pos[q];
+      const int j = cells.nodes[q];
+      const double d2 = dist2_rn(xi - x.x, yi - x.y, zi - x.z);
+      if (d2 > bd[kSlots - 1] || (d2 == bd[kSlots - 1] && j >= bi[kSlots - 1])) continue;
+      int s = kSlots - 1;
+      while (s > 0 && (bd[s - 1] > d2 || (bd[s - 1] == d2 && bi[s - 1] > j))) {
+        bd[s] = bd[s - 1];
+        bi[s] = bi[s - 1];
+        --s;
       }
-  for (int s = 0; s < kSlots; ++s) nbr[(int64_t)i * kSlots + s] = bd[s] < INFINITY ? bi[s] : i;
+      bd[s] = d2;
+      bi[s] = j;
+    }
+  }
+  if (lane == 0)
+    for (int s = 0; s < kSlots; ++s) out[s] = bd[s] < INFINITY ? bi[s] : i;
 }
 
 // Per-node geometry features: φ/ε, n (3), H·ε with H = (2/m) Σ_{j≠i} (n_j − n_i)·(x_j − x_i)/|x_j − x_i|².
@@ -630,34 +727,31 @@ __global__ void __launch_bounds__(256) k_scatter_back(int n, int64_t ld, const i
   write_dz_tile<64>(tile, node0, ld, dZt, dbp);
 }
 
-__global__ void __launch_bounds__(kBlock) k_rev_count(int64_t ne, const int* __restrict__ nbr,
+// Reverse lists: entries e = i·16 + slot by neighbour nbr[e], increasing within a row. The
+// arrival-ordered slot of each entry comes with the count; each entry then ranks itself in its row.
+__global__ void __launch_bounds__(kBlock) k_rev_count(int64_t ne, const int* __restrict__ nbr, int* __restrict__ slot,
                                                       int64_t* __restrict__ cnt) {
   const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (e < ne) atomicAdd((unsigned long long*)&cnt[nbr[e]], 1ull);
+  if (e < ne) slot[e] = (int)atomicAdd((unsigned long long*)&cnt[nbr[e]], 1ull);
 }
 
 __global__ void __launch_bounds__(kBlock) k_rev_fill(int64_t ne, const int* __restrict__ nbr,
-                                                     const int64_t* __restrict__ row, int* __restrict__ cursor,
-                                                     int* __restrict__ ent) {
+                                                     const int64_t* __restrict__ row, const int* __restrict__ slot,
+                                                     int* __restrict__ tmp) {
+  const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (e < ne) tmp[row[nbr[e]] + slot[e]] = (int)e;
+}
+
+__global__ void __launch_bounds__(kBlock) k_rev_place(int64_t ne, const int* __restrict__ nbr,
+                                                      const int64_t* __restrict__ row, const int* __restrict__ tmp,
+                                                      int* __restrict__ ent) {
   const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (e >= ne) return;
   const int j = nbr[e];
-  const int slot = atomicAdd(&cursor[j], 1);
-  ent[row[j] + slot] = (int)e;
-}
-
-__global__ void __launch_bounds__(kBlock) k_rev_sort(int n, const int64_t* __restrict__ row, int* __restrict__ ent) {
-  const int j = blockIdx.x * kBlock + threadIdx.x;
-  if (j >= n) return;
-  for (int64_t q = row[j] + 1; q < row[j + 1]; ++q) {
-    const int v = ent[q];
-    int64_t t = q - 1;
-    while (t >= row[j] && ent[t] > v) {
-      ent[t + 1] = ent[t];
-      --t;
-    }
-    ent[t + 1] = v;
-  }
+  const int64_t s = row[j], t = row[j + 1];
+  int64_t at = s;
+  for (int64_t q = s; q < t; ++q) at += tmp[q] < (int)e;
+  ent[at] = (int)e;
 }
 
 // Adam on the FP32 master parameters (bias-corrected), then the BF16 copies of the weights.
@@ -723,12 +817,11 @@ int wgrad_chunk(int n, int rows, int cout) {
   return (c + 31) / 32 * 32;
 }
 
-pb_status bufs(pb_ctx* ctx, int n, NNBufs& B) {
+// The buffers of one application, and with `train` those of the backward pass.
+pb_status bufs(pb_ctx* ctx, int n, NNBufs& B, bool train = false) {
   auto ws = [&](const char* name, size_t bytes) { return workspace(ctx, name, bytes); };
   B.nbr = (int*)ws("nn_nbr", sizeof(int) * (size_t)n * kSlots);
   B.feat = (float*)ws("nn_feat", sizeof(float) * (size_t)n * 5);
-  B.rrow = (int64_t*)ws("nn_rrow", sizeof(int64_t) * (size_t)(n + 1));
-  B.rent = (int*)ws("nn_rent", sizeof(int) * (size_t)n * kSlots);
   B.s = (double*)ws("nn_s", sizeof(double) * 2);
   B.spart = (double*)ws("nn_spart", sizeof(double) * 2 * kRedBlocks);
   B.G1 = (uint16_t*)ws("nn_G1", sizeof(uint16_t) * (size_t)n * kdim(0));
@@ -736,6 +829,10 @@ pb_status bufs(pb_ctx* ctx, int n, NNBufs& B) {
   B.X[1] = (uint16_t*)ws("nn_X1", sizeof(uint16_t) * (size_t)n * 64);
   B.X[2] = (uint16_t*)ws("nn_X2", sizeof(uint16_t) * (size_t)n * 64);
   B.X[3] = (uint16_t*)ws("nn_X3", sizeof(uint16_t) * (size_t)n * 64);
+  if (!B.nbr || !B.feat || !B.s || !B.spart || !B.G1 || !B.X[1] || !B.X[2] || !B.X[3]) return PB_ENOMEM;
+  if (!train) return PB_OK;
+  B.rrow = (int64_t*)ws("nn_rrow", sizeof(int64_t) * (size_t)(n + 1));
+  B.rent = (int*)ws("nn_rent", sizeof(int) * (size_t)n * kSlots);
   B.T = (float*)ws("nn_T", sizeof(float) * (size_t)n * 2);
   B.dO = (float*)ws("nn_dO", sizeof(float) * (size_t)n * 16);
   const int nt = (n + kGradNodes - 1) / kGradNodes;
@@ -748,8 +845,7 @@ pb_status bufs(pb_ctx* ctx, int n, NNBufs& B) {
                                                         (size_t)((n + cs - 1) / cs) * 256 * 64));
   B.dbp = (float*)ws("nn_dbp", sizeof(float) * (size_t)nt * 64);
   B.lpart = (double*)ws("nn_lpart", sizeof(double) * 2 * kRedBlocks);
-  if (!B.nbr || !B.feat || !B.rrow || !B.rent || !B.s || !B.spart || !B.G1 || !B.X[1] || !B.X[2] || !B.X[3] || !B.T ||
-      !B.dO || !B.dZr || !B.dZt || !B.dA || !B.dWp || !B.dbp || !B.lpart)
+  if (!B.rrow || !B.rent || !B.T || !B.dO || !B.dZr || !B.dZt || !B.dA || !B.dWp || !B.dbp || !B.lpart)
     return PB_ENOMEM;
   return PB_OK;
 }
@@ -758,8 +854,8 @@ float* out_buf(pb_ctx* ctx, int n) { return (float*)workspace(ctx, "nn_O", sizeo
 
 }  // namespace
 
-// Neighbour lists, geometry features and reverse lists of a band, cached on the context for
-// the band last prepared.
+// Neighbour lists and geometry features of a band, cached on the context for the band last
+// prepared. The reverse lists, which only the backward pass reads, are built by its first use.
 pb_status nn_prepare(pb_ctx* ctx, const pb_band* band, const Derived& d) {
   const int n = (int)band->n;
   NNBufs B;
@@ -767,26 +863,33 @@ pb_status nn_prepare(pb_ctx* ctx, const pb_band* band, const Derived& d) {
   if (!band->phi) return ctx->fail(PB_EINVAL, "the learned path needs the band's phi array");
   MixedPlan P;
   PB_TRY(near_build(ctx, band, d, "nn_", P, true));
-  const CellsDev cells{(const int64_t*)ctx->bufs["nn_cell_start"].ptr, (const int*)ctx->bufs["nn_cell_nodes"].ptr,
-                       (const int*)ctx->bufs["nn_cell_of"].ptr, P.ncx, P.ncy, P.ncz};
   const unsigned nb = (unsigned)((n + kBlock - 1) / kBlock);
-  k_knn<<<nb, kBlock, 0, ctx->stream>>>(n, band_dev(band), cells, B.nbr);
+  k_knn<<<(unsigned)((n + kKnnWaves - 1) / kKnnWaves), 64 * kKnnWaves, 0, ctx->stream>>>(n, band_dev(band), cells_dev(P),
+                                                                                       B.nbr);
   k_geom<<<nb, kBlock, 0, ctx->stream>>>(n, band_dev(band), band->phi, d.eps, B.nbr, B.feat);
-  // reverse lists of (node, slot) per neighbour
-  const int64_t ne = (int64_t)n * kSlots;
-  int* cursor = (int*)workspace(ctx, "nn_cursor", sizeof(int) * (size_t)n);
-  if (!cursor) return PB_ENOMEM;
-  PB_HIP(ctx, hipMemsetAsync(B.rrow, 0, sizeof(int64_t) * (size_t)(n + 1), ctx->stream));
-  PB_HIP(ctx, hipMemsetAsync(cursor, 0, sizeof(int) * (size_t)n, ctx->stream));
-  const unsigned nbe = (unsigned)((ne + kBlock - 1) / kBlock);
-  k_rev_count<<<nbe, kBlock, 0, ctx->stream>>>(ne, B.nbr, B.rrow);
-  PB_TRY(launch_ok(ctx, "nn reverse count"));
-  PB_TRY(exclusive_scan_i64(ctx, B.rrow, n + 1, nullptr));
-  k_rev_fill<<<nbe, kBlock, 0, ctx->stream>>>(ne, B.nbr, B.rrow, cursor, B.rent);
-  k_rev_sort<<<nb, kBlock, 0, ctx->stream>>>(n, B.rrow, B.rent);
   PB_TRY(launch_ok(ctx, "nn prepare"));
   ctx->nn_key = band->px;
   ctx->nn_n = n;
+  ctx->nn_rev = false;
+  return PB_OK;
+}
+
+// Reverse lists of (node, slot) per neighbour, of the lists nn_prepare left on the context.
+static pb_status nn_reverse(pb_ctx* ctx, int n, const NNBufs& B) {
+  if (ctx->nn_rev) return PB_OK;
+  const int64_t ne = (int64_t)n * kSlots;
+  int* slot = (int*)workspace(ctx, "nn_rslot", sizeof(int) * 2 * (size_t)ne);
+  if (!slot) return PB_ENOMEM;
+  int* tmp = slot + ne;
+  PB_HIP(ctx, hipMemsetAsync(B.rrow, 0, sizeof(int64_t) * (size_t)(n + 1), ctx->stream));
+  const unsigned nbe = (unsigned)((ne + kBlock - 1) / kBlock);
+  k_rev_count<<<nbe, kBlock, 0, ctx->stream>>>(ne, B.nbr, slot, B.rrow);
+  PB_TRY(launch_ok(ctx, "nn reverse count"));
+  PB_TRY(exclusive_scan_i64(ctx, B.rrow, n + 1, nullptr));
+  k_rev_fill<<<nbe, kBlock, 0, ctx->stream>>>(ne, B.nbr, B.rrow, slot, tmp);
+  k_rev_place<<<nbe, kBlock, 0, ctx->stream>>>(ne, B.nbr, B.rrow, tmp, B.rent);
+  PB_TRY(launch_ok(ctx, "nn reverse lists"));
+  ctx->nn_rev = true;
   return PB_OK;
 }
 
@@ -833,7 +936,8 @@ pb_status nn_grads(pb_ctx* ctx, pb_nn* net, const pb_band* band, const Derived& 
   if (!ptmp) return PB_ENOMEM;
   PB_TRY(nn_apply(ctx, net, band, d, v, ptmp));
   NNBufs B;
-  PB_TRY(bufs(ctx, n, B));
+  PB_TRY(bufs(ctx, n, B, true));
+  PB_TRY(nn_reverse(ctx, n, B));
   float* O = out_buf(ctx, n);
   const unsigned nt = (unsigned)((n + kGradNodes - 1) / kGradNodes);
   Scope t(ctx, "nn");
@@ -1022,11 +1126,10 @@ pb_status nn_batch_prepare(pb_ctx* ctx, int n_mol, const pb_band* bands, const i
     const int n = (int)band->n, o = off_host[m];
     MixedPlan P;
     PB_TRY(near_build(ctx, band, d, "nnb_", P, true));
-    const CellsDev cells{(const int64_t*)ctx->bufs["nnb_cell_start"].ptr, (const int*)ctx->bufs["nnb_cell_nodes"].ptr,
-                         (const int*)ctx->bufs["nnb_cell_of"].ptr, P.ncx, P.ncy, P.ncz};
     const unsigned nbk = (unsigned)((n + kBlock - 1) / kBlock);
     int* nbr_m = nb.nbr + (int64_t)o * kSlots;
-    k_knn<<<nbk, kBlock, 0, ctx->stream>>>(n, band_dev(band), cells, nbr_m);
+    k_knn<<<(unsigned)((n + kKnnWaves - 1) / kKnnWaves), 64 * kKnnWaves, 0, ctx->stream>>>(n, band_dev(band),
+                                                                                         cells_dev(P), nbr_m);
     k_geom<<<nbk, kBlock, 0, ctx->stream>>>(n, band_dev(band), band->phi, d.eps, nbr_m, nb.feat + (int64_t)o * 5);
     k_batch_geometry<<<nbk, kBlock, 0, ctx->stream>>>(n, o, band_dev(band), nbr_m, nb.pos + 3 * (int64_t)o);
     PB_TRY(launch_ok(ctx, "nn batch prepare"));

@@ -11,6 +11,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include "fp64_math.hpp"
 #include "pb_internal.hpp"
 
 namespace pb {
@@ -52,17 +53,12 @@ __device__ __forceinline__ void kern4_f64(double xi, double yi, double zi, doubl
   }
   double dny = dx * nxj + dy * nyj + dz * nzj;
   double nn = nxi * nxj + nyi * nyj + nzi * nzj;
-  // 1/r from the hardware reciprocal square root refined by two Newton steps
-  double rinv = __builtin_amdgcn_rsq(r2);
-  double e = fma(-r2 * rinv, rinv, 1.0);
-  rinv = fma(0.5 * rinv, e, rinv);
-  e = fma(-r2 * rinv, rinv, 1.0);
-  rinv = fma(0.5 * rinv, e, rinv);
+  const double rinv = rsqrt_f64(r2);
   double r = r2 * rinv;
   double r3 = rinv * rinv * rinv;
   double r5 = r3 * rinv * rinv;
   double z = kp.kappa * r;
-  double E = exp(-z);
+  double E = exp_neg_f64(z);
   double a = E * (1.0 + z);
   double b = E * (3.0 + 3.0 * z + z * z);
   k[0] = dny * (1.0 - kp.th1 * a) * r3;
@@ -359,34 +355,6 @@ static __global__ void __attribute__((unused)) __launch_bounds__(kBlock) k_pack_
   N[j] = make_float4((float)b.nx[j], (float)b.ny[j], (float)b.nz[j], (float)w1);
 }
 
-// Bounding box of each aligned group of kGroup records (one block per group):
-// box[2g] = (lo, 0), box[2g + 1] = (hi, 0) over the group's live records.
-static __global__ void __attribute__((unused)) __launch_bounds__(kGroup) k_group_box(int n, const float4* __restrict__ A,
-                                                                  float4* __restrict__ box) {
-  __shared__ float s[6][kGroup];
-  const int i = blockIdx.x * kGroup + threadIdx.x;
-  float v[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
-  if (i < n) {
-    const float4 a = A[i];
-    v[0] = v[3] = a.x;
-    v[1] = v[4] = a.y;
-    v[2] = v[5] = a.z;
-  }
-  for (int q = 0; q < 6; ++q) s[q][threadIdx.x] = v[q];
-  __syncthreads();
-  for (int off = kGroup / 2; off > 0; off >>= 1) {
-    if (threadIdx.x < off)
-      for (int q = 0; q < 6; ++q)
-        s[q][threadIdx.x] = q < 3 ? fminf(s[q][threadIdx.x], s[q][threadIdx.x + off])
-                                  : fmaxf(s[q][threadIdx.x], s[q][threadIdx.x + off]);
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    box[2 * blockIdx.x] = make_float4(s[0][0], s[1][0], s[2][0], 0.f);
-    box[2 * blockIdx.x + 1] = make_float4(s[3][0], s[4][0], s[5][0], 0.f);
-  }
-}
-
 // FP32 far field of one band: block (x: kBlock·TPL targets, y: source chunk).
 template <int TILE, int TPL, bool kScreened>
 static __global__ void __attribute__((unused)) __launch_bounds__(kBlock) k_p2p_f32(const float4* __restrict__ A, const float4* __restrict__ M,
@@ -405,144 +373,35 @@ static __global__ void __attribute__((unused)) __launch_bounds__(kBlock) k_p2p_f
                                               out + n + t0);
 }
 
-// ----------------------------------------------------------------- near field (cell list)
+// ----------------------------------------------------------------- near field
 
+// Cell list of a band (near.hip): cells in lexicographic order, the nodes of a cell in
+// increasing index, with their positions (and h³ω/4π's ω in w) in the same order.
 struct CellsDev {
-  const int64_t* start;  // ncell + 1
-  const int* nodes;      // n, sorted within each cell
-  const int* cell_of;    // n
+  const int* start;     // ncell + 1
+  const int* nodes;     // n
+  const int* cell_of;   // n
+  const double4* pos;   // n, cell order
   int ncx, ncy, ncz;
+  double inv;           // 1 / cell width
 };
 
-static __global__ void __attribute__((unused)) __launch_bounds__(kBlock) k_bbox(int n, BandDev b, double* __restrict__ out /*6 per block*/) {
-  __shared__ double s[6][kBlock];
-  double v[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
-  for (int j = blockIdx.x * kBlock + threadIdx.x; j < n; j += gridDim.x * kBlock) {
-    v[0] = fmin(v[0], b.px[j]); v[1] = fmin(v[1], b.py[j]); v[2] = fmin(v[2], b.pz[j]);
-    v[3] = fmax(v[3], b.px[j]); v[4] = fmax(v[4], b.py[j]); v[5] = fmax(v[5], b.pz[j]);
-  }
-  for (int q = 0; q < 6; ++q) s[q][threadIdx.x] = v[q];
-  __syncthreads();
-  for (int off = kBlock / 2; off > 0; off >>= 1) {
-    if (threadIdx.x < off)
-      for (int q = 0; q < 6; ++q)
-        s[q][threadIdx.x] = q < 3 ? fmin(s[q][threadIdx.x], s[q][threadIdx.x + off])
-                                  : fmax(s[q][threadIdx.x], s[q][threadIdx.x + off]);
-    __syncthreads();
-  }
-  if (threadIdx.x == 0)
-    for (int q = 0; q < 6; ++q) out[6 * blockIdx.x + q] = s[q][0];
+inline CellsDev cells_dev(const MixedPlan& P) {
+  return CellsDev{P.cell_start, P.cell_nodes, P.cell_of, P.cell_pos, P.ncx, P.ncy, P.ncz, 1.0 / P.cell};
 }
 
-static __global__ void __attribute__((unused)) __launch_bounds__(kBlock) k_cell_count(int n, BandDev b, double lx, double ly, double lz,
-                                                       double inv_cell, int ncx, int ncy, int ncz,
-                                                       int* __restrict__ cell_of, int64_t* __restrict__ counts) {
-  int j = blockIdx.x * kBlock + threadIdx.x;
-  if (j >= n) return;
-  int cx = min(ncx - 1, max(0, (int)((b.px[j] - lx) * inv_cell)));
-  int cy = min(ncy - 1, max(0, (int)((b.py[j] - ly) * inv_cell)));
-  int cz = min(ncz - 1, max(0, (int)((b.pz[j] - lz) * inv_cell)));
-  int c = (cx * ncy + cy) * ncz + cz;
-  cell_of[j] = c;
-  atomicAdd((unsigned long long*)&counts[c], 1ull);
-}
-
-static __global__ void __attribute__((unused)) __launch_bounds__(kBlock) k_cell_fill(int n, const int* __restrict__ cell_of,
-                                                      const int64_t* __restrict__ start, int* __restrict__ cursor,
-                                                      int* __restrict__ nodes) {
-  int j = blockIdx.x * kBlock + threadIdx.x;
-  if (j >= n) return;
-  int c = cell_of[j];
-  int slot = atomicAdd(&cursor[c], 1);
-  nodes[start[c] + slot] = j;
-}
-
-// Insertion sort of each cell's node list, so the near-field sums run in a fixed order.
-static __global__ void __attribute__((unused)) __launch_bounds__(kBlock) k_cell_sort(int64_t ncell, const int64_t* __restrict__ start,
-                                                      int* __restrict__ nodes) {
-  int64_t c = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (c >= ncell) return;
-  int64_t s = start[c], e = start[c + 1];
-  for (int64_t q = s + 1; q < e; ++q) {
-    int v = nodes[q];
-    int64_t t = q - 1;
-    while (t >= s && nodes[t] > v) {
-      nodes[t + 1] = nodes[t];
-      --t;
-    }
-    nodes[t + 1] = v;
-  }
-}
-
-// Visits the near sources of target i (FP32 distance below r_c) in a fixed order: the 27
-// neighbouring cells in lexicographic order, each cell's nodes in increasing index. One
-// wave per target: the lanes test a cell's candidates 64 at a time and a ballot numbers the
-// hits in that order; f(j, slot) runs on each hit lane, and the wave's hit count returns.
-template <typename F>
-__device__ __forceinline__ int64_t for_near_wave(int i, const float4* __restrict__ A, const CellsDev& cells,
-                                                 float rc2, F f) {
+// The 27 cells around cell c are nine runs of cells contiguous in z, so nine contiguous ranges
+// of the cell-ordered arrays: lane r < 9 of the wave gets range r (empty outside the grid), in
+// lexicographic cell order.
+__device__ __forceinline__ void cell_ranges(const CellsDev& cells, int c, int& lo, int& hi) {
   const int lane = threadIdx.x & 63;
-  const float4 ta = A[i];
-  const int c = cells.cell_of[i];
   const int cz = c % cells.ncz, cy = (c / cells.ncz) % cells.ncy, cx = c / (cells.ncz * cells.ncy);
-  int64_t base = 0;
-  for (int ax = max(cx - 1, 0); ax <= min(cx + 1, cells.ncx - 1); ++ax)
-    for (int ay = max(cy - 1, 0); ay <= min(cy + 1, cells.ncy - 1); ++ay)
-      for (int az = max(cz - 1, 0); az <= min(cz + 1, cells.ncz - 1); ++az) {
-        const int cc = (ax * cells.ncy + ay) * cells.ncz + az;
-        const int64_t e = cells.start[cc + 1];
-        for (int64_t q0 = cells.start[cc]; q0 < e; q0 += 64) {
-          const int64_t q = q0 + lane;
-          int j = -1;
-          bool hit = false;
-          if (q < e) {
-            j = cells.nodes[q];
-            const float4 sa = A[j];
-            hit = r2_f32(ta.x, ta.y, ta.z, sa.x, sa.y, sa.z) < rc2;
-          }
-          const unsigned long long mask = __ballot(hit);
-          if (hit) f(j, base + __popcll(mask & ((1ull << lane) - 1ull)));
-          base += __popcll(mask);
-        }
-      }
-  return base;
-}
-
-constexpr int kNearWaves = kBlock / 64;  // targets per block of the near-list kernels
-
-static __global__ void __attribute__((unused)) __launch_bounds__(kBlock) k_near_count(int n, const float4* __restrict__ A, CellsDev cells, float rc2,
-                                                       int64_t* __restrict__ counts) {
-  const int i = blockIdx.x * kNearWaves + (threadIdx.x >> 6);
-  if (i >= n) return;
-  const int64_t c = for_near_wave(i, A, cells, rc2, [&](int, int64_t) {});
-  if ((threadIdx.x & 63) == 0) counts[i] = c;
-}
-
-// Near-field block matrix: for each near pair the FP64 coefficients of
-//   y1_i += c0 ψ_j + c1 ψn_j,  y2_i += c2 ψ_j + c3 ψn_j,  with s_j = h³ω_j/(4π)
-//   c0 = 4πK11 s_j, c1 = −4πK12 s_j, c2 = 4πK21 s_j, c3 = −4πK22 s_j.
-// The coefficients depend on geometry only, so they are built once per band.
-static __global__ void __attribute__((unused)) __launch_bounds__(kBlock) k_near_fill(int n, BandDev b, const double* __restrict__ w, double scale,
-                                                      const float4* __restrict__ A, CellsDev cells, float rc2,
-                                                      KParams kp, const int64_t* __restrict__ row,
-                                                      int* __restrict__ col, double4* __restrict__ coef) {
-  const int i = blockIdx.x * kNearWaves + (threadIdx.x >> 6);
-  if (i >= n) return;
-  const double xi = b.px[i], yi = b.py[i], zi = b.pz[i], nxi = b.nx[i], nyi = b.ny[i], nzi = b.nz[i];
-  const double ci = b.curv ? b.curv[i] : 0.0;
-  const int64_t r0 = row[i];
-  // the columns first (a few hits per 64 candidates), then the FP64 coefficients with every
-  // lane busy: entry q = r0 + lane, r0 + lane + 64, ... reads back the column its wave wrote
-  const int64_t cnt = for_near_wave(i, A, cells, rc2, [&](int j, int64_t slot) { col[r0 + slot] = j; });
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  for (int64_t q = r0 + (threadIdx.x & 63); q < r0 + cnt; q += 64) {
-    const int j = col[q];
-    double k[4];
-    kern4_f64(xi, yi, zi, nxi, nyi, nzi, b.px[j], b.py[j], b.pz[j], b.nx[j], b.ny[j], b.nz[j], kp, ci, k);
-    const double sj = scale * w[j];
-    coef[q] = make_double4(k[0] * sj, -k[1] * sj, k[2] * sj, -k[3] * sj);
+  const int ax = cx - 1 + lane / 3, ay = cy - 1 + lane % 3;
+  lo = hi = 0;
+  if (lane < 9 && ax >= 0 && ax < cells.ncx && ay >= 0 && ay < cells.ncy) {
+    const int line = (ax * cells.ncy + ay) * cells.ncz;
+    lo = cells.start[line + max(cz - 1, 0)];
+    hi = cells.start[line + min(cz + 1, cells.ncz - 1) + 1];
   }
 }
 

@@ -64,6 +64,10 @@ struct MixedPlan {
   int* col = nullptr;
   double4* coef = nullptr;
   int far_cfg = 0;                // far-field tile shape chosen by the autotuner
+  const int* cell_start = nullptr;  // cell list (see CellsDev)
+  const int* cell_nodes = nullptr;
+  const int* cell_of = nullptr;
+  const double4* cell_pos = nullptr;
 };
 
 // Treecode far field of the mixed operator for one band (tree.hip): octree over the FP32
@@ -130,6 +134,7 @@ struct pb_ctx {
   hipStream_t batch_stream = nullptr;  // capture stream of the batched solve
   const void* nn_key = nullptr;        // band prepared for the learned preconditioner
   int64_t nn_n = 0;
+  bool nn_rev = false;                 // the reverse lists belong to the neighbour lists last prepared
   // Device flag read by the operator's heavy kernels (far field, FP64 pairs, treecode,
   // network layers): while GMRES runs one Arnoldi step ahead of its convergence test, a
   // step enqueued after the test has been met finds the flag set and does no work.
@@ -137,6 +142,8 @@ struct pb_ctx {
   const int* skip = nullptr;
   int* host_state = nullptr;      // pinned host slots of the per-step GMRES state (2 ints per step)
   int* host_state_dev = nullptr;  // the same memory as the device addresses it
+  double* host_pin = nullptr;     // pinned host slots for small results (kHostPin doubles)
+  double* host_pin_dev = nullptr;
   // status of the last allocation/launch
   pb_status fail(pb_status s, const char* fmt, ...);
 };
@@ -170,8 +177,15 @@ pb_status sync(pb_ctx* ctx, const char* where);
 pb_status launch_ok(pb_ctx* ctx, const char* where);
 
 // Scans and reductions shared by the stages.
-// Exclusive scan of n int64 values in place on the context stream; returns the total on host.
+// Exclusive scan of n values in place on the context stream; returns the total on host (after
+// a stream synchronization) when asked for.
 pb_status exclusive_scan_i64(pb_ctx* ctx, int64_t* data, int64_t n, int64_t* total_host);
+pb_status exclusive_scan_i32(pb_ctx* ctx, int* data, int64_t n);
+
+// Pinned, mapped host memory through which kernels hand small results to the host without a
+// copy: written by kernels, read after a stream synchronization. Allocated on first use.
+constexpr int kHostPin = 2048;
+pb_status host_pin(pb_ctx* ctx);
 
 // Operator internals used by the solver.
 pb_status matvec_fp64(pb_ctx* ctx, const pb_band* band, const Derived& d, const double* p, double* y);
