@@ -207,16 +207,16 @@ pb_status pb_ibim_rhs(pb_ctx* ctx, const pb_band* band, const double* atoms, int
    regularization subsection, h³ and ω folded in. precision PB_FP64 or PB_MIXED.
    p, y: device, 2n; they must not overlap.
    PB_MIXED: FP32 far field + FP64 near field (every pair closer than r_c, the regularized
-   ones included). The far-field kernel is chosen once per band size (per batch shape in
-   pb_ibim_solve_batched) by timing the candidates (bands of 262,144 nodes or more take the
-   symmetric kernel without timing); the environment variable PB_FAR_CFG=k
+   ones included). The far-field kernel is chosen by the band's size: symmetric from 12,800
+   nodes on (16,384 with kappa = 0), one-directional below (pb_ibim_solve_batched chooses once per
+   batch shape by timing the candidates); the environment variable PB_FAR_CFG=k
    fixes it instead: k = 0..3 the one-directional kernel with (sources per LDS tile, targets
    per lane) = (256, 1), (512, 1), (256, 2), (512, 2); k = 4 the symmetric kernel (each
    unordered pair evaluated once for both directions). All give the same operator up to
    FP32 rounding; each is bitwise reproducible from run to run.
-   PB_FP64: the same choice between the one-directional kernel (PB_F64_CFG=0) and the
-   symmetric one (PB_F64_CFG=1), which evaluates the regularization test per direction and
-   skips it on sub-block pairs too far apart for any pair to be regularized. */
+   PB_FP64: the symmetric kernel, which evaluates the regularization test per direction and
+   skips it on sub-block pairs too far apart for any pair to be regularized; PB_F64_CFG=0 asks for
+   the one-directional one. */
 pb_status pb_ibim_matvec(pb_ctx* ctx, const pb_band* band, const pb_params* prm, int precision, const double* p,
                          double* y);
 
@@ -337,8 +337,8 @@ pb_status pb_nn_geometry(pb_ctx* ctx, const pb_band* band, int* nbr_host, float*
 pb_status pb_set_timing(pb_ctx* ctx, int enable);
 pb_status pb_kernel_time(pb_ctx* ctx, const char* name, double* total_ms, int64_t* launches);
 
-/* The far-field kernel the mixed operator uses for bands of n nodes on this context (the
-   autotuner's choice or PB_FAR_CFG; see pb_ibim_matvec): *cfg = 0..3 the one-directional
+/* The far-field kernel the mixed operator last used for bands of n nodes on this context (the
+   rule's choice or PB_FAR_CFG; see pb_ibim_matvec): *cfg = 0..3 the one-directional
    kernel, 4 the symmetric one. PB_EINVAL if no mixed operator was applied to a band of that
    size yet. */
 pb_status pb_far_kernel(pb_ctx* ctx, int64_t n, int* cfg);

@@ -126,7 +126,7 @@ static __global__ void __launch_bounds__(kBlock) k_far32_sym_batch(const Item* _
                                                                    const int* __restrict__ active, F32Params fp,
                                                                    double sig1, double sig2,
                                                                    double* __restrict__ partial) {
-  __shared__ SymShared sh;
+  __shared__ SymShared<4, 1> sh;
   for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
     const Item w = items[it];
     if (!active[w.mol]) continue;
@@ -143,7 +143,7 @@ static __global__ void __launch_bounds__(kBlock) k_far64_sym_batch(const Item* _
                                                                    const double* __restrict__ wpsi,
                                                                    const double* __restrict__ wpsn, KParams kp,
                                                                    double k2, double* __restrict__ partial) {
-  __shared__ Sym64Shared sh;
+  __shared__ Sym64Shared<4, 1> sh;
   for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
     const Item w = items[it];
     if (!active[w.mol]) continue;

@@ -10,9 +10,8 @@
 // Both sides decide "near" with the same FP32 function of the same FP32 records, so each pair
 // is counted exactly once. The near matrix depends only on the geometry and is built once per
 // band; each application is then an SpMV. The far kernel's tile shape (sources per LDS tile,
-// targets per lane) is chosen per band size by timing the candidates once (autotuner); the
-// symmetric kernel (each unordered pair once, both directions) is one of the candidates. The
-// near-field matrix and its cell list are built in near.hip.
+// targets per lane) or the symmetric kernel (each unordered pair once, both directions) is chosen by
+// the band's size (far_choice). The near-field matrix and its cell list are built in near.hip.
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
@@ -34,31 +33,52 @@ constexpr int kNumTiled = sizeof(kFarCfgs) / sizeof(kFarCfgs[0]);
 constexpr int kSymCfg = kNumTiled;  // the symmetric kernel
 constexpr int kNumFarCfgs = kNumTiled + 1;
 
-// Work items (Ic, Jc), Ic ≤ Jc, of the symmetric kernel for a band of n nodes: off-diagonal
-// chunk pairs first (they cost the most), the diagonal ones last.
-std::vector<int2> sym_items(int n) {
-  const int nc = sym_chunks(n);
+// Tiles of the symmetric kernels for a band of n nodes: F nodes per tile (512, 256 or 128: blocks of
+// 4 × 1, 2 × 2 or 1 × 2 waves), chunks of nsub tiles. Small bands take small tiles: tiles of 512 give
+// (n/512)²/2 blocks, too few for 256 CUs below about 40,000 nodes and in few, uneven rounds. Measured
+// far-field times, tiles of 512 / 256 / 128: FP32 at 13,393 nodes 148 / 110 / 111 µs, at 33,866
+// nodes 559 / 565 / 572, at 45,818 nodes 964 / 1021 / 1115; FP64 at 8725 nodes 356 / 192 / 170 µs,
+// at 20,424 nodes 811 / 609 / 653, at 55,111 nodes 3947 / 3879 / –, at 105,085 nodes equal.
+struct SymShape {
+  int F, nsub, chunks;
+};
+SymShape sym_shape(int n, bool f64) {
+  const int F = f64 ? (n < 10240 ? 128 : n < 61440 ? 256 : 512) : (n < 32768 ? 256 : 512);
+  const int C = F == kSymSub ? F * sym_nsub(n) : F;
+  return {F, C / F, (n + C - 1) / C};
+}
+
+// Work items (Ic, Jc) of a symmetric kernel: chunk pairs of different sub-blocks (Ic < Jc) first,
+// then those within a sub-block, which are one-directional (both orders).
+std::vector<int2> sym_items(const SymShape& sh) {
+  const int nc = sh.chunks, per = std::max(1, kSymSub / (sh.F * sh.nsub));
   std::vector<int2> v;
-  v.reserve((size_t)nc * (nc + 1) / 2);
+  v.reserve((size_t)nc * (nc + 1) / 2 + (size_t)nc * per);
   for (int i = 0; i < nc; ++i)
-    for (int j = i + 1; j < nc; ++j) v.push_back(make_int2(i, j));
-  for (int i = 0; i < nc; ++i) v.push_back(make_int2(i, i));
+    for (int j = (i / per + 1) * per; j < nc; ++j) v.push_back(make_int2(i, j));
+  for (int i = 0; i < nc; ++i)
+    for (int j = i / per * per; j < std::min(nc, (i / per + 1) * per); ++j) v.push_back(make_int2(i, j));
   return v;
 }
 
-// The item list on the device for a band of n nodes (rebuilt when n changes).
-const int2* sym_items_dev(pb_ctx* ctx, int n, int* n_items) {
-  const std::vector<int2> v = sym_items(n);
-  int2* d = (int2*)workspace(ctx, "sym_items", sizeof(int2) * v.size());
-  if (!d) return nullptr;
-  if (ctx->sym_items_n != n) {
-    if (hipMemcpyAsync(d, v.data(), sizeof(int2) * v.size(), hipMemcpyHostToDevice, ctx->stream) != hipSuccess)
+// The item list on the device for a band of n nodes (rebuilt when n changes; one list per tile
+// size).
+const int2* sym_items_dev(pb_ctx* ctx, int n, const SymShape& sh, int* n_items) {
+  char nm[32];
+  snprintf(nm, sizeof(nm), "sym_items%d", sh.F);
+  pb_ctx::SymList& l = ctx->sym_list[sh.F];
+  if (l.n != n) {
+    l.n = -1;
+    const std::vector<int2> v = sym_items(sh);
+    int2* d = (int2*)workspace(ctx, nm, sizeof(int2) * v.size());
+    if (!d || hipMemcpyAsync(d, v.data(), sizeof(int2) * v.size(), hipMemcpyHostToDevice, ctx->stream) != hipSuccess)
       return nullptr;
-    ctx->sym_items_n = n;
-    ctx->sym_n_items = (int)v.size();
+    l.n = n;
+    l.n_items = (int)v.size();
+    l.dev = d;
   }
-  *n_items = ctx->sym_n_items;
-  return d;
+  *n_items = l.n_items;
+  return l.dev;
 }
 
 // Source chunks for a launch: at least ~8 blocks per CU, chunks a multiple of the tile.
@@ -90,16 +110,15 @@ int launch_far(pb_ctx* ctx, int cfg, bool screened, const float4* A, const float
                const float4* box, int n, const F32Params& fp, double sig1, double sig2, double* partial,
                const int* skip) {
   if (cfg == kSymCfg) {
+    const SymShape sh = sym_shape(n, false);
     int n_items = 0;
-    const int2* items = sym_items_dev(ctx, n, &n_items);
+    const int2* items = sym_items_dev(ctx, n, sh, &n_items);
     if (!items) return -1;
-    if (screened)
-      k_p2p_f32_sym<true><<<(unsigned)n_items, kBlock, 0, ctx->stream>>>(A, N, box, n, sym_nsub(n), items,
-                                                                          n_items, fp, sig1, sig2, partial, skip);
-    else
-      k_p2p_f32_sym<false><<<(unsigned)n_items, kBlock, 0, ctx->stream>>>(A, N, box, n, sym_nsub(n), items,
-                                                                           n_items, fp, sig1, sig2, partial, skip);
-    return sym_chunks(n);
+    auto k = sh.F == 512 ? (screened ? k_p2p_f32_sym<true, 4, 1> : k_p2p_f32_sym<false, 4, 1>)
+                         : (screened ? k_p2p_f32_sym<true, 2, 2> : k_p2p_f32_sym<false, 2, 2>);
+    k<<<(unsigned)n_items, kBlock, 0, ctx->stream>>>(A, N, box, n, sh.nsub, items, n_items, fp, sig1, sig2, partial,
+                                                     skip);
+    return sh.chunks;
   }
   switch (cfg) {
     case 0: return launch_far_t<256, 1>(ctx, screened, A, M, N, box, n, fp, sig1, sig2, partial, skip);
@@ -110,7 +129,7 @@ int launch_far(pb_ctx* ctx, int cfg, bool screened, const float4* A, const float
 }
 
 int far_max_chunks(pb_ctx* ctx, int n) {
-  int m = sym_chunks(n), c = 0;
+  int m = sym_shape(n, false).chunks, c = 0;
   for (int k = 0; k < kNumTiled; ++k)
     m = std::max(m, far_chunks(ctx, n, kBlock * kFarCfgs[k].tpl, kFarCfgs[k].tile, &c));
   return m;
@@ -118,59 +137,19 @@ int far_max_chunks(pb_ctx* ctx, int n) {
 
 }  // namespace
 
-// Bands from this size on take the symmetric kernels without timing: they were the faster
-// ones at every band size timed (3281 to 638,391 nodes; 1.7× for FP32 and 1.8× for FP64 at
-// the largest), and one timed one-directional launch costs seconds at millions of nodes.
-constexpr int kTuneMaxN = 1 << 18;
-
-// Picks the far-field tile shape for a band of n nodes by timing each candidate once on the
-// packed records (after one warm-up launch); the choice is cached per n on the context.
-// PB_FAR_CFG=<index> in the environment fixes the choice instead.
-pb_status far_autotune(pb_ctx* ctx, int n, bool screened, const float4* A, const float4* M, const float4* N,
-                       const float4* box, const F32Params& fp, double* partial, int* cfg_out) {
-  auto it = ctx->far_cfg.find(n);
-  if (it != ctx->far_cfg.end()) {
-    *cfg_out = it->second;
-    return PB_OK;
-  }
+// The far-field kernel of a band of n nodes: symmetric from 12,800 nodes on (16,384 unscreened, whose
+// pairs are cheaper), one-directional in tiles of 256 below. At 2924 nodes the two take 28 and 33 µs,
+// at 8725 nodes 85 and 65, at 12,056 nodes 158 and 99: the line lies above where the symmetric
+// kernel's small tiles overtake, at the size where its tiles of 512 did, since the two group their FP32
+// partial sums differently (about 2e-8 of the result) and the operator keeps its values. A fixed
+// rule, so that the operator does not depend on timing. PB_FAR_CFG=<index> in the environment fixes the choice instead.
+int far_choice(pb_ctx* ctx, int n, bool screened) {
+  int cfg = n < (screened ? 12800 : 16384) ? 0 : kSymCfg;
   if (const char* env = std::getenv("PB_FAR_CFG")) {
-    int c = std::atoi(env);
-    if (c >= 0 && c < kNumFarCfgs) {
-      ctx->far_cfg[n] = c;
-      *cfg_out = c;
-      return PB_OK;
-    }
+    const int c = std::atoi(env);
+    if (c >= 0 && c < kNumFarCfgs) cfg = c;
   }
-  if (n >= kTuneMaxN) {
-    ctx->far_cfg[n] = kSymCfg;
-    *cfg_out = kSymCfg;
-    return PB_OK;
-  }
-  hipEvent_t e0, e1;
-  PB_HIP(ctx, hipEventCreate(&e0));
-  PB_HIP(ctx, hipEventCreate(&e1));
-  int best = 0;
-  float best_ms = 1e30f;
-  for (int c = 0; c < kNumFarCfgs; ++c) {
-    if (launch_far(ctx, c, screened, A, M, N, box, n, fp, 1.0, 1.0, partial, nullptr) < 0)
-      return ctx->fail(PB_ENOMEM, "far-field work list");
-    PB_HIP(ctx, hipEventRecord(e0, ctx->stream));
-    launch_far(ctx, c, screened, A, M, N, box, n, fp, 1.0, 1.0, partial, nullptr);
-    PB_HIP(ctx, hipEventRecord(e1, ctx->stream));
-    PB_TRY(launch_ok(ctx, "far autotune"));
-    PB_HIP(ctx, hipEventSynchronize(e1));
-    float ms = 0.f;
-    PB_HIP(ctx, hipEventElapsedTime(&ms, e0, e1));
-    if (ms < best_ms) {
-      best_ms = ms;
-      best = c;
-    }
-  }
-  (void)hipEventDestroy(e0);
-  (void)hipEventDestroy(e1);
-  ctx->far_cfg[n] = best;
-  *cfg_out = best;
-  return PB_OK;
+  return ctx->far_cfg[n] = cfg;  // kept for pb_far_kernel
 }
 
 namespace {
@@ -180,12 +159,14 @@ int launch_f64(pb_ctx* ctx, int cfg, const pb_band* band, const double* wpsi, co
                double* partial, const int* skip) {
   const int n = (int)band->n;
   if (cfg == 1) {
+    const SymShape sh = sym_shape(n, true);
     int n_items = 0;
-    const int2* items = sym_items_dev(ctx, n, &n_items);
+    const int2* items = sym_items_dev(ctx, n, sh, &n_items);
     if (!items) return -1;
-    k_p2p_f64_sym<<<(unsigned)n_items, kBlock, 0, ctx->stream>>>(band_dev(band), wpsi, wpsn, n, sym_nsub(n), items,
-                                                                 n_items, kp, kp.kappa * kp.kappa, partial, skip);
-    return sym_chunks(n);
+    auto k = sh.F == 512 ? k_p2p_f64_sym<4, 1> : sh.F == 256 ? k_p2p_f64_sym<2, 2> : k_p2p_f64_sym<1, 2>;
+    k<<<(unsigned)n_items, sh.F == 128 ? 128 : 256, 0, ctx->stream>>>(band_dev(band), wpsi, wpsn, n, sh.nsub, items,
+                                                                      n_items, kp, kp.kappa * kp.kappa, partial, skip);
+    return sh.chunks;
   }
   int chunk = 0;
   const int S = far_chunks(ctx, n, kBlock, kBlock, &chunk);
@@ -195,52 +176,13 @@ int launch_f64(pb_ctx* ctx, int cfg, const pb_band* band, const double* wpsi, co
   return S;
 }
 
-// The FP64 kernel for bands of n nodes: timed once per n (PB_F64_CFG=<0|1> fixes it).
-pb_status f64_autotune(pb_ctx* ctx, const pb_band* band, const double* wpsi, const double* wpsn, const KParams& kp,
-                       double* partial, int* cfg_out) {
-  const int n = (int)band->n;
-  auto it = ctx->f64_cfg.find(n);
-  if (it != ctx->f64_cfg.end()) {
-    *cfg_out = it->second;
-    return PB_OK;
-  }
-  if (const char* env = std::getenv("PB_F64_CFG")) {
-    const int c = std::atoi(env);
-    if (c == 0 || c == 1) {
-      ctx->f64_cfg[n] = c;
-      *cfg_out = c;
-      return PB_OK;
-    }
-  }
-  if (n >= kTuneMaxN) {
-    ctx->f64_cfg[n] = 1;
-    *cfg_out = 1;
-    return PB_OK;
-  }
-  hipEvent_t e0, e1;
-  PB_HIP(ctx, hipEventCreate(&e0));
-  PB_HIP(ctx, hipEventCreate(&e1));
-  int best = 0;
-  float best_ms = 1e30f;
-  for (int c = 0; c < 2; ++c) {
-    PB_HIP(ctx, hipEventRecord(e0, ctx->stream));
-    if (launch_f64(ctx, c, band, wpsi, wpsn, kp, partial, nullptr) < 0)
-      return ctx->fail(PB_ENOMEM, "FP64 work list");
-    PB_HIP(ctx, hipEventRecord(e1, ctx->stream));
-    PB_TRY(launch_ok(ctx, "f64 autotune"));
-    PB_HIP(ctx, hipEventSynchronize(e1));
-    float ms = 0.f;
-    PB_HIP(ctx, hipEventElapsedTime(&ms, e0, e1));
-    if (ms < best_ms) {
-      best_ms = ms;
-      best = c;
-    }
-  }
-  (void)hipEventDestroy(e0);
-  (void)hipEventDestroy(e1);
-  ctx->f64_cfg[n] = best;
-  *cfg_out = best;
-  return PB_OK;
+// The FP64 kernel: the symmetric one, which is faster at every size (2924
+// nodes: 70 against 91 µs; 45,818 nodes: 2.74 against 6.19 ms), unless PB_F64_CFG=0 asks for the
+// one-directional one or the curvature-corrected averages need it.
+int f64_choice(bool curved) {
+  if (curved) return 0;
+  const char* env = std::getenv("PB_F64_CFG");
+  return env && !std::strcmp(env, "0") ? 0 : 1;
 }
 
 }  // namespace
@@ -248,7 +190,7 @@ pb_status f64_autotune(pb_ctx* ctx, const pb_band* band, const double* wpsi, con
 pb_status matvec_fp64(pb_ctx* ctx, const pb_band* band, const Derived& d, const double* p, double* y) {
   const int n = (int)band->n;
   int chunk = 0;
-  const int S64 = std::max(far_chunks(ctx, n, kBlock, kBlock, &chunk), sym_chunks(n));
+  const int S64 = std::max(far_chunks(ctx, n, kBlock, kBlock, &chunk), sym_shape(n, true).chunks);
   double* wpsi = (double*)workspace(ctx, "mv_wpsi", sizeof(double) * n);
   double* wpsn = (double*)workspace(ctx, "mv_wpsn", sizeof(double) * n);
   double* partial = (double*)workspace(ctx, "mv_partial64", sizeof(double) * 2 * (size_t)n * S64);
@@ -256,8 +198,7 @@ pb_status matvec_fp64(pb_ctx* ctx, const pb_band* band, const Derived& d, const 
   const unsigned nb = (unsigned)((n + kBlock - 1) / kBlock);
   k_weights_f64<<<nb, kBlock, 0, ctx->stream>>>(n, band->w, p, d.h3 / (4.0 * kPi), wpsi, wpsn);
   const KParams kp = kparams(d);
-  int cfg = 0;  // the symmetric kernel takes the paper's disc averages only
-  if (!d.curved) PB_TRY(f64_autotune(ctx, band, wpsi, wpsn, kp, partial, &cfg));
+  const int cfg = f64_choice(d.curved);
   int S = 0;
   {
     Scope t(ctx, "p2p_f64");
@@ -282,14 +223,8 @@ pb_status mixed_prepare(pb_ctx* ctx, const pb_band* band, const Derived& d) {
   PB_TRY(near_build(ctx, band, d, "mx_", ctx->mixed));
   const int n = (int)band->n;
   MixedPlan& P = ctx->mixed;
-  double* partial = (double*)workspace(ctx, "mv_partial", sizeof(double) * 2 * (size_t)n * far_max_chunks(ctx, n));
-  if (!partial) return PB_ENOMEM;
-  if (!ctx->far_cfg.count(n)) {  // records (weights zero) for the candidates' timing
-    k_pack_f32<<<(unsigned)((n + kBlock - 1) / kBlock), kBlock, 0, ctx->stream>>>(
-        n, band_dev(band), band->w, nullptr, 0.0, P.cx, P.cy, P.cz, P.sigma, P.A, P.M, P.N);
-    PB_TRY(launch_ok(ctx, "pack"));
-  }
-  return far_autotune(ctx, n, d.kappa > 0.0, P.A, P.M, P.N, P.box, f32params(d, P.sigma), partial, &P.far_cfg);
+  P.far_cfg = far_choice(ctx, n, d.kappa > 0.0);
+  return PB_OK;
 }
 
 pb_status matvec_mixed(pb_ctx* ctx, const pb_band* band, const Derived& d, const double* p, double* y) {

@@ -175,9 +175,9 @@ __device__ __forceinline__ void far_tile_loop(const float4* __restrict__ A, cons
                                               int t_end, int j0, int j1, const F32Params& fp, double sig1,
                                               double sig2, float4* sA, float4* sM, double* __restrict__ out1,
                                               double* __restrict__ out2) {
-  static_assert(TILE % kGroup == 0 && (kBlk * TPL) % kGroup == 0, "tiles are whole groups");
+  static_assert(TILE % kGroup == 0, "source tiles are whole groups");
   float4 tlo, thi;
-  box_union(box, t0 / kGroup, min(t0 + kBlk * TPL, t_end + kGroup - 1) / kGroup, tlo, thi);
+  box_union(box, t0 / kGroup, (min(t0 + kBlk * TPL, t_end) - 1) / kGroup + 1, tlo, thi);
   float4 ta[TPL], tn[TPL];
 #pragma unroll
   for (int t = 0; t < TPL; ++t) {

@@ -63,7 +63,7 @@ struct MixedPlan {
   int64_t* row = nullptr;         // near-field CSR
   int* col = nullptr;
   double4* coef = nullptr;
-  int far_cfg = 0;                // far-field tile shape chosen by the autotuner
+  int far_cfg = 0;                // far-field kernel (far_choice)
   const int* cell_start = nullptr;  // cell list (see CellsDev)
   const int* cell_nodes = nullptr;
   const int* cell_of = nullptr;
@@ -125,11 +125,13 @@ struct pb_ctx {
   pb::MixedPlan mixed;
   pb::TreePlan tree;       // PB_TREE operator (and the inner operator of PB_TREE solves)
   pb::TreePlan tree_fine;  // residual operator of PB_TREE solves on large bands
-  std::map<int, int> far_cfg;          // autotuned far-field tile shape per band size
-  std::map<int, int> f64_cfg;          // FP64 operator kernel per band size (0 tiled, 1 symmetric)
-  int sym_items_n = -1;                // band size the symmetric kernel's item list was built for
-  int sym_n_items = 0;
-  std::map<int64_t, int> batch_cfg;    // the same for batches, per (nodes, molecules)
+  std::map<int, int> far_cfg;          // far-field kernel last used per band size
+  struct SymList {
+    int n = -1, n_items = 0;           // band size the list was built for
+    const int2* dev = nullptr;
+  };
+  std::map<int, SymList> sym_list;     // item lists of the symmetric kernels per tile size
+  std::map<int64_t, int> batch_cfg;    // autotuned far-field kernel for batches, per (nodes, molecules)
   std::map<int64_t, int> batch_cfg64;  // FP64 operator kernel for batches (0 tiled, 1 symmetric)
   hipStream_t batch_stream = nullptr;  // capture stream of the batched solve
   const void* nn_key = nullptr;        // band prepared for the learned preconditioner

@@ -33,15 +33,22 @@
 
 namespace pb {
 
+// Block shape as in SymShared (TW waves of 128 targets, SW waves sharing the sources); a tile's
+// sources are staged kStage at a time, doubled per group of 64 like the FP32 kernel's.
+template <int TW, int SW>
 struct Sym64Shared {
-  double2 s0[kSymSub], s1[kSymSub], s2[kSymSub], s3[kSymSub];  // (x, y), (z, nx), (ny, nz), (wψ, wψn)
-  double racc[kSymWaves][2][64];  // one 64-source group's reverse sums per wave
-  double box[kSymWaves][6];  // per-wave bounding boxes (lo xyz, hi xyz) of a block reduction
+  static constexpr int F = 128 * TW, kThreads = 64 * TW * SW, kStage = F < 256 ? F : 256, kSrc = kStage / SW;
+  static_assert(kSrc % 64 == 0, "whole groups of sources per wave");
+  double2 s0[2 * kStage], s1[2 * kStage], s2[2 * kStage], s3[2 * kStage];  // (x, y), (z, nx), (ny, nz), (wψ, wψn)
+  double racc[TW][2][kStage];
+  double box[TW * SW][6];  // per-wave bounding boxes (lo xyz, hi xyz) of a block reduction
+  double fsum[SW > 1 ? (SW - 1) * TW * 64 * 4 : 1];  // forward sums of the waves ws > 0
 };
 
 // Bounding box over the block: each thread passes the box of its own points (empty: +∞/−∞);
 // every thread gets the block's. Every thread of the block calls it (it synchronizes).
-__device__ __forceinline__ void block_box(double (&lo)[3], double (&hi)[3], Sym64Shared& sh) {
+template <int TW, int SW>
+__device__ __forceinline__ void block_box(double (&lo)[3], double (&hi)[3], Sym64Shared<TW, SW>& sh) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   for (int off = 32; off > 0; off >>= 1)
     for (int c = 0; c < 3; ++c) {
@@ -57,7 +64,7 @@ __device__ __forceinline__ void block_box(double (&lo)[3], double (&hi)[3], Sym6
   for (int c = 0; c < 3; ++c) {
     lo[c] = sh.box[0][c];
     hi[c] = sh.box[0][3 + c];
-    for (int v = 1; v < kSymWaves; ++v) {
+    for (int v = 1; v < TW * SW; ++v) {
       lo[c] = fmin(lo[c], sh.box[v][c]);
       hi[c] = fmax(hi[c], sh.box[v][3 + c]);
     }
@@ -162,19 +169,20 @@ __device__ __forceinline__ double shfl_next(double v, int addr) {
   return __hiloint2double(hi, lo);
 }
 
-// One 64-source group g of sym64_block's pair loop: both directions of every pair between the
-// thread's two targets and sources g..g+63; forward sums into f, the wave's reverse sums of the
-// group into sh.racc[w][·][0..63].
-template <int kMetric, bool kFar>
+// One 64-source group g of a stage: both directions of every pair between the thread's two
+// targets and sources g..g+63; forward sums into f, the wave's reverse sums into
+// sh.racc[wt][·][g..g+63].
+template <int kMetric, bool kFar, int TW, int SW>
 __device__ __forceinline__ void sym64_group(int g, double xa, double ya, double za, double nxa, double nya,
                                             double nza, double wpa, double wna, double xb, double yb, double zb,
                                             double nxb, double nyb, double nzb, double wpb, double wnb,
-                                            const KParams& kp, double k2, Sym64Shared& sh, double (&f)[4]) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+                                            const KParams& kp, double k2, Sym64Shared<TW, SW>& sh, double (&f)[4]) {
+  const int lane = threadIdx.x & 63, wt = (threadIdx.x >> 6) % TW;
   const int next = ((lane + 1) & 63) << 2;
+  const int q0 = 2 * g + lane;
   double ra1 = 0.0, ra2 = 0.0;  // at step s: the reverse sums of source g + ((lane + s) mod 64)
   for (int s = 0; s < 64; ++s) {
-    const int q = g + ((lane + s) & 63);
+    const int q = q0 + s;
     const double2 c0 = sh.s0[q], c1 = sh.s1[q], c2 = sh.s2[q], c3 = sh.s3[q];
     if (kFar) {
       pair_sym_f64_far(xa, ya, za, nxa, nya, nza, wpa, wna, c0, c1, c2, c3, kp, k2, f[0], f[1], ra1, ra2);
@@ -186,118 +194,132 @@ __device__ __forceinline__ void sym64_group(int g, double xa, double ya, double 
     ra1 = shfl_next(ra1, next);
     ra2 = shfl_next(ra2, next);
   }
-  sh.racc[w][0][lane] = ra1;
-  sh.racc[w][1][lane] = ra2;
+  sh.racc[wt][0][g + lane] = ra1;
+  sh.racc[wt][1][g + lane] = ra2;
 }
 
-// Targets [t0, t0 + 512) (full; two per thread, t0 + 128w + l and 64 further, with bounding
-// box tlo/thi) against sources [s0, s0 + 512), s0 ≠ t0, both directions; adds the forward sums
-// into f and stores the reverse sums into rev (index j − s0), or adds them when rev_acc.
-// wpsi/wpsn: h³ωψ/4π, h³ωψn/4π.
-template <int kMetric>
-__device__ __forceinline__ void sym64_block(const BandDev& b, const double* __restrict__ wpsi,
-                                            const double* __restrict__ wpsn, int n, int t0, int s0,
-                                            const KParams& kp, double k2, Sym64Shared& sh, double (&f)[4],
-                                            const double (&tlo)[3], const double (&thi)[3], double* rev1,
-                                            double* rev2, bool rev_acc) {
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  double slo[3] = {INFINITY, INFINITY, INFINITY}, shi[3] = {-INFINITY, -INFINITY, -INFINITY};
-  for (int q = tid; q < kSymSub; q += kBlock) {
-    const int j = s0 + q;
+// Stages the sources [s0, s0 + kStage) and, if asked, their bounding box; beyond n: padding far away
+// with zero weights, which contributes exactly zero both ways. No barrier.
+template <int TW, int SW>
+__device__ __forceinline__ void sym64_stage(const BandDev& b, const double* __restrict__ wpsi,
+                                            const double* __restrict__ wpsn, int n, int s0, Sym64Shared<TW, SW>& sh,
+                                            double (&slo)[3], double (&shi)[3]) {
+  using Sh = Sym64Shared<TW, SW>;
+  for (int q = threadIdx.x; q < Sh::kStage; q += Sh::kThreads) {
+    const int j = s0 + q, at = (q >> 6) * 128 + (q & 63);
+    double2 c0 = make_double2(1e6, 1e6), c1 = make_double2(1e6, 0.0), c2 = make_double2(0.0, 1.0),
+            c3 = make_double2(0.0, 0.0);
     if (j < n) {
       const double x = b.px[j], y = b.py[j], z = b.pz[j];
-      sh.s0[q] = make_double2(x, y);
-      sh.s1[q] = make_double2(z, b.nx[j]);
-      sh.s2[q] = make_double2(b.ny[j], b.nz[j]);
-      sh.s3[q] = make_double2(wpsi[j], wpsn[j]);
+      c0 = make_double2(x, y);
+      c1 = make_double2(z, b.nx[j]);
+      c2 = make_double2(b.ny[j], b.nz[j]);
+      c3 = make_double2(wpsi[j], wpsn[j]);
       slo[0] = fmin(slo[0], x), slo[1] = fmin(slo[1], y), slo[2] = fmin(slo[2], z);
       shi[0] = fmax(shi[0], x), shi[1] = fmax(shi[1], y), shi[2] = fmax(shi[2], z);
-    } else {  // padding far away with zero weights: contributes exactly zero both ways
-      sh.s0[q] = make_double2(1e6, 1e6);
-      sh.s1[q] = make_double2(1e6, 0.0);
-      sh.s2[q] = make_double2(0.0, 1.0);
-      sh.s3[q] = make_double2(0.0, 0.0);
     }
+    sh.s0[at] = sh.s0[at + 64] = c0;
+    sh.s1[at] = sh.s1[at + 64] = c1;
+    sh.s2[at] = sh.s2[at + 64] = c2;
+    sh.s3[at] = sh.s3[at + 64] = c3;
   }
-  block_box(slo, shi, sh);  // synchronizes: the staged sources are visible after it
-  const bool far = kMetric != PB_REG_TANGENT &&
-                   box_gap2_f64(tlo, thi, slo, shi) >=
-                       (kMetric == PB_REG_EUCLIDEAN ? kp.tau2 : kp.four_tau2) * (1.0 + 1e-9);
-  const int ia = t0 + w * 128 + lane, ib = ia + 64;
-  const double xa = b.px[ia], ya = b.py[ia], za = b.pz[ia], nxa = b.nx[ia], nya = b.ny[ia], nza = b.nz[ia];
-  const double xb = b.px[ib], yb = b.py[ib], zb = b.pz[ib], nxb = b.nx[ib], nyb = b.ny[ib], nzb = b.nz[ib];
-  const double wpa = wpsi[ia], wna = wpsn[ia], wpb = wpsi[ib], wnb = wpsn[ib];
-  for (int g = 0; g < kSymSub; g += 64) {
-    if (far)
-      sym64_group<kMetric, true>(g, xa, ya, za, nxa, nya, nza, wpa, wna, xb, yb, zb, nxb, nyb, nzb, wpb, wnb, kp, k2,
-                                 sh, f);
-    else
-      sym64_group<kMetric, false>(g, xa, ya, za, nxa, nya, nza, wpa, wna, xb, yb, zb, nxb, nyb, nzb, wpb, wnb, kp,
-                                  k2, sh, f);
+}
+
+// Targets [t0, t0 + F) (full; two per thread, t0 + 128wt + l and 64 further, with bounding box
+// tlo/thi) against sources [s0, s0 + F) of another sub-block, both directions; adds the forward
+// sums over the wave's share of the sources into f and stores the reverse sums into rev (index
+// j − s0), or adds them when rev_acc. wpsi/wpsn: h³ωψ/4π, h³ωψn/4π.
+template <int kMetric, int TW, int SW>
+__device__ __forceinline__ void sym64_block(const BandDev& b, const double* __restrict__ wpsi,
+                                            const double* __restrict__ wpsn, int n, int t0, int s0,
+                                            const KParams& kp, double k2, Sym64Shared<TW, SW>& sh, double (&f)[4],
+                                            const double (&tlo)[3], const double (&thi)[3], double* rev1,
+                                            double* rev2, bool rev_acc) {
+  using Sh = Sym64Shared<TW, SW>;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, wt = w % TW, ws = w / TW;
+  for (int h = 0; h < Sh::F && s0 + h < n; h += Sh::kStage) {
+    double slo[3] = {INFINITY, INFINITY, INFINITY}, shi[3] = {-INFINITY, -INFINITY, -INFINITY};
+    sym64_stage(b, wpsi, wpsn, n, s0 + h, sh, slo, shi);
+    block_box(slo, shi, sh);  // synchronizes: the staged sources are visible after it
+    const bool far = kMetric != PB_REG_TANGENT &&
+                     box_gap2_f64(tlo, thi, slo, shi) >=
+                         (kMetric == PB_REG_EUCLIDEAN ? kp.tau2 : kp.four_tau2) * (1.0 + 1e-9);
+    const int ia = t0 + wt * 128 + lane, ib = ia + 64;
+    const double xa = b.px[ia], ya = b.py[ia], za = b.pz[ia], nxa = b.nx[ia], nya = b.ny[ia], nza = b.nz[ia];
+    const double xb = b.px[ib], yb = b.py[ib], zb = b.pz[ib], nxb = b.nx[ib], nyb = b.ny[ib], nzb = b.nz[ib];
+    const double wpa = wpsi[ia], wna = wpsn[ia], wpb = wpsi[ib], wnb = wpsn[ib];
+#pragma unroll 1
+  for (int g = ws * Sh::kSrc; g < (ws + 1) * Sh::kSrc; g += 64) {
+      if (far)
+        sym64_group<kMetric, true>(g, xa, ya, za, nxa, nya, nza, wpa, wna, xb, yb, zb, nxb, nyb, nzb, wpb, wnb, kp, k2,
+                                   sh, f);
+      else
+        sym64_group<kMetric, false>(g, xa, ya, za, nxa, nya, nza, wpa, wna, xb, yb, zb, nxb, nyb, nzb, wpb, wnb, kp,
+                                    k2, sh, f);
+    }
     __syncthreads();
-    // the four waves' reverse sums of the group, in wave order: threads 0..63 the ψ sums,
-    // 64..127 the ψn sums
-    if (tid < 128) {
-      const int c = tid >> 6, q = g + lane;
-      if (s0 + q < n) {
+    // the target waves' reverse sums of the stage, in wave order
+    for (int q = tid; q < 2 * Sh::kStage; q += Sh::kThreads) {
+      const int c = q / Sh::kStage, j = q % Sh::kStage;
+      if (s0 + h + j < n) {
         double x = 0.0;
-        for (int v = 0; v < kSymWaves; ++v) x += sh.racc[v][c][lane];
-        double* rev = c ? rev2 : rev1;
-        rev[q] = x + (rev_acc ? rev[q] : 0.0);
+        for (int v = 0; v < TW; ++v) x += sh.racc[v][c][j];
+        double* rev = (c ? rev2 : rev1) + h;
+        rev[j] = x + (rev_acc ? rev[j] : 0.0);
       }
     }
     __syncthreads();
   }
 }
 
-// Targets [t0, t0 + 512) (the same two per thread as sym64_block) against the sources of the
-// same sub-block (self pair included), one direction with the per-pair kernel of the
+// Targets [t0, t0 + F) (the same two per thread as sym64_block) against sources [s0, s0 + F) of the
+// same sub-block (self pairs included), one direction with the per-pair kernel of the
 // one-directional operator; adds into f.
+template <int TW, int SW>
 __device__ __forceinline__ void diag64_block(const BandDev& b, const double* __restrict__ wpsi,
-                                             const double* __restrict__ wpsn, int n, int t0, const KParams& kp,
-                                             Sym64Shared& sh, double (&f)[4]) {
-  const int tid = threadIdx.x;
-  for (int q = tid; q < kSymSub; q += kBlock) {
-    const int j = t0 + q;
-    if (j < n) {
-      sh.s0[q] = make_double2(b.px[j], b.py[j]);
-      sh.s1[q] = make_double2(b.pz[j], b.nx[j]);
-      sh.s2[q] = make_double2(b.ny[j], b.nz[j]);
-      sh.s3[q] = make_double2(wpsi[j], wpsn[j]);
-    }
-  }
-  __syncthreads();
-  const int m = min(kSymSub, n - t0);
-  for (int h = 0; h < 2; ++h) {
-    const int i = t0 + (tid >> 6) * 128 + (tid & 63) + 64 * h;
-    if (i < n) {
-      const double xi = b.px[i], yi = b.py[i], zi = b.pz[i], nxi = b.nx[i], nyi = b.ny[i], nzi = b.nz[i];
-      double s1 = 0.0, s2 = 0.0;
-      for (int q = 0; q < m; ++q) {
-        const double2 c0 = sh.s0[q], c1 = sh.s1[q], c2 = sh.s2[q], c3 = sh.s3[q];
-        pair_f64(xi, yi, zi, nxi, nyi, nzi, c0.x, c0.y, c1.x, c1.y, c2.x, c2.y, c3.x, c3.y, kp, 0.0, s1, s2);
+                                             const double* __restrict__ wpsn, int n, int t0, int s0, const KParams& kp,
+                                             Sym64Shared<TW, SW>& sh, double (&f)[4]) {
+  using Sh = Sym64Shared<TW, SW>;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, wt = w % TW, ws = w / TW;
+  for (int h = 0; h < Sh::F && s0 + h < n; h += Sh::kStage) {
+    double slo[3] = {}, shi[3] = {};
+    sym64_stage(b, wpsi, wpsn, n, s0 + h, sh, slo, shi);
+    __syncthreads();
+    const int q0 = ws * Sh::kSrc, m = min(q0 + Sh::kSrc, n - s0 - h);
+    for (int u = 0; u < 2; ++u) {
+      const int i = t0 + wt * 128 + lane + 64 * u;
+      if (i < n) {
+        const double xi = b.px[i], yi = b.py[i], zi = b.pz[i], nxi = b.nx[i], nyi = b.ny[i], nzi = b.nz[i];
+        double s1 = 0.0, s2 = 0.0;
+        for (int q = q0; q < m; ++q) {
+          const int at = (q >> 6) * 128 + (q & 63);
+          const double2 c0 = sh.s0[at], c1 = sh.s1[at], c2 = sh.s2[at], c3 = sh.s3[at];
+          pair_f64(xi, yi, zi, nxi, nyi, nzi, c0.x, c0.y, c1.x, c1.y, c2.x, c2.y, c3.x, c3.y, kp, 0.0, s1, s2);
+        }
+        f[2 * u] += s1;
+        f[2 * u + 1] += s2;
       }
-      f[2 * h] += s1;
-      f[2 * h + 1] += s2;
     }
+    __syncthreads();
   }
-  __syncthreads();
 }
 
-// One work item (Ic, Jc), Ic ≤ Jc; partial: the band's chunked partial sums; k2 = κ².
+// One work item (Ic, Jc), as for sym_item; partial: the band's chunked partial sums; k2 = κ².
+template <int TW, int SW>
 __device__ __forceinline__ void sym64_item(const BandDev& b, const double* __restrict__ wpsi,
                                            const double* __restrict__ wpsn, int n, int Ic, int Jc, int nsub,
                                            const KParams& kp, double k2, double* __restrict__ partial,
-                                           Sym64Shared& sh) {
-  const int C = nsub * kSymSub;
+                                           Sym64Shared<TW, SW>& sh) {
+  constexpr int F = Sym64Shared<TW, SW>::F;
+  const int C = nsub * F;
   const int i0 = Ic * C, i1 = min(n, i0 + C), j0 = Jc * C, j1 = min(n, j0 + C);
   double* rowF = partial + (int64_t)Jc * 2 * n;
   double* rowR = partial + (int64_t)Ic * 2 * n;
   const bool diag = Ic == Jc;
-  const int tid = threadIdx.x;
-  for (int T = i0; T < i1; T += kSymSub) {
-    const int ia = T + (tid >> 6) * 128 + (tid & 63), ib = ia + 64;
-    // bounding box of the target sub-block (exact FP64)
+  const int w = threadIdx.x >> 6;
+  for (int T = i0; T < i1; T += F) {
+    const int ia = T + (w % TW) * 128 + (threadIdx.x & 63), ib = ia + 64;
+    // bounding box of the target tile (exact FP64)
     double tlo[3] = {INFINITY, INFINITY, INFINITY}, thi[3] = {-INFINITY, -INFINITY, -INFINITY};
     for (int i : {ia, ib})
       if (i < n) {
@@ -309,10 +331,10 @@ __device__ __forceinline__ void sym64_item(const BandDev& b, const double* __res
       }
     block_box(tlo, thi, sh);
     double f[4] = {0.0, 0.0, 0.0, 0.0};
-    const bool rev_acc = T != i0;  // the first target sub-block stores the reverse slots
-    for (int S = (diag ? T : j0); S < j1; S += kSymSub) {
-      if (S == T)
-        diag64_block(b, wpsi, wpsn, n, T, kp, sh, f);
+    const bool rev_acc = T != i0;  // the first target tile stores the reverse slots
+    for (int S = (diag ? max(i0, T / kSymSub * kSymSub) : j0); S < j1; S += F) {
+      if (S / kSymSub == T / kSymSub)
+        diag64_block(b, wpsi, wpsn, n, T, S, kp, sh, f);
       else if (kp.metric == PB_REG_EUCLIDEAN)
         sym64_block<PB_REG_EUCLIDEAN>(b, wpsi, wpsn, n, T, S, kp, k2, sh, f, tlo, thi, rowR + S, rowR + n + S,
                                       rev_acc);
@@ -322,14 +344,15 @@ __device__ __forceinline__ void sym64_item(const BandDev& b, const double* __res
         sym64_block<PB_REG_TANGENT_GUARDED>(b, wpsi, wpsn, n, T, S, kp, k2, sh, f, tlo, thi, rowR + S, rowR + n + S,
                                             rev_acc);
     }
-    // forward sums, once per target sub-block (in a diagonal item the earlier target
-    // sub-blocks' reverse sums are already in these slots)
-    const bool fwd_acc = diag && T != i0;
-    if (ia < n) {
+    // forward sums, once per target tile (in a diagonal item the earlier target tiles' reverse
+    // sums are already in these slots)
+    const bool fwd_acc = diag && T / kSymSub != i0 / kSymSub;
+    const bool mine = sum_forward<TW, SW>(sh, f);
+    if (mine && ia < n) {
       rowF[ia] = f[0] + (fwd_acc ? rowF[ia] : 0.0);
       rowF[n + ia] = f[1] + (fwd_acc ? rowF[n + ia] : 0.0);
     }
-    if (ib < n) {
+    if (mine && ib < n) {
       rowF[ib] = f[2] + (fwd_acc ? rowF[ib] : 0.0);
       rowF[n + ib] = f[3] + (fwd_acc ? rowF[n + ib] : 0.0);
     }
@@ -338,15 +361,16 @@ __device__ __forceinline__ void sym64_item(const BandDev& b, const double* __res
 }
 
 // Symmetric FP64 operator of one band: one block per work item. k2 = κ² (a kernel argument,
-// so that it stays in scalar registers). Capped at 168 VGPRs for three waves per SIMD (37 KB
-// of LDS per block allows four blocks per CU): the pair loops stay free of spills, which fall
-// in the set-up code around them.
-static __global__ void __attribute__((unused)) __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3)))
+// so that it stays in scalar registers). Capped at 168 VGPRs for three waves per SIMD (at most 49
+// KB of LDS per block of four waves): the pair loops stay free of spills, which fall in the set-up
+// code around them.
+template <int TW, int SW>
+static __global__ void __attribute__((unused)) __launch_bounds__(64 * TW * SW) __attribute__((amdgpu_waves_per_eu(3)))
     k_p2p_f64_sym(BandDev b, const double* __restrict__ wpsi, const double* __restrict__ wpsn, int n, int nsub,
                   const int2* __restrict__ items, int n_items, KParams kp, double k2, double* __restrict__ partial,
                   const int* __restrict__ skip) {
   if (skip && *skip) return;
-  __shared__ Sym64Shared sh;
+  __shared__ Sym64Shared<TW, SW> sh;
   for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
     const int2 w = items[it];
     sym64_item(b, wpsi, wpsn, n, w.x, w.y, nsub, kp, k2, partial, sh);

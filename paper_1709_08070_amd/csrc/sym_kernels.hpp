@@ -45,11 +45,18 @@
 namespace pb {
 
 constexpr int kSymSub = 512;  // nodes per sub-block
-constexpr int kSymWaves = kBlock / 64;
 
+// Shape of a block: TW waves of 128 targets by SW waves that split the sources of a tile of
+// F = 128·TW nodes between them (whole groups of 64). Sources are staged twice per group of 64,
+// entries 64..127 repeating 0..63, so that lane l's source at step s is entry l + s: one address per
+// group and constant offsets, no wrap to compute.
+template <int TW, int SW>
 struct SymShared {
-  float4 sA[kSymSub], sN[kSymSub];
-  float racc[kSymWaves][2][kSymSub];
+  static constexpr int F = 128 * TW, kThreads = 64 * TW * SW, kSrc = F / SW;
+  static_assert(kSrc % 64 == 0, "whole groups of sources per wave");
+  float4 sA[2 * F], sN[2 * F];
+  float racc[TW][2][F];
+  double fsum[SW > 1 ? (SW - 1) * TW * 64 * 4 : 1];  // forward sums of the waves ws > 0
 };
 
 // Radial and pair terms shared by both directions (see the header), 1/r' being 0 for a near
@@ -118,55 +125,65 @@ __device__ __forceinline__ void pair_fwd(const float4& ta, const float4& tn, con
   if (kScreened) fa1 = __fmaf_rn(-t.f0r, sa.w, fa1);
 }
 
-// Targets [t0, t0 + 512) (full, 2 per thread: t0 + 128w + l and 64 further) against sources
-// [s0, s0 + 512) of the same records, s0 ≠ t0, both directions. Adds the unscaled forward sums
-// S1, S2 of the thread's two targets into f (a1, a2 of the first, then of the second); stores
-// σ·S1, σ²·S2 of the sources into rev (index j − s0), or adds them when rev_acc. Every thread
-// of the block calls it (it synchronizes).
-template <bool kScreened, bool kCheck>
-__device__ __forceinline__ void sym_block(const float4* __restrict__ A, const float4* __restrict__ N, int n, int t0,
-                                          int s0, const F32Params& fp, double sig1, double sig2, SymShared& sh,
-                                          double (&f)[4], double* rev1, double* rev2, bool rev_acc) {
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  for (int q = tid; q < kSymSub; q += kBlock) {
-    const int j = s0 + q;
-    if (j < n) {
-      sh.sA[q] = A[j];
-      sh.sN[q] = N[j];
-    } else {  // padding: zero weights and normals (such tiles run with the predicate)
-      sh.sA[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-      sh.sN[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-    }
+// Stages the sources [s0, s0 + F) (zero weights and normals beyond n: such tiles run with the
+// predicate) and returns after a barrier.
+template <int TW, int SW>
+__device__ __forceinline__ void sym_stage(const float4* __restrict__ A, const float4* __restrict__ N, int n, int s0,
+                                          SymShared<TW, SW>& sh) {
+  using Sh = SymShared<TW, SW>;
+  for (int q = threadIdx.x; q < Sh::F; q += Sh::kThreads) {
+    const int j = s0 + q, at = (q >> 6) * 128 + (q & 63);
+    const float4 a = j < n ? A[j] : make_float4(0.f, 0.f, 0.f, 0.f);
+    const float4 m = j < n ? N[j] : make_float4(0.f, 0.f, 0.f, 0.f);
+    sh.sA[at] = sh.sA[at + 64] = a;
+    sh.sN[at] = sh.sN[at + 64] = m;
   }
-  const int ia = t0 + w * 128 + lane, ib = ia + 64;
+  __syncthreads();
+}
+
+// Targets [t0, t0 + F) (full; two per thread, t0 + 128wt + l and 64 further) against sources
+// [s0, s0 + F) of the same records in another sub-block, both directions. Adds the unscaled
+// forward sums S1, S2 of the thread's two targets over its wave's share of the sources into f (a1,
+// a2 of the first, then of the second); stores σ·S1, σ²·S2 of the sources into rev (index j − s0),
+// or adds them when rev_acc. Every thread of the block calls it (it synchronizes).
+template <bool kScreened, bool kCheck, int TW, int SW>
+__device__ __forceinline__ void sym_block(const float4* __restrict__ A, const float4* __restrict__ N, int n, int t0,
+                                          int s0, const F32Params& fp, double sig1, double sig2,
+                                          SymShared<TW, SW>& sh, double (&f)[4], double* rev1, double* rev2,
+                                          bool rev_acc) {
+  using Sh = SymShared<TW, SW>;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, wt = w % TW, ws = w / TW;
+  const int ia = t0 + wt * 128 + lane, ib = ia + 64;
   const float4 taa = A[ia], tna = N[ia];
   const float4 tab = A[ib], tnb = N[ib];
-  __syncthreads();
+  sym_stage(A, N, n, s0, sh);
   const int next = ((lane + 1) & 63) << 2;  // byte address of lane l + 1 for ds_bpermute
-  for (int g = 0; g < kSymSub; g += 64) {
+#pragma unroll 1
+  for (int g = ws * Sh::kSrc; g < (ws + 1) * Sh::kSrc; g += 64) {
+    const float4* __restrict__ pA = sh.sA + 2 * g + lane;
+    const float4* __restrict__ pN = sh.sN + 2 * g + lane;
     float fa1 = 0.f, fa2 = 0.f, fb1 = 0.f, fb2 = 0.f;
     float ra1 = 0.f, ra2 = 0.f;  // at step s: the reverse sums of source g + ((lane + s) mod 64)
 #pragma unroll 2
     for (int s = 0; s < 64; ++s) {
-      const int q = g + ((lane + s) & 63);
-      const float4 sa = sh.sA[q], sn = sh.sN[q];
+      const float4 sa = pA[s], sn = pN[s];
       pair_sym<kScreened, kCheck>(taa, tna, sa, sn, fp, fa1, fa2, ra1, ra2);
       pair_sym<kScreened, kCheck>(tab, tnb, sa, sn, fp, fb1, fb2, ra1, ra2);
       ra1 = __int_as_float(__builtin_amdgcn_ds_bpermute(next, __float_as_int(ra1)));
       ra2 = __int_as_float(__builtin_amdgcn_ds_bpermute(next, __float_as_int(ra2)));
     }
-    sh.racc[w][0][g + lane] = ra1;  // 64 rotations: lane l holds source g + l
-    sh.racc[w][1][g + lane] = ra2;
+    sh.racc[wt][0][g + lane] = ra1;  // 64 rotations: lane l holds source g + l
+    sh.racc[wt][1][g + lane] = ra2;
     f[0] += (double)fa1;
     f[1] += (double)fa2;
     f[2] += (double)fb1;
     f[3] += (double)fb2;
   }
   __syncthreads();
-  for (int q = tid; q < kSymSub; q += kBlock) {
+  for (int q = tid; q < Sh::F; q += Sh::kThreads) {
     if (s0 + q < n) {
       double x1 = 0.0, x2 = 0.0;
-      for (int v = 0; v < kSymWaves; ++v) {
+      for (int v = 0; v < TW; ++v) {
         x1 += (double)sh.racc[v][0][q];
         x2 += (double)sh.racc[v][1][q];
       }
@@ -177,33 +194,25 @@ __device__ __forceinline__ void sym_block(const float4* __restrict__ A, const fl
   __syncthreads();
 }
 
-// Targets [t0, t0 + 512) (the same two per thread as sym_block) against the sources of the
+// Targets [t0, t0 + F) (the same two per thread as sym_block) against sources [s0, s0 + F) of the
 // same sub-block, one direction, with the near-pair predicate (the self pair and the nearest
 // pairs are here). Adds the unscaled sums into f.
-template <bool kScreened>
+template <bool kScreened, int TW, int SW>
 __device__ __forceinline__ void diag_block(const float4* __restrict__ A, const float4* __restrict__ N, int n, int t0,
-                                           const F32Params& fp, SymShared& sh, double (&f)[4]) {
-  const int tid = threadIdx.x;
-  for (int q = tid; q < kSymSub; q += kBlock) {
-    const int j = t0 + q;
-    if (j < n) {
-      sh.sA[q] = A[j];
-      sh.sN[q] = N[j];
-    } else {
-      sh.sA[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-      sh.sN[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-  }
-  const int ia = t0 + (tid >> 6) * 128 + (tid & 63), ib = ia + 64;
+                                           int s0, const F32Params& fp, SymShared<TW, SW>& sh, double (&f)[4]) {
+  using Sh = SymShared<TW, SW>;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, wt = w % TW, ws = w / TW;
+  const int ia = t0 + wt * 128 + lane, ib = ia + 64;
   const float4 taa = ia < n ? A[ia] : make_float4(0.f, 0.f, 0.f, 0.f);
   const float4 tna = ia < n ? N[ia] : make_float4(0.f, 0.f, 1.f, 0.f);  // dead targets: results unused
   const float4 tab = ib < n ? A[ib] : make_float4(0.f, 0.f, 0.f, 0.f);
   const float4 tnb = ib < n ? N[ib] : make_float4(0.f, 0.f, 1.f, 0.f);
-  __syncthreads();
-  for (int g = 0; g < kSymSub; g += 64) {
+  sym_stage(A, N, n, s0, sh);
+#pragma unroll 1
+  for (int g = ws * Sh::kSrc; g < (ws + 1) * Sh::kSrc; g += 64) {
     float fa1 = 0.f, fa2 = 0.f, fb1 = 0.f, fb2 = 0.f;
 #pragma unroll 4
-    for (int q = g; q < g + 64; ++q) {
+    for (int q = 2 * g; q < 2 * g + 64; ++q) {
       const float4 sa = sh.sA[q], sn = sh.sN[q];
       pair_fwd<kScreened>(taa, tna, sa, sn, fp, fa1, fa2);
       pair_fwd<kScreened>(tab, tnb, sa, sn, fp, fb1, fb2);
@@ -216,36 +225,54 @@ __device__ __forceinline__ void diag_block(const float4* __restrict__ A, const f
   __syncthreads();
 }
 
-// One work item (Ic, Jc), Ic ≤ Jc, of a band of n records with chunks of nsub sub-blocks.
-// partial: the band's chunked partial sums (slot (c, e) at partial[c·2n + e]).
-template <bool kScreened>
+// Adds the forward sums of the waves ws > 0 to those of ws = 0, in wave order; true on the threads
+// that then hold the sums. Every thread of the block calls it.
+template <int TW, int SW, typename Shared>
+__device__ __forceinline__ bool sum_forward(Shared& sh, double (&f)[4]) {
+  if (SW == 1) return true;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, wt = w % TW, ws = w / TW;
+  if (ws > 0)
+    for (int c = 0; c < 4; ++c) sh.fsum[(((ws - 1) * TW + wt) * 4 + c) * 64 + lane] = f[c];
+  __syncthreads();
+  if (ws > 0) return false;
+  for (int v = 0; v < SW - 1; ++v)
+    for (int c = 0; c < 4; ++c) f[c] += sh.fsum[((v * TW + wt) * 4 + c) * 64 + lane];
+  return true;
+}
+
+// One work item (Ic, Jc) of a band of n records with chunks of nsub tiles of F nodes (chunks are
+// whole sub-blocks, or one tile each): tiles of different sub-blocks meet both ways, each pair of
+// tiles once; tiles of one sub-block one way, each as the other's targets. partial: the band's chunked partial sums
+// (slot (c, e) at partial[c·2n + e]).
+template <bool kScreened, int TW, int SW>
 __device__ __forceinline__ void sym_item(const float4* __restrict__ A, const float4* __restrict__ N,
                                          const float4* __restrict__ box, int n, int Ic, int Jc, int nsub,
                                          const F32Params& fp, double sig1, double sig2, double* __restrict__ partial,
-                                         SymShared& sh) {
-  const int C = nsub * kSymSub;
+                                         SymShared<TW, SW>& sh) {
+  constexpr int F = SymShared<TW, SW>::F;
+  const int C = nsub * F;
   const int i0 = Ic * C, i1 = min(n, i0 + C), j0 = Jc * C, j1 = min(n, j0 + C);
   double* rowF = partial + (int64_t)Jc * 2 * n;  // slots (Jc, i): contributions of chunk Jc
   double* rowR = partial + (int64_t)Ic * 2 * n;  // slots (Ic, j): contributions of chunk Ic
   const bool diag = Ic == Jc;
-  const int tid = threadIdx.x;
-  for (int T = i0; T < i1; T += kSymSub) {
+  const int w = threadIdx.x >> 6;
+  for (int T = i0; T < i1; T += F) {
     float4 tlo, thi;
-    box_union(box, T / kGroup, min(T + kSymSub, n + kGroup - 1) / kGroup, tlo, thi);
+    box_union(box, T / kGroup, (min(T + F, n) - 1) / kGroup + 1, tlo, thi);
     double f[4] = {0.0, 0.0, 0.0, 0.0};
-    // reverse slots of the item's source sub-blocks: stored at the first target sub-block,
-    // added to at the later ones (in a diagonal item a sub-block's slots then also take its
-    // own forward sums, after every reverse contribution, since targets go in increasing order)
+    // reverse slots of the item's source tiles: stored at the first target tile, added to at the
+    // later ones (in a diagonal item a tile's slots then also take its own forward sums, after
+    // every reverse contribution, since targets go in increasing order)
     const bool rev_acc = T != i0;
-    for (int S = (diag ? T : j0); S < j1; S += kSymSub) {
-      if (S == T) {
-        diag_block<kScreened>(A, N, n, T, fp, sh, f);
+    for (int S = (diag ? max(i0, T / kSymSub * kSymSub) : j0); S < j1; S += F) {
+      if (S / kSymSub == T / kSymSub) {
+        diag_block<kScreened>(A, N, n, T, S, fp, sh, f);
         continue;
       }
       int clear = 0;
-      if (S + kSymSub <= n) {
+      if (S + F <= n) {
         float4 slo, shi;
-        box_union(box, S / kGroup, (S + kSymSub) / kGroup, slo, shi);
+        box_union(box, S / kGroup, (S + F - 1) / kGroup + 1, slo, shi);
         clear = box_gap2(tlo, thi, slo, shi) >= fp.far2;
       }
       clear = __builtin_amdgcn_readfirstlane(clear);
@@ -254,15 +281,16 @@ __device__ __forceinline__ void sym_item(const float4* __restrict__ A, const flo
       else
         sym_block<kScreened, true>(A, N, n, T, S, fp, sig1, sig2, sh, f, rowR + S, rowR + n + S, rev_acc);
     }
-    // forward sums of the two targets of this thread, once per target sub-block; in a
-    // diagonal item the earlier target sub-blocks' reverse sums are already in these slots
-    const bool fwd_acc = diag && T != i0;
-    const int ia = T + (tid >> 6) * 128 + (tid & 63), ib = ia + 64;
-    if (ia < n) {
+    // forward sums of the two targets of this thread, once per target tile; in a diagonal item the
+    // earlier target tiles' reverse sums are already in these slots
+    const bool fwd_acc = diag && T / kSymSub != i0 / kSymSub;
+    const bool mine = sum_forward<TW, SW>(sh, f);
+    const int ia = T + (w % TW) * 128 + (threadIdx.x & 63), ib = ia + 64;
+    if (mine && ia < n) {
       rowF[ia] = sig1 * f[0] + (fwd_acc ? rowF[ia] : 0.0);
       rowF[n + ia] = sig2 * f[1] + (fwd_acc ? rowF[n + ia] : 0.0);
     }
-    if (ib < n) {
+    if (mine && ib < n) {
       rowF[ib] = sig1 * f[2] + (fwd_acc ? rowF[ib] : 0.0);
       rowF[n + ib] = sig2 * f[3] + (fwd_acc ? rowF[n + ib] : 0.0);
     }
@@ -271,23 +299,25 @@ __device__ __forceinline__ void sym_item(const float4* __restrict__ A, const flo
 }
 
 // Symmetric FP32 far field of one band: one block per work item (items: (Ic, Jc) pairs).
-template <bool kScreened>
-static __global__ void __attribute__((unused)) __launch_bounds__(kBlock)
+template <bool kScreened, int TW, int SW>
+static __global__ void __attribute__((unused)) __launch_bounds__(64 * TW * SW)
     k_p2p_f32_sym(const float4* __restrict__ A, const float4* __restrict__ N,
                   const float4* __restrict__ box, int n, int nsub, const int2* __restrict__ items, int n_items,
                   F32Params fp, double sig1, double sig2, double* __restrict__ partial,
                   const int* __restrict__ skip) {
   if (skip && *skip) return;
-  __shared__ SymShared sh;
+  __shared__ SymShared<TW, SW> sh;
   for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
     const int2 w = items[it];
     sym_item<kScreened>(A, N, box, n, w.x, w.y, nsub, fp, sig1, sig2, partial, sh);
   }
 }
 
-// Chunking of a band of n nodes for the symmetric kernel: about 100 chunks (≈5000 items)
-// for large bands, chunks of one sub-block for small ones.
-inline int sym_nsub(int n) { return std::max(1, (n + 100 * kSymSub - 1) / (100 * kSymSub)); }
+// Chunking of a band of n nodes for the symmetric kernels in tiles of 512: 128 to 256 chunks (at
+// least 8000 items) for large bands, chunks of one sub-block for small ones. Fewer chunks leave a
+// part-filled last round of blocks: at 55,111 nodes 54 chunks of 1024 nodes took 1571 µs (FP32) and
+// 4377 µs (FP64), 108 of 512 take 1384 and 3947 µs; more only cost partial sums.
+inline int sym_nsub(int n) { return std::max(1, n / (128 * kSymSub)); }
 inline int sym_chunks(int n) {
   const int C = sym_nsub(n) * kSymSub;
   return (n + C - 1) / C;
