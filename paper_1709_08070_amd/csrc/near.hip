@@ -240,6 +240,10 @@ pb_status near_build(pb_ctx* ctx, const pb_band* band, const Derived& d, const c
       lo[a] = std::fmin(lo[a], hb[6 * q + a]);
       hi[a] = std::fmax(hi[a], hb[6 * q + 3 + a]);
     }
+  for (int a = 0; a < 3; ++a) {
+    P.lo[a] = lo[a];
+    P.hi[a] = hi[a];
+  }
   P.band_key = band->px;
   P.n = n;
   P.cx = 0.5 * (lo[0] + hi[0]);

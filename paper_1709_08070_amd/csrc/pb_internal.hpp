@@ -50,6 +50,7 @@ struct MixedPlan {
   const void* band_key = nullptr;
   int64_t n = 0;
   double cx = 0, cy = 0, cz = 0;  // centre of the FP32 coordinates
+  double lo[3] = {}, hi[3] = {};  // bounding box of the projections
   double sigma = 1;               // FP32 coordinates are scaled by σ (= κ when κ > 0)
   double rc = 0;                  // near-field radius (unscaled)
   float rc2f = 0;                 // (σ r_c)² in FP32
@@ -74,6 +75,13 @@ struct MixedPlan {
 // coordinates in Morton order, target batches with their direct source ranges and proxy
 // clusters, and the buffers of one application. Built once per band.
 constexpr int kTreeMaxDegree = 8;
+constexpr int kBatch = 64;         // targets per batch = lanes of the far-field wave
+constexpr int kProxyChunk = 2048;  // sources per proxy work item
+constexpr int kAnchor = 16;        // tree-order nodes per local-coordinate group of direct sources
+// One wave's share of a batch's lists: direct ranges [d0, d1), then proxy clusters [a0, a1).
+struct TreeSeg {
+  int batch, d0, d1, a0, a1;
+};
 struct TreePlan {
   const void* band_key = nullptr;
   int64_t n = 0;
@@ -82,13 +90,15 @@ struct TreePlan {
   float u[kTreeMaxDegree + 1] = {};  // Chebyshev points of the second kind, cos(πa/p)
   MixedPlan near;                    // FP32 records (band order) and the FP64 near field
   int n_batch = 0, n_cl = 0, n_items = 0;
+  int n_seg_max = 0;                 // upper bound of the number of segments
   int64_t n_dir_pairs = 0, n_app_pairs = 0;  // target–source and target–proxy interactions
   int* perm = nullptr;               // tree position → band index
   int2* batch = nullptr;             // target batches (tree-order ranges)
-  int* dir_ptr = nullptr;            // per batch: direct source ranges
-  int2* dir_rng = nullptr;
-  int* app_ptr = nullptr;            // per batch: proxy clusters
-  int* app_cl = nullptr;
+  int2* dir_rng = nullptr;           // direct source ranges
+  int* app_cl = nullptr;             // proxy clusters
+  TreeSeg* seg = nullptr;            // work segments, in batch order
+  int* seg_ptr = nullptr;            // per batch: its segments (n_batch + 1)
+  double* seg_sum = nullptr;         // per segment: far-field sums of its batch's targets
   float4* half = nullptr;            // per cluster: half-widths of its box (scaled coordinates)
   double* ccen = nullptr;            // per cluster: FP64 centre of its box (3 doubles)
   int4* items = nullptr;             // proxy work items (cluster, begin, end, ·)
@@ -222,13 +232,15 @@ pb_status nn_batch_prepare(pb_ctx* ctx, int n_mol, const pb_band* bands, const i
 void nn_batch_apply(hipStream_t stream, const pb_nn* net, const NNBatch& nb, const double* V, double* Z, int64_t ldv,
                     const int* kptr, int kmax, double lam1, double lam2);
 pb_status matvec_mixed(pb_ctx* ctx, const pb_band* band, const Derived& d, const double* p, double* y);
-// Treecode far field (tree.hip): degree of the Chebyshev proxies and the acceptance ratio θ;
-// buffers named `<pfx>...`; near: an existing near field of the same band to share (else built).
-// host: in/out, the Morton order, octree and batches of the band, built by the first plan of a
-// solve and reused by the second (null: built and dropped).
-struct TreeHost;
+// Treecode far field (tree.hip, tree_build.hip): degree of the Chebyshev proxies and the
+// acceptance ratio θ; buffers named `<pfx>...`; near: an existing near field of the same band to
+// share (else built). tree: in/out, the octree and target batches of the band, left in the workspace
+// by the first plan of a solve and reused by the second.
+struct TreeDev;
 pb_status tree_prepare(pb_ctx* ctx, const pb_band* band, const Derived& d, int degree, double theta, TreePlan& T,
-                       const char* pfx, const MixedPlan* near = nullptr, std::shared_ptr<TreeHost>* host = nullptr);
+                       const char* pfx, const MixedPlan* near = nullptr, std::shared_ptr<TreeDev>* tree = nullptr);
+// Exact tree-order coordinates and the anchors of the direct sources' groups.
+pb_status tree_coords(pb_ctx* ctx, const pb_band* band, const TreePlan& T);
 pb_status matvec_tree(pb_ctx* ctx, const pb_band* band, const Derived& d, const double* p, double* y,
                       const TreePlan& T);
 // PB_TREE solves: the refinement's residuals on bands of at least kTreeFineMin nodes come from a

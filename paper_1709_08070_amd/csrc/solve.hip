@@ -494,11 +494,11 @@ extern "C" pb_status pb_ibim_solve(pb_ctx* ctx, const pb_band* band, const doubl
   const bool fine_tree = opts.precision == PB_TREE && n >= kTreeFineMin;
   if (opts.precision == PB_MIXED || (opts.precision == PB_TREE && !fine_tree)) PB_TRY(mixed_prepare(ctx, band, d));
   if (opts.precision == PB_TREE) {
-    std::shared_ptr<TreeHost> host;  // one octree for both plans
-    PB_TRY(tree_prepare(ctx, band, d, prm->tree_degree, prm->tree_theta, ctx->tree, "tc_", nullptr, &host));
+    std::shared_ptr<TreeDev> tree;  // one octree for both plans
+    PB_TRY(tree_prepare(ctx, band, d, prm->tree_degree, prm->tree_theta, ctx->tree, "tc_", nullptr, &tree));
     if (fine_tree)
       PB_TRY(tree_prepare(ctx, band, d, kTreeFineDegree, kTreeFineTheta, ctx->tree_fine, "tf_", &ctx->tree.near,
-                          &host));
+                          &tree));
   }
   int n64 = 0, nmx = 0, nmid = 0, nnn = 0;
   OpFn op64 = [&](const double* in, double* out) {
