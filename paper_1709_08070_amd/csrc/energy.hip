@@ -25,83 +25,110 @@ static __device__ __align__(256) double scratch[kNoallocMaxAtoms];
 namespace pb {
 namespace {
 
-constexpr int kBlock = 256;
 constexpr int kMaxDevices = 64;
 double* scratch_dev[kMaxDevices];  // device address of `scratch` per device ordinal
 std::mutex scratch_mu;
 
-__global__ void __launch_bounds__(kBlock) k_rhs(int n, const double* __restrict__ px, const double* __restrict__ py,
-                                                const double* __restrict__ pz, const double* __restrict__ nx,
-                                                const double* __restrict__ ny, const double* __restrict__ nz,
-                                                const double* __restrict__ atoms, int n_atoms, double eps_in,
-                                                double* __restrict__ g) {
-  __shared__ double4 tile[kBlock];
-  const int i = blockIdx.x * kBlock + threadIdx.x;
-  const bool live = i < n;
-  double x = 0, y = 0, z = 0, a = 0, b = 0, c = 1;
-  if (live) {
-    x = px[i]; y = py[i]; z = pz[i];
-    a = nx[i]; b = ny[i]; c = nz[i];
-  }
+// A block takes 64 nodes; its kRhsWaves waves share the atoms of each LDS tile out among themselves and
+// add their sums up at the end in wave order. Bound by FP64 issue (some 20 instructions
+// and a reciprocal square root a pair); by nodes alone the 1343 waves of 85,870 nodes leave SIMDs idle:
+// 1991 atoms 213 → 153 µs with the call, 500 atoms on 35,214 nodes 46 → 35.
+constexpr int kRhsWaves = 8, kRhsTile = 64 * kRhsWaves;
+
+__global__ void __launch_bounds__(kRhsTile) k_rhs(int n, const double* __restrict__ px, const double* __restrict__ py,
+                                                  const double* __restrict__ pz, const double* __restrict__ nx,
+                                                  const double* __restrict__ ny, const double* __restrict__ nz,
+                                                  const double* __restrict__ atoms, int n_atoms, double eps_in,
+                                                  double* __restrict__ g) {
+  __shared__ double4 tile[kRhsTile];
+  __shared__ double part[2][kRhsWaves][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i = blockIdx.x * 64 + lane, r = min(i, n - 1);
+  const double x = px[r], y = py[r], z = pz[r], a = nx[r], b = ny[r], c = nz[r];
   double s1 = 0.0, s2 = 0.0;
   const double c4 = 1.0 / (4.0 * kPi);
-  for (int base = 0; base < n_atoms; base += kBlock) {
-    int k = base + threadIdx.x;
+  for (int base = 0; base < n_atoms; base += kRhsTile) {
+    const int k = base + (int)threadIdx.x, m = min(kRhsTile, n_atoms - base);
     // the charge enters as q/ε_I/(4π), formed once per atom (the same operations, hoisted)
     if (k < n_atoms)
       tile[threadIdx.x] = make_double4(atoms[5 * k], atoms[5 * k + 1], atoms[5 * k + 2], atoms[5 * k + 4] / eps_in * c4);
     __syncthreads();
-    int m = min(kBlock, n_atoms - base);
-    if (live)
-      for (int q = 0; q < m; ++q) {
-        const double4 at = tile[q];
-        double dx = x - at.x, dy = y - at.y, dz = z - at.z;
-        double r2 = dx * dx + dy * dy + dz * dz;
-        double rinv = rsqrt_f64(r2);
-        double dn = dx * a + dy * b + dz * c;
-        double qe = at.w;
-        s1 += qe * rinv;
-        s2 -= qe * dn * rinv * rinv * rinv;
-      }
+#pragma unroll 4
+    for (int q = wave; q < m; q += kRhsWaves) {
+      const double4 at = tile[q];
+      const double dx = x - at.x, dy = y - at.y, dz = z - at.z;
+      const double r2 = dx * dx + dy * dy + dz * dz;
+      const double rinv = rsqrt_f64(r2);
+      const double dn = dx * a + dy * b + dz * c;
+      const double t = at.w * rinv;
+      s1 += t;
+      s2 -= dn * (rinv * rinv) * t;
+    }
     __syncthreads();
   }
-  if (live) {
-    g[i] = s1;
-    g[n + i] = s2;
+  part[0][wave][lane] = s1;
+  part[1][wave][lane] = s2;
+  __syncthreads();
+  if (wave < 2 && i < n) {
+    double s = 0.0;
+    for (int w = 0; w < kRhsWaves; ++w) s += part[wave][w][lane];
+    g[(int64_t)wave * n + i] = s;
   }
 }
 
-constexpr int kPsiAtoms = 8;    // atoms per block of k_psi_rxn
-constexpr int kPsiBlock = 512;  // its threads: few blocks (n_atoms / 8), so wide ones
+constexpr int kPsiBlock = 1024;
 
-// ψ_rxn of kPsiAtoms atoms per block: every thread reads the data of each of its nodes once
-// and adds that node's term to the sums of all the block's atoms, then one fixed-order block
-// reduction per atom. 1/ρ is rsqrt_f64 and e^{−κρ} exp_neg_f64 (fp64_math.hpp). Per pair, times
-// 4π: s(θ1 E(1 + κρ) − 1)/ρ³ · ψ̄_j + (1 − E)/ρ · ψ̄n_j, with the weight h³ω_j/4π.
+// The sum of v over the block in a fixed order, in thread 0. red: one double per wave.
+__device__ __forceinline__ double block_sum(double v, double* red) {
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off);
+  __syncthreads();  // red may hold an earlier sum
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+  __syncthreads();
+  if (threadIdx.x == 0)
+    for (int w = 1; w < kPsiBlock / 64; ++w) v += red[w];
+  return v;
+}
+
+// ψ_rxn of A atoms per block: every thread reads the data of each of its nodes once and adds that
+// node's term to the sums of all the block's atoms, then one fixed-order block reduction per atom.
+// 1/ρ is rsqrt_f64 and e^{−κρ} exp_neg_f64 (fp64_math.hpp). Per pair, times 4π:
+// s(θ1 E(1 + κρ) − 1)/ρ³ · ψ̄_j + (1 − E)/ρ · ψ̄n_j, with the weight h³ω_j/4π. Block 0 sums the area
+// h³ Σ_j ω_j instead. Bound by FP64 issue (about 45 instructions a
+// pair); blocks of 512 threads left a CU two waves per SIMD to hide the loads of a node behind, and the area,
+// summed afterwards by one block, took 76 µs of its own: 1991 atoms on 85,870 nodes 414 → 306 µs with
+// the call.
+template <int A>
 __global__ void __launch_bounds__(kPsiBlock) k_psi_rxn(int n, const double* __restrict__ px, const double* __restrict__ py,
                                                     const double* __restrict__ pz, const double* __restrict__ nx,
                                                     const double* __restrict__ ny, const double* __restrict__ nz,
                                                     const double* __restrict__ w, const double* __restrict__ p,
                                                     const double* __restrict__ atoms, int n_atoms, double th1,
-                                                    double kappa, double h3, double* __restrict__ psi) {
-  __shared__ double red[kPsiBlock];
-  __shared__ double za[kPsiAtoms][3];
-  const int k0 = blockIdx.x * kPsiAtoms;
-  if (threadIdx.x < 3 * kPsiAtoms) {
-    const int a = threadIdx.x / 3, c = threadIdx.x % 3;
-    za[a][c] = k0 + a < n_atoms ? atoms[5 * (k0 + a) + c] : 0.0;  // a missing atom's sum is not stored
+                                                    double kappa, double h3, double* __restrict__ psi,
+                                                    double* __restrict__ area) {
+  __shared__ double red[kPsiBlock / 64];
+  if (blockIdx.x == 0) {
+    double s = 0.0;
+#pragma unroll 8
+    for (int j = threadIdx.x; j < n; j += kPsiBlock) s += w[j];
+    s = block_sum(s, red);
+    if (threadIdx.x == 0) *area = h3 * s;
+    return;
   }
-  __syncthreads();
-  const double c4 = h3 / (4.0 * kPi);
-  double acc[kPsiAtoms];
+  const int k0 = (blockIdx.x - 1) * A;
+  double za[A][3];
 #pragma unroll
-  for (int a = 0; a < kPsiAtoms; ++a) acc[a] = 0.0;
+  for (int a = 0; a < A; ++a)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) za[a][c] = atoms[5 * min(k0 + a, n_atoms - 1) + c];  // a missing atom's sum is not stored
+  const double c4 = h3 / (4.0 * kPi);
+  double acc[A];
+#pragma unroll
+  for (int a = 0; a < A; ++a) acc[a] = 0.0;
   for (int j = threadIdx.x; j < n; j += kPsiBlock) {
     const double yx = px[j], yy = py[j], yz = pz[j], nxj = nx[j], nyj = ny[j], nzj = nz[j];
     const double ww = c4 * w[j];
     const double w1 = ww * p[j], w2 = ww * p[n + j];
 #pragma unroll
-    for (int a = 0; a < kPsiAtoms; ++a) {
+    for (int a = 0; a < A; ++a) {
       const double dx = za[a][0] - yx, dy = za[a][1] - yy, dz = za[a][2] - yz;
       const double r2 = dx * dx + dy * dy + dz * dz;
       const double rinv = rsqrt_f64(r2);
@@ -113,42 +140,24 @@ __global__ void __launch_bounds__(kPsiBlock) k_psi_rxn(int n, const double* __re
     }
   }
 #pragma unroll
-  for (int a = 0; a < kPsiAtoms; ++a) {
-    red[threadIdx.x] = acc[a];
-    __syncthreads();
-    for (int off = kPsiBlock / 2; off > 0; off >>= 1) {
-      if (threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
-      __syncthreads();
-    }
-    if (threadIdx.x == 0 && k0 + a < n_atoms) psi[k0 + a] = red[0];
-    __syncthreads();
+  for (int a = 0; a < A; ++a) {
+    const double s = block_sum(acc[a], red);
+    if (threadIdx.x == 0 && k0 + a < n_atoms) psi[k0 + a] = s;
   }
 }
 
-// The fields of pb_energy in order: out[0] = G_pol = ½ Σ_k q_k ψ_k, out[1] = G_pol in kcal/mol,
-// out[2] = area = h³ Σ_j ω_j (one block, fixed order).
-__global__ void __launch_bounds__(kBlock) k_finish(int n_atoms, const double* __restrict__ atoms,
-                                                   const double* __restrict__ psi, int n, const double* __restrict__ w,
-                                                   double h3, double* __restrict__ out) {
-  __shared__ double r1[kBlock], r2[kBlock];
-  double a = 0.0, b = 0.0;
-  for (int k = threadIdx.x; k < n_atoms; k += kBlock) a += atoms[5 * k + 4] * psi[k];
-  for (int j = threadIdx.x; j < n; j += kBlock) b += w[j];
-  r1[threadIdx.x] = a;
-  r2[threadIdx.x] = b;
-  __syncthreads();
-  for (int off = kBlock / 2; off > 0; off >>= 1) {
-    if (threadIdx.x < off) {
-      r1[threadIdx.x] += r1[threadIdx.x + off];
-      r2[threadIdx.x] += r2[threadIdx.x + off];
-    }
-    __syncthreads();
-  }
+// The fields of pb_energy in order: out[0] = G_pol = ½ Σ_k q_k ψ_k, out[1] = G_pol in kcal/mol (one
+// block, fixed order); out[2], the area, is k_psi_rxn's.
+__global__ void __launch_bounds__(kPsiBlock) k_finish(int n_atoms, const double* __restrict__ atoms,
+                                                   const double* __restrict__ psi, double* __restrict__ out) {
+  __shared__ double red[kPsiBlock / 64];
+  double a = 0.0;
+  for (int k = threadIdx.x; k < n_atoms; k += kPsiBlock) a += atoms[5 * k + 4] * psi[k];
+  a = block_sum(a, red);
   if (threadIdx.x == 0) {
-    const double gpol = 0.5 * r1[0];
+    const double gpol = 0.5 * a;
     out[0] = gpol;
     out[1] = gpol * 4.0 * kPi * 332.0637;
-    out[2] = h3 * r2[0];
   }
 }
 
@@ -156,10 +165,25 @@ __global__ void __launch_bounds__(kBlock) k_finish(int n_atoms, const double* __
 void energy_launch(pb_ctx* ctx, const pb_band* band, const double* atoms, int n_atoms, const Derived& d,
                    const double* p, double* psi, double* out) {
   const int n = (int)band->n;
-  k_psi_rxn<<<(n_atoms + kPsiAtoms - 1) / kPsiAtoms, kPsiBlock, 0, ctx->stream>>>(
-      n, band->px, band->py, band->pz, band->nx, band->ny, band->nz, band->w, p, atoms, n_atoms, d.th1, d.kappa, d.h3,
-      psi);
-  k_finish<<<1, kBlock, 0, ctx->stream>>>(n_atoms, atoms, psi, n, band->w, d.h3, out);
+  auto launch = [&](auto kernel, int A) {
+    kernel<<<1 + (n_atoms + A - 1) / A, kPsiBlock, 0, ctx->stream>>>(n, band->px, band->py, band->pz, band->nx, band->ny,
+                                                                     band->nz, band->w, p, atoms, n_atoms, d.th1,
+                                                                     d.kappa, d.h3, psi, out + 2);
+  };
+  // One block fits a CU at a time; a turn over the nodes costs about its atoms and two thirds (the loads).
+  // So the atoms per block that need the least in turns of all CUs: for 1000 atoms 4 (121 µs; 8: 194,
+  // 2: 152), for 1991 8 (306; 4: 329), for 5000 4 (1382; 8: 1505), for 500 2 (69; 4: 84, 8: 136).
+  int best = 8;
+  double cost = INFINITY;
+  for (int A = 8; A >= 1; A /= 2) {
+    const double c = (double)(((n_atoms + A - 1) / A + ctx->n_cu - 1) / ctx->n_cu) * (A + 2.0 / 3.0);
+    if (c < cost) cost = c, best = A;
+  }
+  if (best == 8) launch(k_psi_rxn<8>, 8);
+  else if (best == 4) launch(k_psi_rxn<4>, 4);
+  else if (best == 2) launch(k_psi_rxn<2>, 2);
+  else launch(k_psi_rxn<1>, 1);
+  k_finish<<<1, kPsiBlock, 0, ctx->stream>>>(n_atoms, atoms, psi, out);
 }
 
 }  // namespace
@@ -181,9 +205,8 @@ pb_status noalloc_init(pb_ctx* ctx) {
 pb_status rhs(pb_ctx* ctx, const pb_band* band, const double* atoms, int n_atoms, const Derived& d, double* g) {
   const int n = (int)band->n;
   Scope t(ctx, "rhs");
-  k_rhs<<<(unsigned)((n + kBlock - 1) / kBlock), kBlock, 0, ctx->stream>>>(n, band->px, band->py, band->pz, band->nx,
-                                                                          band->ny, band->nz, atoms, n_atoms,
-                                                                          d.eps_in, g);
+  k_rhs<<<(unsigned)((n + 63) / 64), kRhsTile, 0, ctx->stream>>>(n, band->px, band->py, band->pz, band->nx, band->ny,
+                                                                 band->nz, atoms, n_atoms, d.eps_in, g);
   return launch_ok(ctx, "rhs");
 }
 
