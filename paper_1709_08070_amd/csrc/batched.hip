@@ -144,6 +144,8 @@ static __global__ void __launch_bounds__(kBlock) k_far64_sym_batch(const Item* _
                                                                    const double* __restrict__ wpsn, KParams kp,
                                                                    double k2, double* __restrict__ partial) {
   __shared__ Sym64Shared<4, 1> sh;
+  load_exp_table(sh.exp);
+  __syncthreads();
   for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
     const Item w = items[it];
     if (!active[w.mol]) continue;

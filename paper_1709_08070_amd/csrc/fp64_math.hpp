@@ -4,6 +4,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include "exp_table.hpp"
+
 namespace pb {
 
 // e^{−z} for z ≥ 0 in FP64 without branches (Cody–Waite reduction): k = rint(−z·log2 e),
@@ -30,6 +32,26 @@ __device__ __forceinline__ double exp_neg_f64(double z) {
   p = fma(p, t, 1.0);
   p = fma(p, t, 1.0);
   return ldexp(p, (int)k);
+}
+
+// The same with a table in LDS (tab: a copy of kExpTable, 2^{i/256} = T + T_lo): −z = (256q + i)·ln2/256 + r,
+// |r| ≤ ln2/512, e^{−z} = 2^q (T + (T(e^r − 1) + T_lo)), e^r − 1 to degree 4 (exp_coeffs.py, relative
+// error 9.5e-18): 12 FP64 instructions for 18, and one rounding of the sum where the polynomial alone has that of
+// its last two steps. Where 256z/ln2 exceeds an int (z > 5.8e6) the conversion saturates as v_cvt_i32_f64 is
+// defined to and the result is 0.
+__device__ __forceinline__ double exp_neg_tab_f64(double z, const double2* tab) {
+  const double k = __builtin_rint(z * -369.3299304675746);
+  int n;
+  asm("v_cvt_i32_f64 %0, %1" : "=v"(n) : "v"(k));
+  const double2 T = tab[n & 255];
+  const double r = fma(-k, 9.058776616587108e-20, fma(-k, 0.0027076061740622863, -z));
+  const double p = fma(r * fma(r, fma(r, 0.04166666857581546, 0.16666667812155952), 0.5), r, r);
+  return ldexp(T.x + fma(T.x, p, T.y), n >> 8);
+}
+
+// Copies kExpTable to LDS with the whole block; a barrier has to follow.
+__device__ __forceinline__ void load_exp_table(double2* tab) {
+  for (int q = threadIdx.x; q < 256; q += blockDim.x) tab[q] = kExpTable[q];
 }
 
 // 1/√x for x > 0: the hardware estimate y (about 2^-24 relative) and one third-order step of

@@ -42,6 +42,7 @@ struct Sym64Shared {
   double2 s0[2 * kStage], s1[2 * kStage], s2[2 * kStage], s3[2 * kStage];  // (x, y), (z, nx), (ny, nz), (wψ, wψn)
   double racc[TW][2][kStage];
   double box[TW * SW][6];  // per-wave bounding boxes (lo xyz, hi xyz) of a block reduction
+  double2 exp[256];        // kExpTable: the exponential's table
   double fsum[SW > 1 ? (SW - 1) * TW * 64 * 4 : 1];  // forward sums of the waves ws > 0
 };
 
@@ -98,8 +99,8 @@ __device__ __forceinline__ bool reg_f64(double r2, double dn, const KParams& kp)
 template <int kMetric>
 __device__ __forceinline__ void pair_sym_f64(double xi, double yi, double zi, double nxi, double nyi, double nzi,
                                              double wpi, double wni, const double2& s0, const double2& s1,
-                                             const double2& s2, const double2& s3, const KParams& kp, double& f1,
-                                             double& f2, double& g1, double& g2) {
+                                             const double2& s2, const double2& s3, const KParams& kp,
+                                             const double2* tab, double& f1, double& f2, double& g1, double& g2) {
   const double xj = s0.x, yj = s0.y, zj = s1.x, nxj = s1.y, nyj = s2.x, nzj = s2.y, wpj = s3.x, wnj = s3.y;
   const double dx = xi - xj, dy = yi - yj, dz = zi - zj;
   const double r2 = __dadd_rn(__dadd_rn(__dmul_rn(dx, dx), __dmul_rn(dy, dy)), __dmul_rn(dz, dz));
@@ -116,7 +117,7 @@ __device__ __forceinline__ void pair_sym_f64(double xi, double yi, double zi, do
   const double r3 = rinv * rinv * rinv;
   const double r5 = r3 * rinv * rinv;
   const double z = kp.kappa * r;
-  const double E = exp_neg_f64(z);
+  const double E = exp_neg_tab_f64(z, tab);
   const double a = E * (1.0 + z);
   const double b = E * (3.0 + 3.0 * z + z * z);
   const double k12 = (1.0 - E) * rinv;
@@ -132,11 +133,14 @@ __device__ __forceinline__ void pair_sym_f64(double xi, double yi, double zi, do
 }
 
 // Both directions of a pair that cannot be regularized (far sub-block pairs): the same
-// kernels as pair_sym_f64's regular branch, the products free to fuse. k2 = κ².
+// kernels as pair_sym_f64's regular branch, the products free to fuse. k2 = κ². Bound by FP64 issue
+// (62 instructions): with the polynomial exponential 67, 2.77 ms for 45,818 nodes against 2.69 with the
+// table, whose gathers are few enough here (in the energy's pair loop, 39 instructions, they cost what
+// they save).
 __device__ __forceinline__ void pair_sym_f64_far(double xi, double yi, double zi, double nxi, double nyi, double nzi,
                                                  double wpi, double wni, const double2& s0, const double2& s1,
                                                  const double2& s2, const double2& s3, const KParams& kp, double k2,
-                                                 double& f1, double& f2, double& g1, double& g2) {
+                                                 const double2* tab, double& f1, double& f2, double& g1, double& g2) {
   const double xj = s0.x, yj = s0.y, zj = s1.x, nxj = s1.y, nyj = s2.x, nzj = s2.y, wpj = s3.x, wnj = s3.y;
   const double dx = xi - xj, dy = yi - yj, dz = zi - zj;
   const double r2 = fma(dz, dz, fma(dy, dy, dx * dx));
@@ -147,7 +151,7 @@ __device__ __forceinline__ void pair_sym_f64_far(double xi, double yi, double zi
   const double ri2 = rinv * rinv;
   const double r3 = ri2 * rinv;
   const double z = kp.kappa * (r2 * rinv);
-  const double E = exp_neg_f64(z);
+  const double E = exp_neg_tab_f64(z, tab);
   const double a = fma(E, z, E);                    // E(1 + z)
   const double k12 = fma(-E, rinv, rinv);           // (1 − E)/r
   // with b = E(3 + 3z + z²) = 3a + Ez²: −(3 − b)/r² = 3(a − 1)/r² + Eκ² (3u as 4u − u keeps
@@ -185,11 +189,11 @@ __device__ __forceinline__ void sym64_group(int g, double xa, double ya, double 
     const int q = q0 + s;
     const double2 c0 = sh.s0[q], c1 = sh.s1[q], c2 = sh.s2[q], c3 = sh.s3[q];
     if (kFar) {
-      pair_sym_f64_far(xa, ya, za, nxa, nya, nza, wpa, wna, c0, c1, c2, c3, kp, k2, f[0], f[1], ra1, ra2);
-      pair_sym_f64_far(xb, yb, zb, nxb, nyb, nzb, wpb, wnb, c0, c1, c2, c3, kp, k2, f[2], f[3], ra1, ra2);
+      pair_sym_f64_far(xa, ya, za, nxa, nya, nza, wpa, wna, c0, c1, c2, c3, kp, k2, sh.exp, f[0], f[1], ra1, ra2);
+      pair_sym_f64_far(xb, yb, zb, nxb, nyb, nzb, wpb, wnb, c0, c1, c2, c3, kp, k2, sh.exp, f[2], f[3], ra1, ra2);
     } else {
-      pair_sym_f64<kMetric>(xa, ya, za, nxa, nya, nza, wpa, wna, c0, c1, c2, c3, kp, f[0], f[1], ra1, ra2);
-      pair_sym_f64<kMetric>(xb, yb, zb, nxb, nyb, nzb, wpb, wnb, c0, c1, c2, c3, kp, f[2], f[3], ra1, ra2);
+      pair_sym_f64<kMetric>(xa, ya, za, nxa, nya, nza, wpa, wna, c0, c1, c2, c3, kp, sh.exp, f[0], f[1], ra1, ra2);
+      pair_sym_f64<kMetric>(xb, yb, zb, nxb, nyb, nzb, wpb, wnb, c0, c1, c2, c3, kp, sh.exp, f[2], f[3], ra1, ra2);
     }
     ra1 = shfl_next(ra1, next);
     ra2 = shfl_next(ra2, next);
@@ -371,6 +375,8 @@ static __global__ void __attribute__((unused)) __launch_bounds__(64 * TW * SW) _
                   const int* __restrict__ skip) {
   if (skip && *skip) return;
   __shared__ Sym64Shared<TW, SW> sh;
+  load_exp_table(sh.exp);
+  __syncthreads();
   for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
     const int2 w = items[it];
     sym64_item(b, wpsi, wpsn, n, w.x, w.y, nsub, kp, k2, partial, sh);
