@@ -10,7 +10,7 @@
 // autotuner (each candidate timed once).
 //
 // Krylov: every molecule runs its own GMRES (FP64 Arnoldi with CGS2, Givens rotations on the
-// device, one thread per molecule). The vectors of all molecules are concatenated, molecule m
+// device, one wave per molecule). The vectors of all molecules are concatenated, molecule m
 // owning [2·off_m, 2·off_m + 2·n_m) as [ψ̄ | ψ̄_n]. One Arnoldi step of the whole batch —
 // pack, far field, near field, reduce, two Gram–Schmidt passes, norm, Givens, scaling — is
 // captured once as a hipGraph and replayed; the step index lives in device memory, so the
@@ -42,7 +42,9 @@
 namespace pb {
 namespace {
 
-constexpr int kSeg = 4096;  // vector elements per block in the batched reductions
+constexpr int kSeg = 4 * kBlock;  // vector elements per block of the Krylov kernels: four per thread
+
+constexpr int kMaxRestart = 1000;  // of pb_solve_opts
 
 struct MolDev {
   int off;          // first node in the concatenated node index
@@ -253,32 +255,83 @@ struct Segs {
   const int* first;  // first block of each molecule (n_mol + 1 entries)
 };
 
-// partial[b·(m+1) + q] = Σ_{e in block b} w[e]·V[q][e] for q ≤ k (k = *kptr, or kfix when kptr
-// is null), w = V[k+1] (or wfix).
-static __global__ void __launch_bounds__(kBlock) k_dots_batch(int nseg, Segs sg, const int* __restrict__ active,
+// The four elements of a segment that a thread owns, two and two (segments start and end on even
+// elements); zeros beyond its end.
+struct Four {
+  double2 a, b;
+};
+__device__ __forceinline__ Four seg_load(const double* __restrict__ v, int64_t lo, int64_t hi) {
+  const int64_t e = lo + 2 * (int)threadIdx.x, f = e + 2 * kBlock;
+  const double2 z = make_double2(0.0, 0.0);
+  return {e < hi ? *(const double2*)(v + e) : z, f < hi ? *(const double2*)(v + f) : z};
+}
+__device__ __forceinline__ void seg_store(double* __restrict__ v, int64_t lo, int64_t hi, const Four& x) {
+  const int64_t e = lo + 2 * (int)threadIdx.x, f = e + 2 * kBlock;
+  if (e < hi) *(double2*)(v + e) = x.a;
+  if (f < hi) *(double2*)(v + f) = x.b;
+}
+
+// Sums of kDotCols columns over the block in a fixed order, column u to out[u] for u < cols. red: a
+// block's scratch; barriers before and after its use are inside.
+constexpr int kDotCols = 8;
+__device__ __forceinline__ void block_sums(const double (&acc)[kDotCols], int cols, double (&red)[kBlock / 64][kDotCols],
+                                           double* __restrict__ out) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  // three halvings leave lane l with column l & 7 summed over its group of eight
+  double h[4], q[2], r;
+  const bool o1 = lane & 1, o2 = lane & 2, o4 = lane & 4;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) h[u] = (o4 ? acc[4 + u] : acc[u]) + __shfl_xor(o4 ? acc[u] : acc[4 + u], 4);
+#pragma unroll
+  for (int u = 0; u < 2; ++u) q[u] = (o2 ? h[2 + u] : h[u]) + __shfl_xor(o2 ? h[u] : h[2 + u], 2);
+  r = (o1 ? q[1] : q[0]) + __shfl_xor(o1 ? q[0] : q[1], 1);
+  for (int off = 8; off < 64; off <<= 1) r += __shfl_xor(r, off);
+  if (lane < kDotCols) red[wave][lane] = r;
+  __syncthreads();
+  if ((int)threadIdx.x < cols) {
+    double t = red[0][threadIdx.x];
+    for (int w = 1; w < kBlock / 64; ++w) t += red[w][threadIdx.x];
+    out[threadIdx.x] = t;
+  }
+  __syncthreads();
+}
+
+__device__ __forceinline__ double dot4(const Four& x, const Four& y) {
+  return (x.a.x * y.a.x + x.a.y * y.a.y) + (x.b.x * y.b.x + x.b.y * y.b.y);
+}
+
+// out[q] = Σ_e w[e]·V[q][e] over the segment for q < nq.
+__device__ __forceinline__ void seg_dots(const Four& w, const double* __restrict__ V, int64_t ldv, int nq, int64_t lo,
+                                         int64_t hi, double (&red)[kBlock / 64][kDotCols], double* __restrict__ out) {
+  for (int q = 0; q < nq; q += kDotCols) {
+    double acc[kDotCols];
+    Four v[kDotCols];
+#pragma unroll
+    for (int u = 0; u < kDotCols; ++u) v[u] = seg_load(V + (int64_t)min(q + u, nq - 1) * ldv, lo, hi);
+#pragma unroll
+    for (int u = 0; u < kDotCols; ++u) acc[u] = dot4(w, v[u]);
+    block_sums(acc, min(kDotCols, nq - q), red, out + q);
+  }
+}
+
+// partial[b·mstride + q] = Σ_{e in block b} w[e]·V[q][e] for q ≤ k (k = *kptr, or q < nq_fixed when
+// kptr is null), w = V[k+1] (or wfix). Bound by the reads of V. A block keeps its 1024 elements of w and reads
+// eight vectors at a time; with 4096 elements a block and a block reduction per vector the ten molecules of
+// 13,000 to 46,000 nodes had 135 blocks waiting in turn, and the four
+// passes of a step took 296 µs on average; these and k_axpy_batch take 50.
+static __global__ void __launch_bounds__(kBlock) k_dots_batch(Segs sg, const int* __restrict__ active,
                                                               const double* __restrict__ V, int64_t ldv,
                                                               const int* __restrict__ kptr, int kmax, int nq_fixed,
                                                               const double* __restrict__ wfix, int mstride,
                                                               double* __restrict__ partial) {
-  __shared__ double red[kBlock];
+  __shared__ double red[kBlock / 64][kDotCols];
   const int b = blockIdx.x;
-  if (b >= nseg || !active[sg.mol[b]]) return;
+  if (!active[sg.mol[b]]) return;
   if (kptr && *kptr >= kmax) return;
   const int nq = kptr ? *kptr + 1 : nq_fixed;
-  const double* w = wfix ? wfix : V + (int64_t)nq * ldv;
-  for (int q = 0; q < nq; ++q) {
-    const double* vq = V + (int64_t)q * ldv;
-    double a = 0.0;
-    for (int64_t e = sg.lo[b] + threadIdx.x; e < sg.hi[b]; e += kBlock) a += w[e] * vq[e];
-    red[threadIdx.x] = a;
-    __syncthreads();
-    for (int off = kBlock / 2; off > 0; off >>= 1) {
-      if (threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
-      __syncthreads();
-    }
-    if (threadIdx.x == 0) partial[(int64_t)b * mstride + q] = red[0];
-    __syncthreads();
-  }
+  const int64_t lo = sg.lo[b], hi = sg.hi[b];
+  const Four w = seg_load(wfix ? wfix : V + (int64_t)nq * ldv, lo, hi);
+  seg_dots(w, V, ldv, nq, lo, hi, red, partial + (int64_t)b * mstride);
 }
 
 // out[mol·ostride + q] = Σ_{blocks of mol} partial[b·mstride + q]; sqrt if asked.
@@ -304,25 +357,40 @@ static __global__ void __launch_bounds__(64) k_dots_finish_batch(int n_mol, Segs
   if (threadIdx.x == 0) out[(int64_t)mol * ostride + q] = sqrt_out ? sqrt(red[0]) : red[0];
 }
 
-// w[e] += sign·Σ_{q<nq} c[mol][q] V[q][e] over each active molecule's elements.
-static __global__ void __launch_bounds__(kBlock) k_axpy_batch(int nseg, Segs sg, const int* __restrict__ active,
+// w[e] += sign·Σ_{q<nq} c[mol][q] V[q][e] over each active molecule's elements, then of the new w per
+// block, into partial: kAxpyDots its products with V[0..nq−1] (the next Gram–Schmidt pass), kAxpyNorm
+// its squared norm.
+constexpr int kAxpyOnly = 0, kAxpyDots = 1, kAxpyNorm = 2;
+template <int kThen>
+static __global__ void __launch_bounds__(kBlock) k_axpy_batch(Segs sg, const int* __restrict__ active,
                                                               const double* __restrict__ V, int64_t ldv,
                                                               const int* __restrict__ kptr, int kmax,
                                                               const int* __restrict__ nq_mol,
                                                               const double* __restrict__ c, int cstride, double sign,
-                                                              double* __restrict__ wfix) {
+                                                              double* __restrict__ wfix, int mstride,
+                                                              double* __restrict__ partial) {
+  __shared__ double red[kBlock / 64][kDotCols];
   const int b = blockIdx.x;
-  if (b >= nseg) return;
   const int mol = sg.mol[b];
   if (!active[mol]) return;
   if (kptr && *kptr >= kmax) return;
   const int nq = kptr ? *kptr + 1 : nq_mol[mol];
-  double* w = wfix ? wfix : const_cast<double*>(V) + (int64_t)nq * ldv;
+  const int64_t lo = sg.lo[b], hi = sg.hi[b];
+  double* wv = wfix ? wfix : const_cast<double*>(V) + (int64_t)nq * ldv;
   const double* cm = c + (int64_t)mol * cstride;
-  for (int64_t e = sg.lo[b] + threadIdx.x; e < sg.hi[b]; e += kBlock) {
-    double s = 0.0;
-    for (int q = 0; q < nq; ++q) s += cm[q] * V[(int64_t)q * ldv + e];
-    w[e] += sign * s;
+  Four w = seg_load(wv, lo, hi), s{};
+#pragma unroll 8
+  for (int q = 0; q < nq; ++q) {
+    const Four v = seg_load(V + (int64_t)q * ldv, lo, hi);
+    const double cq = cm[q];
+    s.a.x += cq * v.a.x, s.a.y += cq * v.a.y, s.b.x += cq * v.b.x, s.b.y += cq * v.b.y;
+  }
+  w.a.x += sign * s.a.x, w.a.y += sign * s.a.y, w.b.x += sign * s.b.x, w.b.y += sign * s.b.y;
+  seg_store(wv, lo, hi, w);
+  if (kThen == kAxpyDots) seg_dots(w, V, ldv, nq, lo, hi, red, partial + (int64_t)b * mstride);
+  if (kThen == kAxpyNorm) {
+    const double acc[kDotCols] = {dot4(w, w)};
+    block_sums(acc, 1, red, partial + (int64_t)b * mstride);
   }
 }
 
@@ -345,89 +413,87 @@ static __global__ void __launch_bounds__(kBlock) k_scale_batch(int nseg, Segs sg
   for (int64_t e = sg.lo[b] + threadIdx.x; e < sg.hi[b]; e += kBlock) dst[e] = src[e] * s;
 }
 
-// One thread per molecule: the new Hessenberg column from the two Gram–Schmidt passes and
-// the norm, the previous rotations, a new rotation, the residual estimate and the stop test.
-static __global__ void k_givens_batch(int n_mol, int m, const int* __restrict__ kptr, const double* __restrict__ h,
-                                      int hstride, double* __restrict__ H, double* __restrict__ cs,
-                                      double* __restrict__ sn, double* __restrict__ s, KState* __restrict__ st,
-                                      int* __restrict__ active, int* __restrict__ n_active) {
-  const int mol = blockIdx.x * blockDim.x + threadIdx.x;
-  if (mol >= n_mol || !active[mol]) return;
+// One wave per molecule: the norm of the new vector from its blocks' partial sums, the new Hessenberg
+// column from the two Gram–Schmidt passes, the previous rotations (staged in LDS, they follow one another),
+// a new rotation, the residual estimate and the stop test.
+static __global__ void __launch_bounds__(64) k_givens_batch(int m, Segs sg, const double* __restrict__ npart,
+                                                            const int* __restrict__ kptr, double* __restrict__ h,
+                                                            int hstride, double* __restrict__ H, double* __restrict__ cs,
+                                                            double* __restrict__ sn, double* __restrict__ s,
+                                                            KState* __restrict__ st, int* __restrict__ active,
+                                                            int* __restrict__ n_active) {
+  __shared__ double col[kMaxRestart + 1], lc[kMaxRestart], ls[kMaxRestart];
+  const int mol = blockIdx.x, lane = threadIdx.x;
+  if (!active[mol]) return;
   const int k = *kptr;
   if (k >= m) return;
-  const double* hm = h + (int64_t)mol * hstride;  // [pass1 (m+1) | pass2 (m+1) | norm]
+  double* hm = h + (int64_t)mol * hstride;  // [pass1 (m+1) | pass2 (m+1) | norm]
   double* Hm = H + (int64_t)mol * (m + 1) * m;
   double* csm = cs + (int64_t)mol * m;
   double* snm = sn + (int64_t)mol * m;
   double* sm = s + (int64_t)mol * (m + 1);
-  const double hn = hm[2 * (m + 1)];
-  for (int i = 0; i <= k; ++i) Hm[(int64_t)i * m + k] = hm[i] + hm[(m + 1) + i];
-  Hm[(int64_t)(k + 1) * m + k] = hn;
-  for (int i = 0; i < k; ++i) {
-    const double a = Hm[(int64_t)i * m + k], b = Hm[(int64_t)(i + 1) * m + k];
-    Hm[(int64_t)i * m + k] = csm[i] * a + snm[i] * b;
-    Hm[(int64_t)(i + 1) * m + k] = -snm[i] * a + csm[i] * b;
+  for (int i = lane; i <= k; i += 64) {
+    col[i] = hm[i] + hm[(m + 1) + i];
+    if (i < k) lc[i] = csm[i], ls[i] = snm[i];
   }
-  const double a = Hm[(int64_t)k * m + k], b = Hm[(int64_t)(k + 1) * m + k];
-  const double den = sqrt(a * a + b * b);
-  csm[k] = den > 0 ? a / den : 1.0;
-  snm[k] = den > 0 ? b / den : 0.0;
-  Hm[(int64_t)k * m + k] = den;
-  Hm[(int64_t)(k + 1) * m + k] = 0.0;
-  sm[k + 1] = -snm[k] * sm[k];
-  sm[k] = csm[k] * sm[k];
-  st[mol].k_used = k + 1;
-  st[mol].iters += 1;
-  const bool reached = fabs(sm[k + 1]) <= st[mol].tol_abs || !(hn > 0.0);
-  if (reached || k + 1 >= m) {
-    st[mol].early = reached;
-    st[mol].t_inner = wall_clock64();
-    active[mol] = 0;
-    atomicSub(n_active, 1);
-  }
-}
-
-// partial[b] = Σ_{e in block b} w[e]² with w = V[*kptr + 1].
-static __global__ void __launch_bounds__(kBlock) k_wnorm_batch(int nseg, Segs sg, const int* __restrict__ active,
-                                                               const double* __restrict__ V, int64_t ldv,
-                                                               const int* __restrict__ kptr, int kmax,
-                                                               double* __restrict__ partial) {
-  __shared__ double red[kBlock];
-  const int b = blockIdx.x;
-  if (b >= nseg || !active[sg.mol[b]]) return;
-  if (*kptr >= kmax) return;
-  const double* w = V + (int64_t)(*kptr + 1) * ldv;
-  double a = 0.0;
-  for (int64_t e = sg.lo[b] + threadIdx.x; e < sg.hi[b]; e += kBlock) a += w[e] * w[e];
-  red[threadIdx.x] = a;
+  double n2 = 0.0;
+  for (int b = sg.first[mol] + lane; b < sg.first[mol + 1]; b += 64) n2 += npart[b];
+  for (int off = 32; off > 0; off >>= 1) n2 += __shfl_xor(n2, off);
   __syncthreads();
-  for (int off = kBlock / 2; off > 0; off >>= 1) {
-    if (threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
-    __syncthreads();
+  if (lane == 0) {
+    const double hn = sqrt(n2);
+    hm[2 * (m + 1)] = hn;
+    double a = col[0];
+    for (int i = 0; i < k; ++i) {
+      const double b = col[i + 1];
+      col[i] = lc[i] * a + ls[i] * b;
+      a = -ls[i] * a + lc[i] * b;
+    }
+    const double den = sqrt(a * a + hn * hn);
+    const double c = den > 0 ? a / den : 1.0, z = den > 0 ? hn / den : 0.0, sk = sm[k];
+    csm[k] = c;
+    snm[k] = z;
+    col[k] = den;
+    sm[k + 1] = -z * sk;
+    sm[k] = c * sk;
+    st[mol].k_used = k + 1;
+    st[mol].iters += 1;
+    const bool reached = fabs(z * sk) <= st[mol].tol_abs || !(hn > 0.0);
+    if (reached || k + 1 >= m) {
+      st[mol].early = reached;
+      st[mol].t_inner = wall_clock64();
+      active[mol] = 0;
+      atomicSub(n_active, 1);
+    }
   }
-  if (threadIdx.x == 0) partial[b] = red[0];
+  __syncthreads();
+  for (int i = lane; i <= k; i += 64) Hm[(int64_t)i * m + k] = col[i];
+  if (lane == 0) Hm[(int64_t)(k + 1) * m + k] = 0.0;
 }
 
 static __global__ void k_advance(int* kptr, int kmax) {
   if (*kptr < kmax) *kptr += 1;
 }
 
-// One thread per molecule: y = H⁻¹ s over the k_used steps (upper triangular).
-static __global__ void k_trisolve_batch(int n_mol, int m, const int* __restrict__ cycle_active,
-                                        const double* __restrict__ H, const double* __restrict__ s,
-                                        const KState* __restrict__ st, double* __restrict__ y, int* __restrict__ nq) {
-  const int mol = blockIdx.x * blockDim.x + threadIdx.x;
-  if (mol >= n_mol) return;
+// One wave per molecule: y = H⁻¹ s over the k_used steps (upper triangular).
+static __global__ void __launch_bounds__(64) k_trisolve_batch(int m, const int* __restrict__ cycle_active,
+                                                              const double* __restrict__ H, const double* __restrict__ s,
+                                                              const KState* __restrict__ st, double* __restrict__ y,
+                                                              int* __restrict__ nq) {
+  __shared__ double ys[kMaxRestart];
+  const int mol = blockIdx.x, lane = threadIdx.x;
   const int k = cycle_active[mol] ? st[mol].k_used : 0;
-  nq[mol] = k;
   const double* Hm = H + (int64_t)mol * (m + 1) * m;
   const double* sm = s + (int64_t)mol * (m + 1);
-  double* ym = y + (int64_t)mol * m;
   for (int i = k - 1; i >= 0; --i) {
-    double acc = sm[i];
-    for (int j = i + 1; j < k; ++j) acc -= Hm[(int64_t)i * m + j] * ym[j];
-    ym[i] = acc / Hm[(int64_t)i * m + i];
+    double acc = 0.0;
+    for (int j = i + 1 + lane; j < k; j += 64) acc += Hm[(int64_t)i * m + j] * ys[j];
+    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+    if (lane == 0) ys[i] = (sm[i] - acc) / Hm[(int64_t)i * m + i];
+    __syncthreads();
   }
+  for (int i = lane; i < k; i += 64) y[(int64_t)mol * m + i] = ys[i];
+  if (lane == 0) nq[mol] = k;
 }
 
 // Start of a cycle: s = [β, 0, …], active, tolerance; one thread per molecule.
@@ -748,7 +814,7 @@ void op_mixed(Batch& B, const double* x, double* y, const int* kptr, int64_t ldv
 
 // Per-molecule 2-norms of v over the molecules in sel, into out[mol].
 void norms(Batch& B, const double* v, const int* sel, double* out) {
-  k_dots_batch<<<B.nseg, kBlock, 0, B.st>>>(B.nseg, B.segs, sel, v, 0, nullptr, 0, 1, v, 1, B.dpart);
+  k_dots_batch<<<B.nseg, kBlock, 0, B.st>>>(B.segs, sel, v, 0, nullptr, 0, 1, v, 1, B.dpart);
   k_dots_finish_batch<<<dim3(B.n_mol, 1), 64, 0, B.st>>>(B.n_mol, B.segs, sel, B.dpart, 1, nullptr, 0, 1, out, 1, 1);
 }
 
@@ -763,20 +829,20 @@ void arnoldi_step(Batch& B, bool prec) {
   } else {
     op_mixed(B, B.V, B.V, B.kptr, B.M, B.active);
   }
+  k_dots_batch<<<B.nseg, kBlock, 0, B.st>>>(B.segs, B.active, B.V, B.M, B.kptr, m, 0, nullptr, m + 1, B.dpart);
   for (int pass = 0; pass < 2; ++pass) {
     double* hv = B.hbuf + pass * (m + 1);
-    k_dots_batch<<<B.nseg, kBlock, 0, B.st>>>(B.nseg, B.segs, B.active, B.V, B.M, B.kptr, m, 0, nullptr, m + 1,
-                                              B.dpart);
     k_dots_finish_batch<<<dim3(B.n_mol, m), 64, 0, B.st>>>(B.n_mol, B.segs, B.active, B.dpart, m + 1, B.kptr, m, 0, hv,
                                                            hs, 0);
-    k_axpy_batch<<<B.nseg, kBlock, 0, B.st>>>(B.nseg, B.segs, B.active, B.V, B.M, B.kptr, m, nullptr, hv, hs, -1.0,
-                                              nullptr);
+    if (pass == 0)
+      k_axpy_batch<kAxpyDots><<<B.nseg, kBlock, 0, B.st>>>(B.segs, B.active, B.V, B.M, B.kptr, m, nullptr, hv, hs, -1.0,
+                                                           nullptr, m + 1, B.dpart);
+    else
+      k_axpy_batch<kAxpyNorm><<<B.nseg, kBlock, 0, B.st>>>(B.segs, B.active, B.V, B.M, B.kptr, m, nullptr, hv, hs, -1.0,
+                                                           nullptr, 1, B.dpart);
   }
-  k_wnorm_batch<<<B.nseg, kBlock, 0, B.st>>>(B.nseg, B.segs, B.active, B.V, B.M, B.kptr, m, B.dpart);
-  k_dots_finish_batch<<<dim3(B.n_mol, 1), 64, 0, B.st>>>(B.n_mol, B.segs, B.active, B.dpart, 1, nullptr, 0, 1,
-                                                         B.hbuf + 2 * (m + 1), hs, 1);
-  k_givens_batch<<<(B.n_mol + 63) / 64, 64, 0, B.st>>>(B.n_mol, m, B.kptr, B.hbuf, hs, B.H, B.cs, B.sn, B.s, B.kst,
-                                                       B.active, B.n_active);
+  k_givens_batch<<<B.n_mol, 64, 0, B.st>>>(m, B.segs, B.dpart, B.kptr, B.hbuf, hs, B.H, B.cs, B.sn, B.s, B.kst,
+                                           B.active, B.n_active);
   k_scale_batch<<<B.nseg, kBlock, 0, B.st>>>(B.nseg, B.segs, B.active, B.V, B.M, B.kptr, m, 1, 1, nullptr,
                                              B.hbuf + 2 * (m + 1), hs);
   k_advance<<<1, 1, 0, B.st>>>(B.kptr, m);
@@ -796,7 +862,7 @@ extern "C" pb_status pb_ibim_solve_batched(pb_ctx* ctx, int n_mol, const pb_band
   pb_solve_opts opts;
   if (opts_in) opts = *opts_in;
   else pb_default_solve_opts(&opts);
-  if (!(opts.tol > 0.0) || opts.max_iter < 1 || opts.restart < 1 || opts.restart > 1000)
+  if (!(opts.tol > 0.0) || opts.max_iter < 1 || opts.restart < 1 || opts.restart > kMaxRestart)
     return ctx->fail(PB_EINVAL, "bad tolerance or iteration limits");
   if (opts.precision != PB_FP64 && opts.precision != PB_MIXED) return ctx->fail(PB_EINVAL, "unknown precision");
   if (prm->reg_metric == PB_REG_TANGENT)
@@ -1135,9 +1201,9 @@ extern "C" pb_status pb_ibim_solve_batched(pb_ctx* ctx, int n_mol, const pb_band
       // iterations actually taken this cycle per molecule
       std::vector<KState> ks(n_mol);
       PB_HIP(ctx, hipMemcpyAsync(ks.data(), B.kst, sizeof(KState) * n_mol, hipMemcpyDeviceToHost, B.st));
-      k_trisolve_batch<<<(n_mol + 63) / 64, 64, 0, B.st>>>(n_mol, m, B.cycle, B.H, B.s, B.kst, B.ybuf, B.nq);
-      k_axpy_batch<<<B.nseg, kBlock, 0, B.st>>>(B.nseg, B.segs, B.cycle, with_prec ? B.Z : B.V, B.M, nullptr, m, B.nq,
-                                                B.ybuf, m, 1.0, sol);
+      k_trisolve_batch<<<n_mol, 64, 0, B.st>>>(m, B.cycle, B.H, B.s, B.kst, B.ybuf, B.nq);
+      k_axpy_batch<kAxpyOnly><<<B.nseg, kBlock, 0, B.st>>>(B.segs, B.cycle, with_prec ? B.Z : B.V, B.M, nullptr, m, B.nq,
+                                                           B.ybuf, m, 1.0, sol, 0, nullptr);
       PB_HIP(ctx, hipStreamSynchronize(B.st));
       int maxk = 0;
       for (int i = 0; i < n_mol; ++i)
