@@ -280,9 +280,16 @@ __global__ void __launch_bounds__(kBlock) k_rms_partial(int n, const double* __r
   }
 }
 
-// One block: strided partial sums per thread, then a fixed tree over the block.
-__global__ void __launch_bounds__(kBlock) k_rms_finish(int n, int nb, const double* __restrict__ part,
-                                                       double* __restrict__ s) {
+// The two inputs of a node as the network reads them: v/s per half, BF16, the first in the low bits.
+__device__ __forceinline__ uint32_t input_pair(double v1, double v2, double s1, double s2) {
+  return (uint32_t)bf16_bits((float)(v1 / s1)) | (uint32_t)bf16_bits((float)(v2 / s2)) << 16;
+}
+
+// s from the partial sums of k_rms_partial (strided sums per thread, then a fixed tree: every block forms
+// it for itself, block 0 stores it), and the scaled inputs of every node.
+__global__ void __launch_bounds__(kBlock) k_pack_in(int n, int nb, const double* __restrict__ part,
+                                                    const double* __restrict__ v, double* __restrict__ s,
+                                                    uint32_t* __restrict__ vs) {
   __shared__ double r1[kBlock], r2[kBlock];
   double a = 0.0, c = 0.0;
   for (int q = threadIdx.x; q < nb; q += kBlock) {
@@ -299,110 +306,122 @@ __global__ void __launch_bounds__(kBlock) k_rms_finish(int n, int nb, const doub
     }
     __syncthreads();
   }
-  if (threadIdx.x == 0) {
-    a = sqrt(r1[0] / n);
-    c = sqrt(r2[0] / n);
-    s[0] = a > 0.0 ? a : 1.0;
-    s[1] = c > 0.0 ? c : 1.0;
+  a = sqrt(r1[0] / n);
+  c = sqrt(r2[0] / n);
+  a = a > 0.0 ? a : 1.0;
+  c = c > 0.0 ? c : 1.0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    s[0] = a;
+    s[1] = c;
   }
+  const int i = blockIdx.x * kBlock + threadIdx.x;
+  if (i < n) vs[i] = input_pair(v[i], v[n + i], a, c);
 }
 
-// Layer-1 input rows G1[i] = 16 slots × 16 features (BF16).
+// Layer-1 input rows G1[i] = 16 slots × 16 features (BF16), all but features 5 and 6, the neighbour's scaled
+// inputs, which layer 1 puts in from vs: a solve applies the network to many inputs on one geometry.
 __global__ void __launch_bounds__(kBlock) k_build_g1(int n, BandDev b, const int* __restrict__ nbr,
-                                                     const float* __restrict__ feat, const double* __restrict__ v,
-                                                     const double* __restrict__ s, double eps,
+                                                     const float* __restrict__ feat, double eps,
                                                      uint16_t* __restrict__ G1) {
   const int t = blockIdx.x * kBlock + threadIdx.x;
   if (t >= n * kSlots) return;
   const int i = t / kSlots, slot = t % kSlots;
   const int j = nbr[(int64_t)i * kSlots + slot];
   const float* fj = feat + (int64_t)j * 5;
-  float f[16];
-  f[0] = fj[0];
-  f[1] = fj[1];
-  f[2] = fj[2];
-  f[3] = fj[3];
-  f[4] = fj[4];
-  f[5] = (float)(v[j] / s[0]);
-  f[6] = (float)(v[n + j] / s[1]);
-  f[7] = (float)((b.px[j] - b.px[i]) / eps);
-  f[8] = (float)((b.py[j] - b.py[i]) / eps);
-  f[9] = (float)((b.pz[j] - b.pz[i]) / eps);
-  for (int q = 10; q < 16; ++q) f[q] = 0.f;
-  uint16_t* out = G1 + (int64_t)t * 16;
-  for (int q = 0; q < 16; ++q) out[q] = bf16_bits(f[q]);
+  const float lo[8] = {fj[0], fj[1], fj[2], fj[3], fj[4], 0.f, 0.f, (float)((b.px[j] - b.px[i]) / eps)};
+  const float hi[8] = {(float)((b.py[j] - b.py[i]) / eps), (float)((b.pz[j] - b.pz[i]) / eps), 0.f, 0.f, 0.f, 0.f, 0.f,
+                       0.f};
+  bf16x8_t* out = reinterpret_cast<bf16x8_t*>(G1 + (int64_t)t * 16);
+  out[0] = pack8(lo);
+  out[1] = pack8(hi);
 }
 
 // ---------------------------------------------------------------- forward
 
-// Z = A·W + b for 16-node wave tiles; A rows are G1 (dense, BF16, K = 256) or the gathered
-// BF16 activations of the 16 neighbour slots (8 channels, one 16-byte load per lane and
-// step). kAct (hidden layers) applies the leaky ReLU and stores BF16, rounded to nearest even
-// once here (the rounding every consumer applies: the next layer's MFMA operand and the
-// weight gradient's); the output layer stores FP32. Block = 4 waves = 64 nodes. The BF16 weights are staged in LDS in chunks of
-// kWChunk columns and shared by the block's four waves (each wave would otherwise stream the
-// whole matrix from the caches); rows are padded by 8 elements so that the 16 rows a wave
-// reads at one column offset fall on different banks.
-constexpr int kWChunk = 256;
+// Z = A·W + b for 16-node wave tiles; A rows are G1 (dense, BF16, K = 256) with the neighbours' inputs
+// vs put in (and, for the weight gradient, stored back into G1 if asked), or the gathered BF16
+// activations of the 16 neighbour slots (8 channels, one 16-byte load per lane and step). kAct (hidden
+// layers) applies the leaky ReLU and stores BF16, rounded to nearest even once here (the rounding every
+// consumer applies: the next layer's MFMA operand and the weight gradient's); the output layer stores
+// FP32. The BF16 weights are staged in LDS in chunks of kWChunk columns and shared by the block's W waves
+// (each wave would otherwise stream the whole matrix from the caches); rows are padded by 8 elements so
+// that the 16 rows a wave reads at one column offset fall on different banks. Bound by the latency of the
+// gathers, chunk after chunk, so by the waves in flight: chunks of 128 columns leave room for four a SIMD
+// (256 columns, 150 VGPRs with the weights loaded ahead: two), and the weights of the next chunk are loaded
+// before this one's products. A layer of 64 → 64 at 45,818 nodes 27.8 → 18.0 µs, 64 → 16 17.8 → 13.5.
+constexpr int kWChunk = 128;
 constexpr int kWPad = 8;
-constexpr int kFwdWaves = 8;  // 128 nodes per block: each staged weight chunk serves twice as many nodes
-constexpr int kFwdNodes = 16 * kFwdWaves;
 
-template <bool kDense, int CIN, int COUT, bool kAct>
-__global__ void __launch_bounds__(64 * kFwdWaves) k_layer_fwd(int n, const uint16_t* __restrict__ G1,
-                                                   const uint16_t* __restrict__ X, const int* __restrict__ nbr,
-                                                   const uint16_t* __restrict__ Wt, const float* __restrict__ bias,
-                                                   std::conditional_t<kAct, uint16_t, float>* __restrict__ Y,
-                                                   const int* __restrict__ skip) {
+template <bool kDense, int CIN, int COUT, bool kAct, int W>
+__global__ void __launch_bounds__(64 * W) k_layer_fwd(int n, uint16_t* __restrict__ G1,
+                                                      const uint32_t* __restrict__ vs, int store,
+                                                      const uint16_t* __restrict__ X, const int* __restrict__ nbr,
+                                                      const uint16_t* __restrict__ Wt, const float* __restrict__ bias,
+                                                      std::conditional_t<kAct, uint16_t, float>* __restrict__ Y,
+                                                      const int* __restrict__ skip) {
   if (skip && *skip) return;
   constexpr int K = kSlots * CIN;
   constexpr int NT = COUT / 16;
-  constexpr int KC = K < kWChunk ? K : kWChunk;
+  constexpr int KC = K < kWChunk ? K : kWChunk, KU = KC / 32;
+  constexpr int kThreads = 64 * W, kParts = COUT * KC / 8, kMine = (kParts + kThreads - 1) / kThreads;
   static_assert(K % KC == 0 && KC % 32 == 0, "whole chunks of 32-column steps");
   __shared__ uint16_t sW[COUT][KC + kWPad];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int node0 = (blockIdx.x * kFwdWaves + wave) * 16;
-  const int node = node0 + (lane & 15);
-  const bool live = node < n;
+  const int node0 = (blockIdx.x * W + wave) * 16;
+  const int node = node0 + (lane & 15), row = min(node, n - 1);  // beyond the last node: its row, not stored
   const int kq = 8 * (lane >> 4);
   f32x4_t acc[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t) acc[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  // the node's neighbour rows, looked up once (the gathered layers read every slot)
+  short8_t w[kMine];  // the thread's part of a chunk of weights
+  auto load_w = [&](int k0) {
+#pragma unroll
+    for (int r = 0; r < kMine; ++r) {
+      const int e = threadIdx.x + r * kThreads;
+      if (e < kParts)
+        w[r] = *reinterpret_cast<const short8_t*>(Wt + (int64_t)(e / (KC / 8)) * K + k0 + (e % (KC / 8)) * 8);
+    }
+  };
+  load_w(0);
+  // the node's neighbour rows, looked up once
   int rows[kSlots];
 #pragma unroll
-  for (int q = 0; q < kSlots; ++q) rows[q] = 0;
-  if (!kDense && live) {
-#pragma unroll
-    for (int q = 0; q < kSlots; q += 4) {
-      const int4 v = *reinterpret_cast<const int4*>(nbr + (int64_t)node * kSlots + q);
-      rows[q] = v.x, rows[q + 1] = v.y, rows[q + 2] = v.z, rows[q + 3] = v.w;
-    }
+  for (int q = 0; q < kSlots; q += 4) {
+    const int4 v = *reinterpret_cast<const int4*>(nbr + (int64_t)row * kSlots + q);
+    rows[q] = v.x, rows[q + 1] = v.y, rows[q + 2] = v.z, rows[q + 3] = v.w;
   }
-  for (int k0 = 0; k0 < K; k0 += KC) {
-    // this chunk's A operands, loaded before the weights are staged so that the gathers'
-    // latency overlaps the staging
-    bf16x8_t a[KC / 32];
 #pragma unroll
-    for (int u = 0; u < KC / 32; ++u) {
-      const int kk = k0 + u * 32 + kq;
-      if (!live) {
-        a[u] = __builtin_bit_cast(bf16x8_t, short8_t{0, 0, 0, 0, 0, 0, 0, 0});
-      } else if (kDense) {
-        a[u] = load8_bf16(G1 + (int64_t)node * K + kk);
+  for (int k0 = 0; k0 < K; k0 += KC) {
+    // this chunk's A operands, loaded before the weights are staged so that the gathers' latency
+    // overlaps the staging
+    bf16x8_t a[KU];
+#pragma unroll
+    for (int u = 0; u < KU; ++u) {
+      const int slot = (k0 + u * 32) / CIN;
+      if (kDense) {
+        uint16_t* g = G1 + (int64_t)row * K + k0 + u * 32 + kq;
+        short8_t x = *reinterpret_cast<const short8_t*>(g);
+        if (!(kq & 8)) {  // features 0..7 of a slot
+          const uint32_t in = vs[kq ? rows[slot + 1] : rows[slot]];
+          x[5] = (short)(in & 0xffffu);
+          x[6] = (short)(in >> 16);
+          if (store && node < n) *reinterpret_cast<short8_t*>(g) = x;
+        }
+        a[u] = __builtin_bit_cast(bf16x8_t, x);
       } else {
-        a[u] = load8_bf16(X + (int64_t)rows[kk / CIN] * CIN + kk % CIN);
+        a[u] = load8_bf16(X + (int64_t)rows[slot] * CIN + (u * 32) % CIN + kq);
       }
     }
-    __syncthreads();  // the previous chunk is no longer read
-    for (int e = threadIdx.x; e < COUT * KC / 8; e += 64 * kFwdWaves) {
-      const int row = e / (KC / 8), col = (e % (KC / 8)) * 8;
-      *reinterpret_cast<short8_t*>(&sW[row][col]) =
-          *reinterpret_cast<const short8_t*>(Wt + (int64_t)row * K + k0 + col);
+    if (k0) __syncthreads();  // the previous chunk is no longer read
+#pragma unroll
+    for (int r = 0; r < kMine; ++r) {
+      const int e = threadIdx.x + r * kThreads;
+      if (e < kParts) *reinterpret_cast<short8_t*>(&sW[e / (KC / 8)][(e % (KC / 8)) * 8]) = w[r];
     }
+    if (k0 + KC < K) load_w(k0 + KC);
     __syncthreads();
 #pragma unroll
-    for (int u = 0; u < KC / 32; ++u) {
+    for (int u = 0; u < KU; ++u) {
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
         const bf16x8_t bw = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const short8_t*>(
@@ -795,6 +814,7 @@ struct NNBufs {
   int* rent;
   double* s;
   double* spart;
+  uint32_t* vs;  // the scaled inputs of every node (k_pack_in)
   uint16_t* G1;
   uint16_t* X[kLayers];  // BF16; X[0] unused (layer 0 reads G1); X[l] = input of layer l
   float* T;
@@ -824,12 +844,13 @@ pb_status bufs(pb_ctx* ctx, int n, NNBufs& B, bool train = false) {
   B.feat = (float*)ws("nn_feat", sizeof(float) * (size_t)n * 5);
   B.s = (double*)ws("nn_s", sizeof(double) * 2);
   B.spart = (double*)ws("nn_spart", sizeof(double) * 2 * kRedBlocks);
+  B.vs = (uint32_t*)ws("nn_vs", sizeof(uint32_t) * (size_t)n);
   B.G1 = (uint16_t*)ws("nn_G1", sizeof(uint16_t) * (size_t)n * kdim(0));
   B.X[0] = nullptr;
   B.X[1] = (uint16_t*)ws("nn_X1", sizeof(uint16_t) * (size_t)n * 64);
   B.X[2] = (uint16_t*)ws("nn_X2", sizeof(uint16_t) * (size_t)n * 64);
   B.X[3] = (uint16_t*)ws("nn_X3", sizeof(uint16_t) * (size_t)n * 64);
-  if (!B.nbr || !B.feat || !B.s || !B.spart || !B.G1 || !B.X[1] || !B.X[2] || !B.X[3]) return PB_ENOMEM;
+  if (!B.nbr || !B.feat || !B.s || !B.spart || !B.vs || !B.G1 || !B.X[1] || !B.X[2] || !B.X[3]) return PB_ENOMEM;
   if (!train) return PB_OK;
   B.rrow = (int64_t*)ws("nn_rrow", sizeof(int64_t) * (size_t)(n + 1));
   B.rent = (int*)ws("nn_rent", sizeof(int) * (size_t)n * kSlots);
@@ -899,8 +920,47 @@ static pb_status nn_check_prepared(pb_ctx* ctx, const pb_band* band) {
   return PB_OK;
 }
 
-// p = M(v); keeps the activations of this application in the workspace.
-pb_status nn_apply(pb_ctx* ctx, const pb_nn* net, const pb_band* band, const Derived& d, const double* v, double* p) {
+// The four layers over n nodes in blocks of W waves: X[1..3] and O from the layer-1 rows and inputs.
+template <int W>
+static void forward_w(hipStream_t st, const pb_nn* net, int n, uint16_t* G1, const uint32_t* vs, bool store,
+                      const int* nbr, uint16_t* const* X, float* O, const int* skip) {
+  const unsigned blocks = (unsigned)((n + 16 * W - 1) / (16 * W));
+  const uint16_t* wt = net->wt;
+  const float* prm = net->params;
+  k_layer_fwd<true, 16, 64, true, W><<<blocks, 64 * W, 0, st>>>(n, G1, vs, store, nullptr, nbr, wt + wbf_off(0),
+                                                                prm + b_off(0), X[1], skip);
+  for (int l = 1; l < 3; ++l)
+    k_layer_fwd<false, 64, 64, true, W><<<blocks, 64 * W, 0, st>>>(n, nullptr, nullptr, 0, X[l], nbr, wt + wbf_off(l),
+                                                                   prm + b_off(l), X[l + 1], skip);
+  k_layer_fwd<false, 64, 16, false, W><<<blocks, 64 * W, 0, st>>>(n, nullptr, nullptr, 0, X[3], nbr, wt + wbf_off(3),
+                                                                  prm + b_off(3), O, skip);
+}
+
+// Eight waves share the weights where the nodes fill the chip several times over, four spread fewer
+// nodes more evenly: one application 105 µs with four waves a block and 113 with eight at 43,035 nodes (8591
+// nodes: 71 and 80), 166 and 154 at 86,513, 249 and 234 at 156,535.
+static void forward(hipStream_t st, const pb_nn* net, int n, uint16_t* G1, const uint32_t* vs, bool store,
+                    const int* nbr, uint16_t* const* X, float* O, const int* skip) {
+  if (n < 65536) forward_w<4>(st, net, n, G1, vs, store, nbr, X, O, skip);
+  else forward_w<8>(st, net, n, G1, vs, store, nbr, X, O, skip);
+}
+
+// The geometry's part of the layer-1 rows of the band last prepared.
+pb_status nn_rows(pb_ctx* ctx, const pb_band* band, const Derived& d) {
+  PB_TRY(nn_check_prepared(ctx, band));
+  const int n = (int)band->n;
+  NNBufs B;
+  PB_TRY(bufs(ctx, n, B));
+  Scope t(ctx, "nn");
+  k_build_g1<<<(unsigned)(((int64_t)n * kSlots + kBlock - 1) / kBlock), kBlock, 0, ctx->stream>>>(
+      n, band_dev(band), B.nbr, B.feat, d.eps, B.G1);
+  return launch_ok(ctx, "nn rows");
+}
+
+// p = M(v), after nn_rows on the same band; keeps the activations of this application in the workspace,
+// with `train` its layer-1 rows too.
+pb_status nn_apply(pb_ctx* ctx, const pb_nn* net, const pb_band* band, const Derived& d, const double* v, double* p,
+                   bool train) {
   PB_TRY(nn_check_prepared(ctx, band));
   const int n = (int)band->n;
   NNBufs B;
@@ -908,22 +968,10 @@ pb_status nn_apply(pb_ctx* ctx, const pb_nn* net, const pb_band* band, const Der
   float* O = out_buf(ctx, n);
   if (!O) return PB_ENOMEM;
   const unsigned nb = (unsigned)((n + kBlock - 1) / kBlock);
-  const unsigned nbf = (unsigned)((n + kFwdNodes - 1) / kFwdNodes);
   Scope t(ctx, "nn");
   k_rms_partial<<<kRedBlocks, kBlock, 0, ctx->stream>>>(n, v, B.spart);
-  k_rms_finish<<<1, kBlock, 0, ctx->stream>>>(n, kRedBlocks, B.spart, B.s);
-  k_build_g1<<<(unsigned)(((int64_t)n * kSlots + kBlock - 1) / kBlock), kBlock, 0, ctx->stream>>>(
-      n, band_dev(band), B.nbr, B.feat, v, B.s, d.eps, B.G1);
-  const uint16_t* wt = net->wt;
-  const float* prm = net->params;
-  k_layer_fwd<true, 16, 64, true><<<nbf, 64 * kFwdWaves, 0, ctx->stream>>>(n, B.G1, nullptr, B.nbr, wt + wbf_off(0),
-                                                                 prm + b_off(0), B.X[1], ctx->skip);
-  k_layer_fwd<false, 64, 64, true><<<nbf, 64 * kFwdWaves, 0, ctx->stream>>>(n, nullptr, B.X[1], B.nbr, wt + wbf_off(1),
-                                                                  prm + b_off(1), B.X[2], ctx->skip);
-  k_layer_fwd<false, 64, 64, true><<<nbf, 64 * kFwdWaves, 0, ctx->stream>>>(n, nullptr, B.X[2], B.nbr, wt + wbf_off(2),
-                                                                  prm + b_off(2), B.X[3], ctx->skip);
-  k_layer_fwd<false, 64, 16, false><<<nbf, 64 * kFwdWaves, 0, ctx->stream>>>(n, nullptr, B.X[3], B.nbr, wt + wbf_off(3),
-                                                                   prm + b_off(3), O, ctx->skip);
+  k_pack_in<<<nb, kBlock, 0, ctx->stream>>>(n, kRedBlocks, B.spart, v, B.s, B.vs);
+  forward(ctx->stream, net, n, B.G1, B.vs, train, B.nbr, B.X, O, ctx->skip);
   k_apply_out<<<nb, kBlock, 0, ctx->stream>>>(n, v, O, B.s, d.lam1, d.lam2, p);
   return launch_ok(ctx, "nn apply");
 }
@@ -934,7 +982,8 @@ pb_status nn_grads(pb_ctx* ctx, pb_nn* net, const pb_band* band, const Derived& 
   const int n = (int)band->n;
   double* ptmp = (double*)workspace(ctx, "nn_ptmp", sizeof(double) * 2 * (size_t)n);
   if (!ptmp) return PB_ENOMEM;
-  PB_TRY(nn_apply(ctx, net, band, d, v, ptmp));
+  PB_TRY(nn_rows(ctx, band, d));
+  PB_TRY(nn_apply(ctx, net, band, d, v, ptmp, true));
   NNBufs B;
   PB_TRY(bufs(ctx, n, B, true));
   PB_TRY(nn_reverse(ctx, n, B));
@@ -1024,39 +1073,18 @@ __global__ void __launch_bounds__(kBlock) k_rms_batch(int n_mol, const int* __re
   }
 }
 
-// Layer-1 input rows of every node of the batch (as k_build_g1, per molecule).
-__global__ void __launch_bounds__(kBlock) k_build_g1_batch(int ntot, const int* __restrict__ mol_of,
-                                                           const int* __restrict__ off, const int* __restrict__ cnt,
-                                                           const double* __restrict__ pos, const int* __restrict__ nbr,
-                                                           const float* __restrict__ feat,
-                                                           const double* __restrict__ V, int64_t ldv,
-                                                           const int* __restrict__ kptr, int kmax,
-                                                           const double* __restrict__ s, double eps,
-                                                           uint16_t* __restrict__ G1) {
-  const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (t >= (int64_t)ntot * kSlots) return;
+// The scaled inputs of every node of the batch.
+__global__ void __launch_bounds__(kBlock) k_pack_in_batch(int ntot, const int* __restrict__ mol_of,
+                                                          const int* __restrict__ off, const int* __restrict__ cnt,
+                                                          const double* __restrict__ V, int64_t ldv,
+                                                          const int* __restrict__ kptr, int kmax,
+                                                          const double* __restrict__ s, uint32_t* __restrict__ vs) {
+  const int i = blockIdx.x * kBlock + threadIdx.x;
+  if (i >= ntot) return;
   if (kptr && *kptr >= kmax) return;
-  const int i = (int)(t / kSlots), slot = (int)(t % kSlots);
-  const int j = nbr[(int64_t)i * kSlots + slot];
-  const int m = mol_of[i];
-  const int n = cnt[m];
+  const int m = mol_of[i], n = cnt[m], l = i - off[m];
   const double* v = V + (kptr ? (int64_t)(*kptr) * ldv : 0) + 2 * (int64_t)off[m];
-  const int lj = j - off[m];
-  const float* fj = feat + (int64_t)j * 5;
-  float f[16];
-  f[0] = fj[0];
-  f[1] = fj[1];
-  f[2] = fj[2];
-  f[3] = fj[3];
-  f[4] = fj[4];
-  f[5] = (float)(v[lj] / s[2 * m]);
-  f[6] = (float)(v[n + lj] / s[2 * m + 1]);
-  f[7] = (float)((pos[3 * (int64_t)j] - pos[3 * (int64_t)i]) / eps);
-  f[8] = (float)((pos[3 * (int64_t)j + 1] - pos[3 * (int64_t)i + 1]) / eps);
-  f[9] = (float)((pos[3 * (int64_t)j + 2] - pos[3 * (int64_t)i + 2]) / eps);
-  for (int q = 10; q < 16; ++q) f[q] = 0.f;
-  uint16_t* out = G1 + t * 16;
-  for (int q = 0; q < 16; ++q) out[q] = bf16_bits(f[q]);
+  vs[i] = input_pair(v[l], v[n + l], s[2 * m], s[2 * m + 1]);
 }
 
 // p = Λ⁻¹(v + s_m ⊙ O[:, 0:2]) over every molecule's segment.
@@ -1076,15 +1104,10 @@ __global__ void __launch_bounds__(kBlock) k_apply_out_batch(int ntot, const int*
   Z[base + n + l] = (V[base + n + l] + s[2 * m + 1] * (double)O[(int64_t)i * 16 + 1]) / lam2;
 }
 
-// Local neighbour indices of one molecule → global node indices; positions into the batch table.
-__global__ void __launch_bounds__(kBlock) k_batch_geometry(int n, int off, BandDev b, int* __restrict__ nbr,
-                                                           double* __restrict__ pos) {
-  const int i = blockIdx.x * kBlock + threadIdx.x;
-  if (i >= n) return;
-  for (int q = 0; q < kSlots; ++q) nbr[(int64_t)i * kSlots + q] += off;
-  pos[3 * (int64_t)i] = b.px[i];
-  pos[3 * (int64_t)i + 1] = b.py[i];
-  pos[3 * (int64_t)i + 2] = b.pz[i];
+// Local neighbour indices of one molecule → global node indices.
+__global__ void __launch_bounds__(kBlock) k_batch_nbr(int64_t ne, int off, int* __restrict__ nbr) {
+  const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (t < ne) nbr[t] += off;
 }
 
 }  // namespace
@@ -1102,11 +1125,10 @@ pb_status nn_batch_prepare(pb_ctx* ctx, int n_mol, const pb_band* bands, const i
   auto ws = [&](const char* name, size_t bytes) { return workspace(ctx, name, bytes); };
   nb.n_mol = n_mol;
   nb.ntot = ntot;
-  nb.eps = d.eps;
   nb.mol_of = mol_of;
   nb.off = (int*)ws("nnb_off", sizeof(int) * n_mol);
   nb.cnt = (int*)ws("nnb_cnt", sizeof(int) * n_mol);
-  nb.pos = (double*)ws("nnb_pos", sizeof(double) * 3 * (size_t)ntot);
+  nb.vs = (uint32_t*)ws("nnb_vs", sizeof(uint32_t) * (size_t)ntot);
   nb.nbr = (int*)ws("nnb_nbr", sizeof(int) * kSlots * (size_t)ntot);
   nb.feat = (float*)ws("nnb_feat", sizeof(float) * 5 * (size_t)ntot);
   nb.s = (double*)ws("nnb_s", sizeof(double) * 2 * n_mol);
@@ -1116,7 +1138,7 @@ pb_status nn_batch_prepare(pb_ctx* ctx, int n_mol, const pb_band* bands, const i
   nb.X[2] = (uint16_t*)ws("nnb_X2", sizeof(uint16_t) * 64 * (size_t)ntot);
   nb.X[3] = (uint16_t*)ws("nnb_X3", sizeof(uint16_t) * 64 * (size_t)ntot);
   nb.O = (float*)ws("nnb_O", sizeof(float) * 16 * (size_t)ntot);
-  if (!nb.off || !nb.cnt || !nb.pos || !nb.nbr || !nb.feat || !nb.s || !nb.G1 || !nb.X[1] || !nb.X[2] || !nb.X[3] ||
+  if (!nb.off || !nb.cnt || !nb.vs || !nb.nbr || !nb.feat || !nb.s || !nb.G1 || !nb.X[1] || !nb.X[2] || !nb.X[3] ||
       !nb.O)
     return PB_ENOMEM;
   PB_HIP(ctx, hipMemcpyAsync(nb.off, off_host, sizeof(int) * n_mol, hipMemcpyHostToDevice, ctx->stream));
@@ -1131,7 +1153,11 @@ pb_status nn_batch_prepare(pb_ctx* ctx, int n_mol, const pb_band* bands, const i
     k_knn<<<(unsigned)((n + kKnnWaves - 1) / kKnnWaves), 64 * kKnnWaves, 0, ctx->stream>>>(n, band_dev(band),
                                                                                          cells_dev(P), nbr_m);
     k_geom<<<nbk, kBlock, 0, ctx->stream>>>(n, band_dev(band), band->phi, d.eps, nbr_m, nb.feat + (int64_t)o * 5);
-    k_batch_geometry<<<nbk, kBlock, 0, ctx->stream>>>(n, o, band_dev(band), nbr_m, nb.pos + 3 * (int64_t)o);
+    const int64_t ne = (int64_t)n * kSlots;
+    const unsigned nbe = (unsigned)((ne + kBlock - 1) / kBlock);
+    k_build_g1<<<nbe, kBlock, 0, ctx->stream>>>(n, band_dev(band), nbr_m, nb.feat + (int64_t)o * 5, d.eps,
+                                                nb.G1 + (int64_t)o * kdim(0));
+    k_batch_nbr<<<nbe, kBlock, 0, ctx->stream>>>(ne, o, nbr_m);
     PB_TRY(launch_ok(ctx, "nn batch prepare"));
   }
   return PB_OK;
@@ -1141,19 +1167,9 @@ void nn_batch_apply(hipStream_t stream, const pb_nn* net, const NNBatch& nb, con
                     const int* kptr, int kmax, double lam1, double lam2) {
   const int ntot = nb.ntot;
   k_rms_batch<<<nb.n_mol, kBlock, 0, stream>>>(nb.n_mol, nb.off, nb.cnt, V, ldv, kptr, kmax, nb.s);
-  k_build_g1_batch<<<(unsigned)(((int64_t)ntot * kSlots + kBlock - 1) / kBlock), kBlock, 0, stream>>>(
-      ntot, nb.mol_of, nb.off, nb.cnt, nb.pos, nb.nbr, nb.feat, V, ldv, kptr, kmax, nb.s, nb.eps, nb.G1);
-  const unsigned nbf = (unsigned)((ntot + kFwdNodes - 1) / kFwdNodes);
-  const uint16_t* wt = net->wt;
-  const float* prm = net->params;
-  k_layer_fwd<true, 16, 64, true><<<nbf, 64 * kFwdWaves, 0, stream>>>(ntot, nb.G1, nullptr, nb.nbr, wt + wbf_off(0),
-                                                          prm + b_off(0), nb.X[1], nullptr);
-  k_layer_fwd<false, 64, 64, true><<<nbf, 64 * kFwdWaves, 0, stream>>>(ntot, nullptr, nb.X[1], nb.nbr, wt + wbf_off(1),
-                                                           prm + b_off(1), nb.X[2], nullptr);
-  k_layer_fwd<false, 64, 64, true><<<nbf, 64 * kFwdWaves, 0, stream>>>(ntot, nullptr, nb.X[2], nb.nbr, wt + wbf_off(2),
-                                                           prm + b_off(2), nb.X[3], nullptr);
-  k_layer_fwd<false, 64, 16, false><<<nbf, 64 * kFwdWaves, 0, stream>>>(ntot, nullptr, nb.X[3], nb.nbr, wt + wbf_off(3),
-                                                            prm + b_off(3), nb.O, nullptr);
+  k_pack_in_batch<<<(unsigned)((ntot + kBlock - 1) / kBlock), kBlock, 0, stream>>>(ntot, nb.mol_of, nb.off, nb.cnt, V, ldv,
+                                                                                 kptr, kmax, nb.s, nb.vs);
+  forward(stream, net, ntot, nb.G1, nb.vs, false, nb.nbr, nb.X, nb.O, nullptr);
   k_apply_out_batch<<<(unsigned)((ntot + kBlock - 1) / kBlock), kBlock, 0, stream>>>(
       ntot, nb.mol_of, nb.off, nb.cnt, V, Z, ldv, kptr, kmax, nb.O, nb.s, lam1, lam2);
 }
@@ -1253,6 +1269,7 @@ pb_status pb_nn_apply(pb_ctx* ctx, const pb_nn* net, const pb_band* band, const 
   PB_TRY(check_params(ctx, prm));
   PB_TRY(check_band(ctx, band));
   PB_HIP(ctx, hipSetDevice(ctx->device));
+  PB_TRY(nn_rows(ctx, band, derive(*prm)));
   PB_TRY(nn_apply(ctx, net, band, derive(*prm), v, p));
   return sync(ctx, "pb_nn_apply");
 }

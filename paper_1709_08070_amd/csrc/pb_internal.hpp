@@ -208,16 +208,17 @@ struct F32Params;
 F32Params f32params(const Derived& d, double sigma);
 // learned preconditioner (nn.hip)
 pb_status nn_prepare(pb_ctx* ctx, const pb_band* band, const Derived& d);
-pb_status nn_apply(pb_ctx* ctx, const pb_nn* net, const pb_band* band, const Derived& d, const double* v, double* p);
+pb_status nn_rows(pb_ctx* ctx, const pb_band* band, const Derived& d);
+pb_status nn_apply(pb_ctx* ctx, const pb_nn* net, const pb_band* band, const Derived& d, const double* v, double* p,
+                   bool train = false);
 // The same network over a batch of bands whose nodes are concatenated: molecule m owns nodes
 // [off[m], off[m] + cnt[m]) and vector entries [2·off[m], 2·off[m] + 2·cnt[m]) as [ψ | ψn].
 struct NNBatch {
   int n_mol = 0, ntot = 0;
-  double eps = 0.0;
   const int* mol_of = nullptr;  // node → molecule (caller-owned)
   int* off = nullptr;           // per molecule, device
   int* cnt = nullptr;
-  double* pos = nullptr;        // ntot × 3 projections
+  uint32_t* vs = nullptr;       // the nodes' scaled inputs
   int* nbr = nullptr;           // ntot × 16 neighbour slots, global node indices
   float* feat = nullptr;        // ntot × 5 node features
   double* s = nullptr;          // per molecule: RMS of the two halves of the input

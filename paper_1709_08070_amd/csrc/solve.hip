@@ -485,7 +485,10 @@ extern "C" pb_status pb_ibim_solve(pb_ctx* ctx, const pb_band* band, const doubl
   PB_TRY(norm2(ctx, K, g, &gnorm));
   if (!std::isfinite(gnorm)) return ctx->fail(PB_EINVAL, "non-finite right-hand side");
   if (gnorm == 0.0) gnorm = 1.0;
-  if (learned) PB_TRY(nn_prepare(ctx, band, d));
+  if (learned) {
+    PB_TRY(nn_prepare(ctx, band, d));
+    PB_TRY(nn_rows(ctx, band, d));
+  }
   if (opts.x0 == PB_X0_DIAG) k_diag_solve<<<vb, kBlock, 0, ctx->stream>>>(n, g, d.lam1, d.lam2, p);
   else if (opts.x0 == PB_X0_ZERO) k_zero<<<vb, kBlock, 0, ctx->stream>>>(M, p);
   else if (opts.x0 == PB_X0_LEARNED) PB_TRY(nn_apply(ctx, net, band, d, g, p));
