@@ -35,29 +35,31 @@ constexpr int kNumFarCfgs = kNumTiled + 1;
 
 // Tiles of the symmetric kernels for a band of n nodes: F nodes per tile (512, 256 or 128: blocks of
 // 4 × 1, 2 × 2 or 1 × 2 waves), chunks of nsub tiles. Small bands take small tiles: tiles of 512 give
-// (n/512)²/2 blocks, too few for 256 CUs below about 40,000 nodes and in few, uneven rounds. Measured
-// far-field times, tiles of 512 / 256 / 128: FP32 at 13,393 nodes 148 / 110 / 111 µs, at 33,866
-// nodes 559 / 565 / 572, at 45,818 nodes 964 / 1021 / 1115; FP64 at 8725 nodes 356 / 192 / 170 µs,
-// at 20,424 nodes 811 / 609 / 653, at 55,111 nodes 3947 / 3879 / –, at 105,085 nodes equal.
+// (n/512)²/2 blocks, too few for 256 CUs below about 40,000 nodes and in few, uneven rounds. Measured,
+// tiles of 512 / 256 / 128, FP32 operator with its near field: at 13,393 nodes (far field alone) 148 /
+// 110 / 111 µs, at 35,214 787 / 747 / –, at 43,035 1074 / 1040 / –, at 54,655 1589 / 1581 / –, at 61,591
+// 1980 / 1985 / –; FP64 at 8725 nodes 356 / 192 / 170 µs, at 12,300 – / 264 / 260, at 16,020 – / 391 /
+// 395, at 55,111 3947 / 3879 / –, at 105,085 equal.
 struct SymShape {
   int F, nsub, chunks;
 };
 SymShape sym_shape(int n, bool f64) {
-  const int F = f64 ? (n < 10240 ? 128 : n < 61440 ? 256 : 512) : (n < 32768 ? 256 : 512);
+  const int F = n >= 61440 ? 512 : f64 && n < 13312 ? 128 : 256;
   const int C = F == kSymSub ? F * sym_nsub(n) : F;
   return {F, C / F, (n + C - 1) / C};
 }
 
-// Work items (Ic, Jc) of a symmetric kernel: chunk pairs of different sub-blocks (Ic < Jc) first,
-// then those within a sub-block, which are one-directional (both orders).
+// Work items (Ic, Jc) of a symmetric kernel: chunk pairs within a sub-block first, which are
+// one-directional (both orders) and the longer ones (last, they end the FP64 operator 3 to 6% later
+// below 20,000 nodes), then those of different sub-blocks (Ic < Jc).
 std::vector<int2> sym_items(const SymShape& sh) {
   const int nc = sh.chunks, per = std::max(1, kSymSub / (sh.F * sh.nsub));
   std::vector<int2> v;
   v.reserve((size_t)nc * (nc + 1) / 2 + (size_t)nc * per);
   for (int i = 0; i < nc; ++i)
-    for (int j = (i / per + 1) * per; j < nc; ++j) v.push_back(make_int2(i, j));
-  for (int i = 0; i < nc; ++i)
     for (int j = i / per * per; j < std::min(nc, (i / per + 1) * per); ++j) v.push_back(make_int2(i, j));
+  for (int i = 0; i < nc; ++i)
+    for (int j = (i / per + 1) * per; j < nc; ++j) v.push_back(make_int2(i, j));
   return v;
 }
 

@@ -14,7 +14,7 @@ import pytest
 
 pytestmark = pytest.mark.gpu
 
-SIZES = [1, 64, 127, 128, 129, 255, 257, 511, 512, 513, 1025, 10239, 10241, 12799, 12801, 32769]
+SIZES = [1, 64, 127, 128, 129, 255, 257, 511, 512, 513, 1025, 10239, 10241, 12799, 12801, 13311, 13313, 32769, 61439, 61441]
 
 
 def _band(pb, torch, n):
