@@ -250,12 +250,58 @@ __global__ void __launch_bounds__(kScanBlock) k_scan_apply(T* __restrict__ data,
   if (total && blockIdx.x == gridDim.x - 1 && threadIdx.x == kScanBlock - 1) *total = run;
 }
 
+// The scan by one block: kOnePer values a thread and turn, carried from turn to turn.
+constexpr int kOneBlock = 1024, kOnePer = 8, kOneMax = 2 * kOneBlock * kOnePer;
+template <typename T>
+__global__ void __launch_bounds__(kOneBlock) k_scan_one(T* __restrict__ data, int n, T* __restrict__ total) {
+  __shared__ T s[kOneBlock / 64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  T carry = 0;
+  for (int base = 0; base < n; base += kOneBlock * kOnePer) {
+    const int i0 = base + (int)threadIdx.x * kOnePer;
+    T v[kOnePer], t = 0;
+#pragma unroll
+    for (int r = 0; r < kOnePer; ++r) {
+      v[r] = i0 + r < n ? data[i0 + r] : 0;
+      t += v[r];
+    }
+    T u = t;
+    for (int off = 1; off < 64; off <<= 1) {
+      const T e = __shfl_up(u, off);
+      if (lane >= off) u += e;
+    }
+    if (lane == 63) s[wave] = u;
+    __syncthreads();
+    T before = 0, all = 0;
+    for (int w = 0; w < kOneBlock / 64; ++w) {
+      if (w < wave) before += s[w];
+      all += s[w];
+    }
+    T run = carry + before + u - t;
+#pragma unroll
+    for (int r = 0; r < kOnePer; ++r) {
+      if (i0 + r < n) data[i0 + r] = run;
+      run += v[r];
+    }
+    carry += all;
+    __syncthreads();
+  }
+  if (total && threadIdx.x == 0) *total = carry;
+}
+
+// One block scans short arrays (up to 8192 values in 6 µs, 16,384 in 9, 32,768 in 14) where the two launches
+// take 11 to 13 and the gap between them: the FP32 operator at 6905 nodes 168 → 160 µs with its lists, at
+// 8591 202 → 191.
 template <typename T>
 static pb_status scan(pb_ctx* ctx, T* data, int64_t n, T* total_dev) {
+  if (n <= kOneMax) {
+    k_scan_one<T><<<1, kOneBlock, 0, ctx->stream>>>(data, (int)n, total_dev);
+    return launch_ok(ctx, "scan");
+  }
   const int64_t nb = (n + kScanTile - 1) / kScanTile;
   T* sums = (T*)workspace(ctx, "scan_sums", sizeof(int64_t) * (size_t)nb);
   if (!sums) return PB_ENOMEM;
-  if (nb > 1) k_scan_sums<T><<<(unsigned)nb, kScanBlock, 0, ctx->stream>>>(data, n, sums);
+  k_scan_sums<T><<<(unsigned)nb, kScanBlock, 0, ctx->stream>>>(data, n, sums);
   k_scan_apply<T><<<(unsigned)nb, kScanBlock, 0, ctx->stream>>>(data, n, sums, total_dev);
   return launch_ok(ctx, "scan");
 }

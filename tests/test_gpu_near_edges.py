@@ -85,3 +85,20 @@ def test_mixed_operator(env, kind, n):
     ref = pb.pb_ibim_matvec(ctx, b, prm, p, pb.PB_FP64)
     assert torch.equal(y, y2)
     assert float((y - ref).abs().max()) <= 1e-5 * float(ref.abs().max())
+
+
+@pytest.mark.parametrize("n", [8190, 8191, 8192, 16382, 16383, 16384, 33000])
+def test_row_scan_lengths(env, n):
+    """Row starts of n + 1 values around the turns of the one-block scan (8192 values each) and its end
+    (16,384): a wrong start would put near pairs in other rows."""
+    pb, torch, ctx = env
+    print("case: row scan, n =", n, flush=True)
+    rng = np.random.default_rng(n)
+    x = rng.normal(size=(n, 3))
+    x *= (0.15 * np.sqrt(n) / np.linalg.norm(x, axis=1))[:, None]
+    prm = pb.params(0.5)
+    b = _band(pb, torch, x[np.lexsort(x.T[::-1].round(0))], n)
+    p = torch.tensor(rng.normal(size=2 * n), device="cuda")
+    y = pb.pb_ibim_matvec(ctx, b, prm, p, pb.PB_MIXED)
+    ref = pb.pb_ibim_matvec(ctx, b, prm, p, pb.PB_FP64)
+    assert float((y - ref).abs().max()) <= 1e-5 * float(ref.abs().max())
