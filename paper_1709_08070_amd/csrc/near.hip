@@ -122,21 +122,42 @@ __global__ void __launch_bounds__(kBlock) k_cell_place(int n, BandDev b, const d
 constexpr int kNearWaves = kBlock / 64;  // targets per block of the near-list kernels
 
 // Visits the near sources of target i (FP32 distance below r_c) in a fixed order: the nine
-// ranges of cell_ranges, 64 candidates at a time. Per step every lane calls f(hit, q, mask) with
-// its candidate's place q in cell order and the ballot of the hits. One wave per target.
+// ranges of cell_ranges one after the other, 64 candidates at a time. Per step every lane calls
+// f(hit, q, node, mask) with its candidate's place q in cell order and the ballot of the hits. One wave
+// per target. The ranges (30 to 45 candidates each) are read as one sequence, four steps' records at once:
+// bound by the latency of those reads, of which a loop over the ranges has nine in a row.
 template <typename F>
 __device__ __forceinline__ void for_near_wave(const float3& t, int c, const float4* __restrict__ key,
                                               const CellsDev& cells, float rc2, F f) {
+  constexpr int kAhead = 4;
   const int lane = threadIdx.x & 63;
   int lo, hi;
   cell_ranges(cells, c, lo, hi);
+  int first[9], shift[9], m = 0;  // range r holds candidates first[r] … of the sequence, at shift[r] + its number
+#pragma unroll
   for (int r = 0; r < 9; ++r) {
     const int a = __builtin_amdgcn_readlane(lo, r), e = __builtin_amdgcn_readlane(hi, r);
-    for (int q0 = a; q0 < e; q0 += 64) {
-      const int q = q0 + lane;
-      const float4 k = key[min(q, e - 1)];
-      const bool hit = q < e && r2_f32(t.x, t.y, t.z, k.x, k.y, k.z) < rc2;
-      f(hit, q, __float_as_int(k.w), __ballot(hit));
+    first[r] = m;
+    shift[r] = a - m;
+    m += e - a;
+  }
+  for (int f0 = 0; f0 < m; f0 += 64 * kAhead) {
+    int q[kAhead];
+    float4 k[kAhead];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const int g = min(f0 + 64 * u + lane, m - 1);
+      int s = shift[0];
+#pragma unroll
+      for (int r = 1; r < 9; ++r) s = g >= first[r] ? shift[r] : s;
+      q[u] = g + s;
+      k[u] = key[q[u]];
+    }
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      if (f0 + 64 * u >= m) break;
+      const bool hit = f0 + 64 * u + lane < m && r2_f32(t.x, t.y, t.z, k[u].x, k[u].y, k[u].z) < rc2;
+      f(hit, q[u], __float_as_int(k[u].w), __ballot(hit));
     }
   }
 }
@@ -211,9 +232,9 @@ __global__ void __launch_bounds__(kBlock) k_near_fill(int n, BandDev b, double c
 
 }  // namespace
 
-// At 185,127 nodes (9.3M pairs) the count takes 104 µs and the fill 228 µs (its 335 MB of matrix
-// at 1.5 TB/s, the FP64 kernels beside it), against 345 and 558 µs with 27 separate cells walked
-// through index lists and the library's exp.
+// At 185,127 nodes (9.3M pairs) the count takes 70 µs and the fill 183 µs (its 335 MB of matrix
+// at 1.8 TB/s, the FP64 kernels beside it); 104 and 228 with a loop over the nine ranges, 345 and 558 with 27
+// separate cells walked through index lists and the library's exp.
 
 // Geometry of the mixed operator for one band: centre and scale of the FP32 records, the
 // cell list and the FP64 near-field CSR matrix. Buffers are named `<pfx>...` in the context
