@@ -137,21 +137,20 @@ struct Frac {
   double n, d;
 };
 
-// v: the middle difference of the side's five; c1..c3: its candidates minus 6v; q = (ε + β)² of the
-// three candidates. Weights 1/q₁ : 6/q₂ : 3/q₃, over the common denominator q₁q₂q₃.
+// v: the middle difference of the side's five; c1..c3: its candidates minus 6v; b = ε + β of the
+// three candidates. Weights 1/b₁² : 6/b₂² : 3/b₃², over their common denominator.
 __device__ __forceinline__ Frac weno_side(double v, double c1, double c2, double c3, double b1, double b2, double b3) {
 #pragma clang fp contract(fast)
-  const double q1 = 3.0 * sq(b1), q2 = sq(b2), q3 = 2.0 * sq(b3), A = q2 * q3;  // A = 2 q₂q₃
-  const double D = fma(q1, fma(2.0, q3, q2 + q2), A);                            // twice the weights' sum
-  const double N = fma(q1, fma(2.0 * c2, q3, (c3 + c3) * q2), c1 * A);
+  const double q1 = 3.0 * sq(b1), q2 = sq(b2), q3 = sq(b3), d3 = q3 + q3, A = q2 * q3;
+  const double D = fma(q1, q2 + d3, A);
+  const double N = fma(q1, fma(c2, d3, c3 * q2), c1 * A);
   return {fma(6.0 * v, D, N), D};
 }
 
-// n/d for d > 0 (not subnormal): hardware reciprocal, two Newton steps, one correction of the
-// quotient.
+// n/d for d > 0 (not subnormal): the hardware reciprocal (2^-24 or better) and one Newton step (2^-47),
+// then one correction of the quotient, whose own error is the square of that.
 __device__ __forceinline__ double div_pos(double n, double d) {
   double r = __builtin_amdgcn_rcp(d);
-  r = fma(fma(-d, r, 1.0), r, r);
   r = fma(fma(-d, r, 1.0), r, r);
   const double q = n * r;
   return fma(fma(-d, q, n), r, q);
@@ -162,10 +161,10 @@ __device__ __forceinline__ double div_pos(double n, double d) {
 // max((a⁺)², (b⁻)²) for sg > 0 and max((a⁻)², (b⁺)²) for sg < 0. It works on the differences
 // d = h·D instead of the divided differences D and on their differences e: the smoothness indicators
 // are taken ×4h² (13t²/3 + u², ε entering as e4 = 4h²ε, the same weights) and the candidates ×6h, the
-// middle difference split off (a = 6d2 + a convex combination of c1..c3), so the value returned is
+// middle difference split off (a = 6d2 + a convex combination of c1..c3), so that what is added to acc is
 // (6h)² times the axis's term; the larger of the two quotients is chosen by cross multiplication
 // (their denominators are positive), one division instead of two.
-__device__ __forceinline__ double godunov_axis(const double f[7], double e4, double sg) {
+__device__ __forceinline__ double godunov_axis(const double f[7], double e4, double sg, double acc) {
 #pragma clang fp contract(fast)
   const double d0 = f[1] - f[0], d1 = f[2] - f[1], d2 = f[3] - f[2], d3 = f[4] - f[3], d4 = f[5] - f[4],
                d5 = f[6] - f[5];
@@ -176,14 +175,15 @@ __device__ __forceinline__ double godunov_axis(const double f[7], double e4, dou
   const double t0 = e1 - e0, s0 = fma(g * t0, t0, e4), t3 = e_4 - e3, s3 = fma(g * t3, t3, e4);
   const double ua1 = 3.0 * e1 - e0, ua2 = e1 + e2, ua3 = e3 - 3.0 * e2;
   const double ub1 = 3.0 * e3 - e_4, ub2 = e2 + e3, ub3 = e1 - 3.0 * e2;
-  const Frac a = weno_side(d2, 5.0 * e1 - 2.0 * e0, e1 + 2.0 * e2, 4.0 * e2 - e3, fma(ua1, ua1, s0),
-                           fma(ua2, ua2, s1), fma(ua3, ua3, s2));
-  const Frac b = weno_side(d3, 2.0 * e_4 - 5.0 * e3, -e3 - 2.0 * e2, e1 - 4.0 * e2, fma(ub1, ub1, s3),
-                           fma(ub2, ub2, s2), fma(ub3, ub3, s1));
+  // the candidates from the same differences as the indicators: 5e1 − 2e0, e1 + 2e2, 4e2 − e3 and mirrored
+  const Frac a = weno_side(d2, 2.0 * ua1 - e1, ua2 + e2, e2 - ua3, fma(ua1, ua1, s0), fma(ua2, ua2, s1),
+                           fma(ua3, ua3, s2));
+  const Frac b = weno_side(d3, e3 - 2.0 * ub1, -e2 - ub2, ub3 - e2, fma(ub1, ub1, s3), fma(ub2, ub2, s2),
+                           fma(ub3, ub3, s1));
   const double A = fmax(sg * a.n, 0.0), B = fmax(-sg * b.n, 0.0);
   const bool left = A * b.d >= B * a.d;
   const double x = div_pos(left ? A : B, left ? a.d : b.d);
-  return x * x;
+  return fma(x, x, acc);
 }
 
 // One TVD-RK3 stage: L = L(φ_in), then
@@ -212,8 +212,8 @@ constexpr int kXcds = 8;
 // node indexing (grids hold fewer than 2^31 nodes). The XCDs take slabs of ny/8 rows, so that the
 // planes of a node's x neighbours lie in the L2 of its own XCD.
 // Small grids wait on launches and on one chain of loads and FP64 arithmetic (two waves per SIMD at 135,000
-// nodes): 1297 → 1094 µs for the level set of 54 × 51 × 49 nodes (150 stages), 3.87 → 3.63 ms at
-// 117 × 106 × 93, from fewer FP64 instructions in godunov_axis and the reciprocal forms above.
+// nodes): 1290 → 975 µs for the level set of 54 × 51 × 49 nodes (150 stages; cavities included), 4.0 → 3.15
+// ms at 117 × 106 × 93, from 250 FP64 instructions a node where there were some 330.
 template <int MODE>
 __global__ void __launch_bounds__(kBlock) k_rk_node(GridDev g, const double* __restrict__ phi_in,
                                                     const double* __restrict__ phi_n, const double* __restrict__ S,
@@ -241,7 +241,7 @@ __global__ void __launch_bounds__(kBlock) k_rk_node(GridDev g, const double* __r
 #pragma unroll
       for (int m = 0; m < 7; ++m) f[m] = p[(reflect(c3[ax] + m - 3, n3[ax]) - c3[ax]) * stride[ax]];
     }
-    acc += godunov_axis(f, e, sg);
+    acc = godunov_axis(f, e, sg, acc);
   }
   out[uid] = stage_value<MODE>(acc, c, s, p[0], dt, stage > 0 ? phi_n[uid] : 0.0, stage);
 }
@@ -252,8 +252,9 @@ __global__ void __launch_bounds__(kBlock) k_rk_node(GridDev g, const double* __r
 // loads from far away (next x plane, S, φ_n) are issued a step ahead. Tiles go to the XCDs in
 // contiguous runs along j.
 // With one thread per node the L1 serves 19 values a node, 72% of the kernel's cycles beside 65%
-// VALU; here it is bound by FP64 issue (366 vector instructions a node). Level set of 286 × 253 × 217 nodes:
-// 53.6 ms before, 47.4 ms with k_rk_node, 40.5 ms with this kernel; 208 × 185 × 159: 18.8, 16.6, 14.4 ms.
+// VALU; here it is bound by FP64 issue and the reads of φ, φ_n and S (at 15.7M nodes 250 FP64
+// instructions a node, 145 µs, and 0.6 GB, 125 µs; a stage takes 185). Level set of 286 × 253 × 217 nodes:
+// 53 ms before, 40.8 ms with k_rk_node, 33.9 ms with this kernel; 208 × 185 × 159: 18.4, 14.3, 12.2 ms.
 constexpr int kStageK = 32, kStageJ = 2 * kBlock / kStageK;
 
 struct D2 {
@@ -318,14 +319,14 @@ __global__ void __launch_bounds__(kBlock) k_rk_march(GridDev g, const double* __
       double f[7];
 #pragma unroll
       for (int m = 0; m < 7; ++m) f[m] = w[m].v[u];
-      double acc = godunov_axis(f, e, sg);
+      double acc = godunov_axis(f, e, sg, 0.0);
 #pragma unroll
       for (int m = 0; m < 3; ++m) f[m] = y[m].v[u], f[4 + m] = y[3 + m].v[u];
       f[3] = w[3].v[u];
-      acc += godunov_axis(f, e, sg);
+      acc = godunov_axis(f, e, sg, acc);
 #pragma unroll
       for (int m = 0; m < 7; ++m) f[m] = z[m + u];
-      acc += godunov_axis(f, e, sg);
+      acc = godunov_axis(f, e, sg, acc);
       v[u] = stage_value<MODE>(acc, c, su, w[3].v[u], dt, pn.v[u], stage);
     }
     if (live) {
@@ -341,9 +342,9 @@ __global__ void __launch_bounds__(kBlock) k_rk_march(GridDev g, const double* __
 
 // Whether a grid of so many nodes marches, and how far a thread then goes.
 // Marching pays once it has some 1300 blocks; below that too few waves are in flight: 161 × 145 × 127
-// nodes (2.97M) 7.65 ms marching, 8.32 ms by nodes; 137 × 120 × 103 (1.69M) 5.52 and 4.80 ms. A longer
+// nodes (2.97M) 6.87 ms marching, 7.28 ms by nodes; 137 × 120 × 103 (1.69M) 5.00 and 4.40 ms. A longer
 // march loads the seven starting planes less often but needs a larger grid for as many blocks: 4, 8 and 16
-// nodes take 14.6, 14.6, 15.6 ms at 6.1M nodes and 42.3, 41.2, 40.6 ms at 15.7M.
+// nodes take 12.4, 12.8, 13.6 ms at 6.1M nodes and 35.5, 34.2, 33.7 ms at 15.7M.
 bool stage_marches(int64_t total) { return total >= (int64_t)5 << 19; }
 int march_len(int64_t total) { return (int)std::min<int64_t>(std::max<int64_t>(total >> 20, 4), 16); }
 
