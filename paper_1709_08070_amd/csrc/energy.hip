@@ -91,8 +91,8 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
 // ψ_rxn of A atoms per block: every thread reads the data of each of its nodes once and adds that
 // node's term to the sums of all the block's atoms, then one fixed-order block reduction per atom.
 // 1/ρ is rsqrt_f64 and e^{−κρ} exp_neg_f64 (fp64_math.hpp). Per pair, times 4π:
-// s(θ1 E(1 + κρ) − 1)/ρ³ · ψ̄_j + (1 − E)/ρ · ψ̄n_j, with the weight h³ω_j/4π. Block 0 sums the area
-// h³ Σ_j ω_j instead. Bound by FP64 issue (about 45 instructions a
+// (s(θ1 E(1 + κρ) − 1)/ρ² · ψ̄_j + (1 − E) · ψ̄n_j)/ρ, with the weight h³ω_j/4π, ψ̄_j's in the normal. Block 0 sums the area
+// h³ Σ_j ω_j instead. Bound by FP64 issue (about 40 instructions a
 // pair); blocks of 512 threads left a CU two waves per SIMD to hide the loads of a node behind, and the area,
 // summed afterwards by one block, took 76 µs of its own: 1991 atoms on 85,870 nodes 414 → 306 µs with
 // the call.
@@ -124,9 +124,10 @@ __global__ void __launch_bounds__(kPsiBlock) k_psi_rxn(int n, const double* __re
 #pragma unroll
   for (int a = 0; a < A; ++a) acc[a] = 0.0;
   for (int j = threadIdx.x; j < n; j += kPsiBlock) {
-    const double yx = px[j], yy = py[j], yz = pz[j], nxj = nx[j], nyj = ny[j], nzj = nz[j];
+    const double yx = px[j], yy = py[j], yz = pz[j];
     const double ww = c4 * w[j];
     const double w1 = ww * p[j], w2 = ww * p[n + j];
+    const double mx = w1 * nx[j], my = w1 * ny[j], mz = w1 * nz[j];
 #pragma unroll
     for (int a = 0; a < A; ++a) {
       const double dx = za[a][0] - yx, dy = za[a][1] - yy, dz = za[a][2] - yz;
@@ -134,9 +135,9 @@ __global__ void __launch_bounds__(kPsiBlock) k_psi_rxn(int n, const double* __re
       const double rinv = rsqrt_f64(r2);
       const double z = kappa * (r2 * rinv);
       const double E = exp_neg_f64(z);
-      const double s = dx * nxj + dy * nyj + dz * nzj;
-      const double r3 = rinv * rinv * rinv;
-      acc[a] += w1 * (s * r3 * (th1 * fma(E, z, E) - 1.0)) + w2 * ((1.0 - E) * rinv);
+      const double s = dx * mx + dy * my + dz * mz;
+      const double t = fma(s * (rinv * rinv), fma(th1, fma(E, z, E), -1.0), fma(-E, w2, w2));
+      acc[a] = fma(rinv, t, acc[a]);
     }
   }
 #pragma unroll
