@@ -204,46 +204,67 @@ __device__ __forceinline__ double stage_value(double acc, double c, double s, do
   return stage == 0 ? v0 : stage == 1 ? 0.75 * phi_n + 0.25 * v0 : phi_n * (1.0 / 3.0) + (2.0 / 3.0) * v0;
 }
 
-__device__ __forceinline__ int reflect(int q, int n) { return q < 0 ? -q : (q > n - 1 ? 2 * (n - 1) - q : q); }
+// The node that position q (−3 … n + 2) stands for.
+__device__ __forceinline__ int reflect(int q, int n) { return min(abs(q), 2 * (n - 1) - abs(q)); }
 
 constexpr int kXcds = 8;
+
+// t / d for t < 2^32 from m = ⌈2^64 / d⌉ (d ≥ 2): m·d exceeds 2^64 by less than d < 2^32, so the product
+// with t is right to the last bit of its high word.
+struct Div {
+  uint32_t hi, lo;
+};
+inline Div div_by(uint64_t d) {
+  const uint64_t m = ~0ull / d + 1;
+  return {(uint32_t)(m >> 32), (uint32_t)m};
+}
+__device__ __forceinline__ unsigned div_u32(unsigned t, Div m) {
+  return (unsigned)(((uint64_t)t * m.hi + __umulhi(t, m.lo)) >> 32);
+}
 
 // The stage with one thread per node: e = 4h²ε and c = 1/(6h) undo the scaling of godunov_axis. 32-bit
 // node indexing (grids hold fewer than 2^31 nodes). The XCDs take slabs of ny/8 rows, so that the
 // planes of a node's x neighbours lie in the L2 of its own XCD.
-// Small grids wait on launches and on one chain of loads and FP64 arithmetic (two waves per SIMD at 135,000
-// nodes): 1290 → 975 µs for the level set of 54 × 51 × 49 nodes (150 stages; cavities included), 4.0 → 3.15
-// ms at 117 × 106 × 93, from 250 FP64 instructions a node where there were some 330.
+// Small grids wait on launches (an empty one takes 4 µs, a stage here under 6) and on one chain of index
+// arithmetic, loads and FP64 work (two waves per SIMD at 135,000 nodes): no divisions, no branch that a wave
+// takes both ways, 250 FP64 instructions a node. Level set of 54 × 51 × 49 nodes (150 stages; cavities
+// included) 1270 → 900 µs, of 85 × 79 × 70 2.11 → 1.56 ms, of 117 × 106 × 93 3.9 → 2.9 ms.
 template <int MODE>
 __global__ void __launch_bounds__(kBlock) k_rk_node(GridDev g, const double* __restrict__ phi_in,
                                                     const double* __restrict__ phi_n, const double* __restrict__ S,
                                                     double* __restrict__ out, int stage, double dt, double e,
-                                                    double c) {
+                                                    double c, Div by_less, Div by_more, Div by_nz) {
   const unsigned xcd = blockIdx.x % kXcds, t = blockIdx.x / kXcds * kBlock + threadIdx.x;
   const unsigned j0 = (unsigned)g.ny * xcd / kXcds, j1 = (unsigned)g.ny * (xcd + 1) / kXcds;
   const unsigned plane = (j1 - j0) * (unsigned)g.nz;
   if (plane == 0 || t >= plane * (unsigned)g.nx) return;
-  const int i = (int)(t / plane), r = (int)(t % plane), j = (int)j0 + r / g.nz, k = r % g.nz;
+  const int i = (int)div_u32(t, j1 - j0 == (unsigned)g.ny / kXcds ? by_less : by_more), r = (int)(t - i * plane);
+  const int row = (int)div_u32((unsigned)r, by_nz), j = (int)j0 + row, k = r - row * g.nz;
   const unsigned uid = ((unsigned)i * g.ny + j) * g.nz + k;
   const double* __restrict__ p = phi_in + uid;
-  const int n3[3] = {g.nx, g.ny, g.nz};
-  const int c3[3] = {i, j, k};
-  const int stride[3] = {g.ny * g.nz, g.nz, 1};
   const double s = MODE == 1 ? S[uid] : -1.0;
   const double sg = s >= 0.0 ? 1.0 : -1.0;
-  double acc = 0.0, f[7];
+  // all values before any arithmetic; ghosts by index in z and y, where a wave mostly has some, by branch
+  // in x, where it has them as a whole
+  double f[3][7];
 #pragma unroll
-  for (int ax = 0; ax < 3; ++ax) {
-    if ((unsigned)(c3[ax] - 3) <= (unsigned)(n3[ax] - 7)) {
-#pragma unroll
-      for (int m = 0; m < 7; ++m) f[m] = p[(m - 3) * stride[ax]];
-    } else {
-#pragma unroll
-      for (int m = 0; m < 7; ++m) f[m] = p[(reflect(c3[ax] + m - 3, n3[ax]) - c3[ax]) * stride[ax]];
-    }
-    acc = godunov_axis(f, e, sg, acc);
+  for (int m = 0; m < 7; ++m) {
+    f[2][m] = p[reflect(k + m - 3, g.nz) - k];
+    if (m != 3) f[1][m] = p[(reflect(j + m - 3, g.ny) - j) * g.nz];
   }
-  out[uid] = stage_value<MODE>(acc, c, s, p[0], dt, stage > 0 ? phi_n[uid] : 0.0, stage);
+  f[1][3] = f[2][3];
+  const int plane_x = g.ny * g.nz;
+  if ((unsigned)(i - 3) <= (unsigned)(g.nx - 7)) {
+#pragma unroll
+    for (int m = 0; m < 7; ++m) f[0][m] = p[(m - 3) * plane_x];
+  } else {
+#pragma unroll
+    for (int m = 0; m < 7; ++m) f[0][m] = p[(reflect(i + m - 3, g.nx) - i) * plane_x];
+  }
+  double acc = 0.0;
+#pragma unroll
+  for (int ax = 0; ax < 3; ++ax) acc = godunov_axis(f[ax], e, sg, acc);
+  out[uid] = stage_value<MODE>(acc, c, s, f[2][3], dt, stage > 0 ? phi_n[uid] : 0.0, stage);
 }
 
 // The stage on large grids: a thread takes two nodes consecutive in k (16-byte loads, 8-byte aligned
@@ -342,7 +363,7 @@ __global__ void __launch_bounds__(kBlock) k_rk_march(GridDev g, const double* __
 
 // Whether a grid of so many nodes marches, and how far a thread then goes.
 // Marching pays once it has some 1300 blocks; below that too few waves are in flight: 161 × 145 × 127
-// nodes (2.97M) 6.87 ms marching, 7.28 ms by nodes; 137 × 120 × 103 (1.69M) 5.00 and 4.40 ms. A longer
+// nodes (2.97M) 6.95 ms marching, 7.15 ms by nodes; 137 × 120 × 103 (1.69M) 5.00 and 4.18 ms. A longer
 // march loads the seven starting planes less often but needs a larger grid for as many blocks: 4, 8 and 16
 // nodes take 12.4, 12.8, 13.6 ms at 6.1M nodes and 35.5, 34.2, 33.7 ms at 15.7M.
 bool stage_marches(int64_t total) { return total >= (int64_t)5 << 19; }
@@ -547,12 +568,15 @@ pb_status tvd_rk3(pb_ctx* ctx, const GridDev& g, double*& cur, double*& spare, d
             nic = (g.nx + len - 1) / len, nb = nkt * njt * nic;
   const unsigned blocks = kXcds * (march ? (unsigned)((nb + kXcds - 1) / kXcds)
                                          : blocks_for((int64_t)((g.ny + kXcds - 1) / kXcds) * g.nz * g.nx));
+  const uint64_t rows = (uint64_t)(g.ny / kXcds);  // or one more, of an XCD's slab in k_rk_node
+  const Div by_less = div_by(std::max<uint64_t>(rows, 1) * g.nz), by_more = div_by((rows + 1) * g.nz), by_nz = div_by(g.nz);
   auto stage = [&](const double* in, const double* phi_n, double* out, int st) {
     if (march)
       (mode == 0 ? k_rk_march<0> : k_rk_march<1>)<<<blocks, kBlock, 0, ctx->stream>>>(g, in, phi_n, S, out, st, dt, e,
                                                                                      c, len, nkt, nic, nb);
     else
-      (mode == 0 ? k_rk_node<0> : k_rk_node<1>)<<<blocks, kBlock, 0, ctx->stream>>>(g, in, phi_n, S, out, st, dt, e, c);
+      (mode == 0 ? k_rk_node<0> : k_rk_node<1>)<<<blocks, kBlock, 0, ctx->stream>>>(g, in, phi_n, S, out, st, dt, e, c,
+                                                                                  by_less, by_more, by_nz);
   };
   for (int s = 0; s < steps; ++s) {
     Scope t(ctx, "levelset");
