@@ -147,7 +147,7 @@ def load_net(ctx, args):
 
 def timed_solve(ctx, band, at, prm, opts, q, warm=True, warm_tol=None):
     """Wall time of one solve from x0; returns (seconds, stats). warm: one untimed solve
-    first (it warms the caches, the workspace and the far-field autotuner), to warm_tol if
+    first (it warms the caches, the workspace and a batch's far-field autotuner), to warm_tol if
     given (a loose tolerance: the same set-up for a fraction of the iterations)."""
     import torch
 
@@ -343,7 +343,7 @@ def batch_leg(net, rec, tol):
 
 def bench_batch(args):
     """64 molecules of uneven size: per step, every level set and band, then one batched
-    mixed-precision solve (persistent far-field launch, captured Arnoldi-step graph) and
+    mixed-precision solve (one far-field launch per application, captured Arnoldi-step graph) and
     every energy."""
     import torch
 

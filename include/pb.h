@@ -258,7 +258,7 @@ typedef struct {
   int graph_replays;   /* replays of the captured Arnoldi-step graph */
   int far_tile;        /* far-field sources per LDS tile chosen by the autotuner */
   int far_tpl;         /* far-field targets per lane chosen by the autotuner */
-  int n_items;         /* work items of the persistent far-field launch */
+  int n_items;         /* work items (blocks) of a far-field launch */
   int outer;           /* refinement steps */
   int far_symmetric;   /* 1 if the autotuner chose the symmetric far-field kernel (each
                           unordered pair once, both directions; far_tile/far_tpl then give
@@ -267,7 +267,7 @@ typedef struct {
 
 /* Solves n_mol independent molecules (section "Fast linear solvers" for each) in one batch,
    mixed precision (opts->precision must be PB_MIXED): every operator application of the
-   batch is one persistent far-field launch over a largest-first list of equal-cost
+   batch is one far-field launch over a largest-first list of equal-cost
    (molecule, target block, source chunk) items plus one near-field/reduce launch; one
    Arnoldi step of all molecules is a captured hipGraph replayed until every molecule has
    converged. bands: host array of n_mol bands (device arrays inside). atoms: host array of
