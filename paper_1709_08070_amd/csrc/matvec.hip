@@ -221,8 +221,8 @@ F32Params f32params(const Derived& d, double sigma) {
                    (float)(rcs * rcs * 1.001)};
 }
 
-pb_status mixed_prepare(pb_ctx* ctx, const pb_band* band, const Derived& d) {
-  PB_TRY(near_build(ctx, band, d, "mx_", ctx->mixed));
+pb_status mixed_prepare(pb_ctx* ctx, const pb_band* band, const Derived& d, NearBuild what) {
+  PB_TRY(near_build(ctx, band, d, "mx_", ctx->mixed, what));
   const int n = (int)band->n;
   MixedPlan& P = ctx->mixed;
   P.far_cfg = far_choice(ctx, n, d.kappa > 0.0);
@@ -249,8 +249,7 @@ pb_status matvec_mixed(pb_ctx* ctx, const pb_band* band, const Derived& d, const
   if (S < 0) return ctx->fail(PB_ENOMEM, "far-field work list");
   {
     Scope t(ctx, "near_f64");
-    k_near_spmv<<<(unsigned)(((int64_t)n * kRowLanes + kBlock - 1) / kBlock), kBlock, 0, ctx->stream>>>(
-        n, P.row, P.col, P.coef, p, near);
+    PB_TRY(near_apply(ctx, band, d, P, p, near));
   }
   {
     Scope t(ctx, "reduce");
@@ -280,11 +279,15 @@ extern "C" pb_status pb_ibim_matvec(pb_ctx* ctx, const pb_band* band, const pb_p
   if (precision == PB_FP64) {
     PB_TRY(matvec_fp64(ctx, band, d, p, y));
   } else if (precision == PB_MIXED) {
-    PB_TRY(mixed_prepare(ctx, band, d));
+    PB_TRY(mixed_prepare(ctx, band, d, NearBuild::once));
     PB_TRY(matvec_mixed(ctx, band, d, p, y));
   } else {
-    PB_TRY(tree_prepare(ctx, band, d, prm->tree_degree, prm->tree_theta, ctx->tree, "tc_"));
-    PB_TRY(matvec_tree(ctx, band, d, p, y, ctx->tree));
+    PB_TRY(tree_prepare(ctx, band, d, prm->tree_degree, prm->tree_theta, ctx->tree, "tc_", nullptr, nullptr,
+                        NearBuild::once));
+    PB_TRY(matvec_tree(ctx, band, d, p, y, ctx->tree, (int64_t*)ctx->host_pin_dev));
+    PB_TRY(sync(ctx, "pb_ibim_matvec"));
+    ctx->tree.near.nnz = *(volatile int64_t*)ctx->host_pin;
+    return PB_OK;
   }
   return sync(ctx, "pb_ibim_matvec");
 }

@@ -883,7 +883,7 @@ pb_status nn_prepare(pb_ctx* ctx, const pb_band* band, const Derived& d) {
   PB_TRY(bufs(ctx, n, B));
   if (!band->phi) return ctx->fail(PB_EINVAL, "the learned path needs the band's phi array");
   MixedPlan P;
-  PB_TRY(near_build(ctx, band, d, "nn_", P, true));
+  PB_TRY(near_build(ctx, band, d, "nn_", P, NearBuild::cells));
   const unsigned nb = (unsigned)((n + kBlock - 1) / kBlock);
   k_knn<<<(unsigned)((n + kKnnWaves - 1) / kKnnWaves), 64 * kKnnWaves, 0, ctx->stream>>>(n, band_dev(band), cells_dev(P),
                                                                                        B.nbr);
@@ -1147,7 +1147,7 @@ pb_status nn_batch_prepare(pb_ctx* ctx, int n_mol, const pb_band* bands, const i
     const pb_band* band = &bands[m];
     const int n = (int)band->n, o = off_host[m];
     MixedPlan P;
-    PB_TRY(near_build(ctx, band, d, "nnb_", P, true));
+    PB_TRY(near_build(ctx, band, d, "nnb_", P, NearBuild::cells));
     const unsigned nbk = (unsigned)((n + kBlock - 1) / kBlock);
     int* nbr_m = nb.nbr + (int64_t)o * kSlots;
     k_knn<<<(unsigned)((n + kKnnWaves - 1) / kKnnWaves), 64 * kKnnWaves, 0, ctx->stream>>>(n, band_dev(band),

@@ -61,7 +61,7 @@ struct MixedPlan {
   float4* M = nullptr;            //               σ·(ψ weight)·n
   float4* N = nullptr;            //               n (the target side's normal)
   float4* box = nullptr;          // bounding boxes of groups of 256 records (lo, hi)
-  int64_t* row = nullptr;         // near-field CSR
+  int64_t* row = nullptr;         // near-field CSR (null in a plan for one application)
   int* col = nullptr;
   double4* coef = nullptr;
   int far_cfg = 0;                // far-field kernel (far_choice)
@@ -69,6 +69,8 @@ struct MixedPlan {
   const int* cell_nodes = nullptr;
   const int* cell_of = nullptr;
   const double4* cell_pos = nullptr;
+  const double4* cell_nrm = nullptr;  // normals and FP32 keys in cell order (not with cells alone)
+  const float4* cell_key = nullptr;
 };
 
 // Treecode far field of the mixed operator for one band (tree.hip): octree over the FP32
@@ -203,9 +205,15 @@ pb_status host_pin(pb_ctx* ctx);
 
 // Operator internals used by the solver.
 pb_status matvec_fp64(pb_ctx* ctx, const pb_band* band, const Derived& d, const double* p, double* y);
-pb_status mixed_prepare(pb_ctx* ctx, const pb_band* band, const Derived& d);
+// What near_build makes: the cell list alone; that and the FP32 records' geometry, for an operator that is
+// applied once (near_apply then walks the cells); or the near-field matrix as well.
+enum class NearBuild { cells, once, matrix };
+pb_status mixed_prepare(pb_ctx* ctx, const pb_band* band, const Derived& d, NearBuild what = NearBuild::matrix);
 pb_status near_build(pb_ctx* ctx, const pb_band* band, const Derived& d, const char* pfx, MixedPlan& P,
-                     bool cells_only = false);
+                     NearBuild what = NearBuild::matrix);
+// total_dev: receives the number of near pairs of a plan without a matrix (may be null).
+pb_status near_apply(pb_ctx* ctx, const pb_band* band, const Derived& d, const MixedPlan& P, const double* p,
+                     double* near, int64_t* total_dev = nullptr);
 struct F32Params;
 F32Params f32params(const Derived& d, double sigma);
 // learned preconditioner (nn.hip)
@@ -241,11 +249,12 @@ pb_status matvec_mixed(pb_ctx* ctx, const pb_band* band, const Derived& d, const
 // by the first plan of a solve and reused by the second.
 struct TreeDev;
 pb_status tree_prepare(pb_ctx* ctx, const pb_band* band, const Derived& d, int degree, double theta, TreePlan& T,
-                       const char* pfx, const MixedPlan* near = nullptr, std::shared_ptr<TreeDev>* tree = nullptr);
+                       const char* pfx, const MixedPlan* near = nullptr, std::shared_ptr<TreeDev>* tree = nullptr,
+                       NearBuild what = NearBuild::matrix);
 // Exact tree-order coordinates and the anchors of the direct sources' groups.
 pb_status tree_coords(pb_ctx* ctx, const pb_band* band, const TreePlan& T);
 pb_status matvec_tree(pb_ctx* ctx, const pb_band* band, const Derived& d, const double* p, double* y,
-                      const TreePlan& T);
+                      const TreePlan& T, int64_t* near_total_dev = nullptr);
 // PB_TREE solves: the refinement's residuals on bands of at least kTreeFineMin nodes come from a
 // finer treecode (degree 7, θ = 0.5: at the FP32 rounding level of the dense mixed operator,
 // and about 5× cheaper than it at 6e5 nodes), below that from the dense mixed operator.

@@ -425,7 +425,7 @@ pb_status tree_coords(pb_ctx* ctx, const pb_band* band, const TreePlan& T) {
 }
 
 pb_status matvec_tree(pb_ctx* ctx, const pb_band* band, const Derived& d, const double* p, double* y,
-                      const TreePlan& T) {
+                      const TreePlan& T, int64_t* near_total_dev) {
   const MixedPlan& P = T.near;
   const int n = (int)band->n;
   if (T.band_key != band->px || T.n != n || T.rc != d.rc)
@@ -444,8 +444,7 @@ pb_status matvec_tree(pb_ctx* ctx, const pb_band* band, const Derived& d, const 
   }
   {
     Scope t(ctx, "near_f64");
-    k_near_spmv<<<(unsigned)(((int64_t)n * kRowLanes + kBlock - 1) / kBlock), kBlock, 0, ctx->stream>>>(
-        n, P.row, P.col, P.coef, p, near);
+    PB_TRY(near_apply(ctx, band, d, P, p, near, near_total_dev));
   }
   {
     Scope t(ctx, "reduce");

@@ -871,11 +871,11 @@ pb_status tree_build(pb_ctx* ctx, const pb_band* band, const MixedPlan& P, TreeD
 }  // namespace
 
 pb_status tree_prepare(pb_ctx* ctx, const pb_band* band, const Derived& d, int degree, double theta, TreePlan& T,
-                       const char* pfx, const MixedPlan* near, std::shared_ptr<TreeDev>* tree) {
+                       const char* pfx, const MixedPlan* near, std::shared_ptr<TreeDev>* tree, NearBuild what) {
   const int n = (int)band->n;
   const std::string px_ = pfx;
   if (near) T.near = *near;  // the near field depends on the geometry only: shared between plans
-  else PB_TRY(near_build(ctx, band, d, (px_ + "n_").c_str(), T.near));
+  else PB_TRY(near_build(ctx, band, d, (px_ + "n_").c_str(), T.near, what));
   const MixedPlan& P = T.near;
   const int P1 = degree + 1, P3 = P1 * P1 * P1;
   std::shared_ptr<TreeDev> hp = tree && *tree && (*tree)->n == n ? *tree : nullptr;

@@ -102,3 +102,42 @@ def test_row_scan_lengths(env, n):
     y = pb.pb_ibim_matvec(ctx, b, prm, p, pb.PB_MIXED)
     ref = pb.pb_ibim_matvec(ctx, b, prm, p, pb.PB_FP64)
     assert float((y - ref).abs().max()) <= 1e-5 * float(ref.abs().max())
+
+
+@pytest.mark.parametrize("n", [1, 3, 63, 64, 65, 127, 128, 129, 300])
+def test_operator_of_near_pairs_only(env, n):
+    """Every pair nearer than r_c: the mixed and the tree operator are then their FP64 near fields alone,
+    n sources for each target, around the turns of 64 and the queue of 128. Bar 1e-9 of the largest
+    entry: both sides are FP64, and a pair in FP32, left out or taken twice shows at 1e-7 or above."""
+    pb, torch, ctx = env
+    print("case: near pairs only, n =", n, flush=True)
+    prm = pb.params(0.5)
+    x = _cloud("ball", n)
+    x *= 0.45 * prm.near_k * prm.h / np.linalg.norm(x, axis=1).max()
+    b = _band(pb, torch, x, n)
+    p = torch.tensor(np.random.default_rng(n).normal(size=2 * n), device="cuda")
+    ref = pb.pb_ibim_matvec(ctx, b, prm, p, pb.PB_FP64)
+    for precision in (pb.PB_MIXED, pb.PB_TREE):
+        y = pb.pb_ibim_matvec(ctx, b, prm, p, precision)
+        assert float((y - ref).abs().max()) <= 1e-9 * float(ref.abs().max())
+    assert ctx.tree_info()["near_pairs"] == n * n
+
+
+@pytest.mark.parametrize("n", [8190, 8191, 8192, 16382, 16383, 16384])
+def test_near_matrix_row_starts(env, n):
+    """A solve keeps its near field as a matrix: four steps with it and four with the FP64 operator from the same
+    start give the same iterate, to 1e-3 of its largest entry (1e-5 per application, the bar of the operator
+    above, times the growth over four steps); rows that start wrong change entries by their own size."""
+    pb, torch, ctx = env
+    print("case: near matrix, n =", n, flush=True)
+    rng = np.random.default_rng(n)
+    x = rng.normal(size=(n, 3))
+    x *= (0.15 * np.sqrt(n) / np.linalg.norm(x, axis=1))[:, None]
+    b = _band(pb, torch, x[np.lexsort(x.T[::-1].round(0))], n)
+    atoms = torch.tensor([[0.0, 0.0, 0.0, 1.5, 1.0]], dtype=torch.float64, device="cuda")
+    prm = pb.params(0.5)
+    out = []
+    for precision in (pb.PB_MIXED, pb.PB_FP64):
+        opts = pb.solve_opts(precision=precision, tol=1e-12, max_iter=4)
+        out.append(pb.pb_ibim_solve(ctx, b, atoms, prm, opts, allow_noconv=True)[0])
+    assert float((out[0] - out[1]).abs().max()) <= 1e-3 * float(out[1].abs().max())
