@@ -120,17 +120,19 @@ __global__ void __launch_bounds__(kBlock) k_cell_place(int n, BandDev b, const d
 }
 
 constexpr int kNearWaves = kBlock / 64;  // targets per block of the near-list kernels
+constexpr int kAhead = 4;                // steps of 64 candidates read at once
+constexpr int kNearQueue = 64 * kAhead + 64;
 constexpr int kHitSlots = 1024;          // counters of k_near_once, by target, so that few waves share one
 
 // Visits the near sources of target i (FP32 distance below r_c) in a fixed order: the nine
 // ranges of cell_ranges one after the other, 64 candidates at a time. Per step every lane calls
-// f(hit, q, node, mask) with its candidate's place q in cell order and the ballot of the hits. One wave
+// f(hit, q, mask) with its candidate's place q in cell order and the ballot of the hits, and after each turn of
+// kAhead steps turn(last). One wave
 // per target. The ranges (30 to 45 candidates each) are read as one sequence, four steps' records at once:
 // bound by the latency of those reads, of which a loop over the ranges has nine in a row.
-template <typename F>
+template <typename F, typename T>
 __device__ __forceinline__ void for_near_wave(const float3& t, int c, const float4* __restrict__ key,
-                                              const CellsDev& cells, float rc2, F f) {
-  constexpr int kAhead = 4;
+                                              const CellsDev& cells, float rc2, F f, T turn) {
   const int lane = threadIdx.x & 63;
   int lo, hi;
   cell_ranges(cells, c, lo, hi);
@@ -158,8 +160,9 @@ __device__ __forceinline__ void for_near_wave(const float3& t, int c, const floa
     for (int u = 0; u < kAhead; ++u) {
       if (f0 + 64 * u >= m) break;
       const bool hit = f0 + 64 * u + lane < m && r2_f32(t.x, t.y, t.z, k[u].x, k[u].y, k[u].z) < rc2;
-      f(hit, q[u], __float_as_int(k[u].w), __ballot(hit));
+      f(hit, q[u], __ballot(hit));
     }
+    turn(f0 + 64 * kAhead >= m);
   }
 }
 
@@ -167,11 +170,11 @@ __device__ __forceinline__ void for_near_wave(const float3& t, int c, const floa
 __global__ void __launch_bounds__(kBlock) k_near_count(int n, BandDev b, double cx, double cy, double cz, double sigma,
                                                        const float4* __restrict__ key, CellsDev cells, float rc2,
                                                        int64_t* __restrict__ counts) {
-  const int i = blockIdx.x * kNearWaves + (threadIdx.x >> 6);
+  const int i = __builtin_amdgcn_readfirstlane(blockIdx.x * kNearWaves + (threadIdx.x >> 6));
   if (i >= n) return;
   int64_t cnt = 0;
   for_near_wave(coords_f32(b, i, cx, cy, cz, sigma), cells.cell_of[i], key, cells, rc2,
-                [&](bool, int, int, unsigned long long mask) { cnt += __popcll(mask); });
+                [&](bool, int, unsigned long long mask) { cnt += __popcll(mask); }, [](bool) {});
   if ((threadIdx.x & 63) == 0) {
     counts[i] = cnt;
     if (i == n - 1) counts[n] = 0;
@@ -179,8 +182,9 @@ __global__ void __launch_bounds__(kBlock) k_near_count(int n, BandDev b, double 
 }
 
 // The near pairs of target i, up to 64 at a time: hits (about 50 of 200 to 400 candidates) queue up in
-// the wave's 128 entries of LDS, and pairs(q) is called by every lane that has one, with the source's
-// place q in cell order, and full(cnt) by all lanes after each turn of cnt ≤ 64 pairs. Whole waves; no block barrier.
+// the wave's kNearQueue entries of LDS over a turn of kAhead steps, and pairs(q) is called by every lane that has
+// one, with the source's place q in cell order, and full(cnt) by all lanes after each cnt ≤ 64 pairs. One place
+// for the pairs' code, outside the unrolled steps. Whole waves; no block barrier.
 template <typename P, typename F>
 __device__ __forceinline__ void for_near_pairs(const float3& t, int c, const float4* __restrict__ key,
                                                const CellsDev& cells, float rc2, int* queue, P pairs, F full) {
@@ -191,22 +195,26 @@ __device__ __forceinline__ void for_near_pairs(const float3& t, int c, const flo
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   };
-  for_near_wave(t, c, key, cells, rc2, [&](bool hit, int q, int, unsigned long long mask) {
-    if (hit) queue[pending + __popcll(mask & ((1ull << lane) - 1ull))] = q;
-    pending += __popcll(mask);
-    if (pending >= 64) {
-      lds_order();
-      pairs(queue[lane]);
-      full(64);
-      pending -= 64;
-      const int rest = lane < pending ? queue[64 + lane] : 0;
-      lds_order();
-      if (lane < pending) queue[lane] = rest;
-    }
-  });
-  lds_order();
-  if (lane < pending) pairs(queue[lane]);
-  full(pending);
+  for_near_wave(
+      t, c, key, cells, rc2,
+      [&](bool hit, int q, unsigned long long mask) {  // pending < 64 before a turn's first step
+        if (hit) queue[pending + __popcll(mask & ((1ull << lane) - 1ull))] = q;
+        pending += __popcll(mask);
+      },
+      [&](bool last) {
+        lds_order();
+        int at = 0;
+        for (; pending - at >= (last ? 1 : 64); at += 64) {
+          const int cnt = min(pending - at, 64);
+          if (lane < cnt) pairs(queue[at + lane]);
+          full(cnt);
+        }
+        if (last) return;
+        pending -= at;
+        const int rest = lane < pending ? queue[at + lane] : 0;
+        lds_order();
+        if (lane < pending) queue[lane] = rest;
+      });
 }
 
 // Near-field block matrix: for each near pair the FP64 coefficients of
@@ -219,9 +227,9 @@ __global__ void __launch_bounds__(kBlock) k_near_fill(int n, BandDev b, double c
                                                       const double4* __restrict__ nrm, CellsDev cells, float rc2,
                                                       KParams kp, const int64_t* __restrict__ row,
                                                       int* __restrict__ col, double4* __restrict__ coef) {
-  __shared__ int queue[kNearWaves][128];
+  __shared__ int queue[kNearWaves][kNearQueue];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int i = blockIdx.x * kNearWaves + wave;
+  const int i = __builtin_amdgcn_readfirstlane(blockIdx.x * kNearWaves + wave);  // the wave's: scalar loads
   if (i >= n) return;
   const double xi = b.px[i], yi = b.py[i], zi = b.pz[i], nxi = b.nx[i], nyi = b.ny[i], nzi = b.nz[i];
   const double ci = b.curv ? b.curv[i] : 0.0;
@@ -242,16 +250,16 @@ __global__ void __launch_bounds__(kBlock) k_near_fill(int n, BandDev b, double c
 // near = (near block matrix)·p without the matrix, for an operator that is applied once to its band: the
 // same pairs and coefficients as k_near_fill's, multiplied where they are formed, the lanes' sums added in a
 // fixed order. Each wave adds its pairs to one of kHitSlots counters (hits, may be null). At 13,393 nodes it
-// takes 17 µs in place of count, scan, fill and product (9 + 12 + 19 + 8) and a synchronization between them; 195 at
-// 185,127, 748 at 724,665.
+// takes 14 µs in place of count, scan, fill and product (9 + 12 + 19 + 8) and a synchronization between them; 141 at
+// 185,127, 566 at 724,665 (17, 195 and 748 with four waves a SIMD).
 __global__ void __launch_bounds__(kBlock) k_near_once(int n, BandDev b, double cx, double cy, double cz, double sigma,
                                                       double scale, const float4* __restrict__ key,
                                                       const double4* __restrict__ nrm, CellsDev cells, float rc2,
                                                       KParams kp, const double* __restrict__ p,
                                                       double* __restrict__ near, unsigned long long* __restrict__ hits) {
-  __shared__ int queue[kNearWaves][128];
+  __shared__ int queue[kNearWaves][kNearQueue];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int i = blockIdx.x * kNearWaves + wave;
+  const int i = __builtin_amdgcn_readfirstlane(blockIdx.x * kNearWaves + wave);  // the wave's: scalar loads
   if (i >= n) return;
   const double xi = b.px[i], yi = b.py[i], zi = b.pz[i], nxi = b.nx[i], nyi = b.ny[i], nzi = b.nz[i];
   const double ci = b.curv ? b.curv[i] : 0.0;
@@ -296,9 +304,12 @@ __global__ void __launch_bounds__(kHitSlots) k_hit_total(const unsigned long lon
 
 }  // namespace
 
-// At 185,127 nodes (9.3M pairs) the count takes 70 µs and the fill 183 µs (its 335 MB of matrix
-// at 1.8 TB/s, the FP64 kernels beside it); 104 and 228 with a loop over the nine ranges, 345 and 558 with 27
-// separate cells walked through index lists and the library's exp.
+// Count and fill are bound by the waves in flight over a chain of five dependent reads (cell, ranges, keys, records,
+// queue): with the pairs' code in one place and the target's data in scalar registers k_near_fill holds 76 vector
+// registers instead of 112, six waves a SIMD instead of four: 40 µs at 45,818 nodes (52), the count 20 (22). At 185,127 nodes
+// (9.3M pairs) the earlier form took 183 and 70 µs; 228 and 104 with a loop over the nine ranges, 558 and 345 with 27
+// separate cells walked through index lists and the library's exp. Turns of 2, 3 and 6 steps are no faster (601, 563, 589 µs
+// against 566 in k_near_once at 724,665 nodes), nor is a bound of eight waves, which spills.
 
 // Geometry of the mixed operator for one band: centre and scale of the FP32 records, the
 // cell list and the FP64 near-field CSR matrix. Buffers are named `<pfx>...` in the context
