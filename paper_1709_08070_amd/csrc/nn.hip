@@ -17,6 +17,7 @@
 // Training target for a pair (v, u = A⁻¹v): T = (Λu − v)/s per node; the loss is
 // Σ|O − T|² / Σ|T|² over the band.
 #include <algorithm>
+#include <climits>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -103,15 +104,17 @@ __device__ __forceinline__ float dact(float x) { return x > 0.f ? 1.f : kSlope; 
 // 16 nearest band nodes by projection distance (ties by index; self first), from the cell list:
 // one wave per node.
 //  1. The lanes form the squared distances of the node's candidates (the nine ranges of its 27
-//     cells) and keep them in LDS (kKnnCand) and from there in registers.
+//     cells, up to kKnnCand) in registers, 64 a row.
 //  2. Bisection on a squared radius, by ballots, for one that holds 16 to 64 candidates (all
 //     of them where there are no more than 64).
 //  3. Those are compacted, and each ranks itself among them by (distance, index): rank s < 16 is
 //     slot s.
 // Where a node has more than kKnnCand candidates or no such radius exists (48 equal distances),
-// the wave's first lane keeps a sorted list of 16 over a scan of the ranges instead. 112 µs at
-// 55,111 nodes; one thread per node keeping such a list took 594 µs: its insertions are a serial
-// chain and the lanes' candidates are scattered.
+// the wave takes the least (distance, index) beyond the last sixteen times over the candidates.
+// Bound by the waves in flight over the chain of reads and ballots: 57 µs at 55,111 nodes, with the ranges
+// read as one sequence, four rows at once, and 59 registers, eight waves a SIMD. A loop over the nine ranges
+// through 24 KB of LDS a block took 115 µs, a sorted list per thread 594. The general case takes
+// 6.7 ms where 40,000 nodes fill a ball of 2.8 Å (15.7 with a sorted list in one lane).
 constexpr int kKnnCand = 512;
 constexpr int kKnnWaves = 4;
 
@@ -120,10 +123,10 @@ __device__ __forceinline__ double dist2_rn(double dx, double dy, double dz) {
 }
 
 __global__ void __launch_bounds__(64 * kKnnWaves) k_knn(int n, BandDev b, CellsDev cells, int* __restrict__ nbr) {
-  __shared__ double sd[kKnnWaves][kKnnCand];
-  __shared__ int sq[kKnnWaves][kKnnCand];
+  __shared__ double sd[kKnnWaves][64];
+  __shared__ int sq[kKnnWaves][64];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int i = blockIdx.x * kKnnWaves + w;
+  const int i = __builtin_amdgcn_readfirstlane(blockIdx.x * kKnnWaves + w);
   if (i >= n) return;  // whole waves; the kernel has no block barrier
   auto lds_order = [] {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -133,26 +136,43 @@ __global__ void __launch_bounds__(64 * kKnnWaves) k_knn(int n, BandDev b, CellsD
   const double xi = b.px[i], yi = b.py[i], zi = b.pz[i];
   int lo, hi;
   cell_ranges(cells, cells.cell_of[i], lo, hi);
-  int m = 0;
-  for (int r = 0; r < 9; ++r) m += __builtin_amdgcn_readlane(hi, r) - __builtin_amdgcn_readlane(lo, r);
+  int first[9], shift[9], m = 0;  // range r holds candidates first[r] … of one sequence, at shift[r] + their number
+#pragma unroll
+  for (int r = 0; r < 9; ++r) {
+    const int a = __builtin_amdgcn_readlane(lo, r), e = __builtin_amdgcn_readlane(hi, r);
+    first[r] = m;
+    shift[r] = a - m;
+    m += e - a;
+  }
   int* __restrict__ out = nbr + (int64_t)i * kSlots;
   bool done = false;
   if (m <= kKnnCand) {
-    int at = 0;
-    for (int r = 0; r < 9; ++r) {
-      const int a = __builtin_amdgcn_readlane(lo, r), e = __builtin_amdgcn_readlane(hi, r);
-      for (int q = a + lane; q < e; q += 64) {
-        const double4 x = cells.pos[q];
-        sd[w][at + q - a] = dist2_rn(xi - x.x, yi - x.y, zi - x.z);
-        sq[w][at + q - a] = q;
-      }
-      at += e - a;
-    }
-    lds_order();
-    constexpr int kRows = kKnnCand / 64;
+    constexpr int kRows = kKnnCand / 64, kAhead = 4;  // rows read at once
     double d[kRows];
+    int q[kRows];
 #pragma unroll
-    for (int r = 0; r < kRows; ++r) d[r] = r * 64 + lane < m ? sd[w][r * 64 + lane] : INFINITY;
+    for (int r0 = 0; r0 < kRows; r0 += kAhead) {
+#pragma unroll
+      for (int r = r0; r < r0 + kAhead; ++r) {
+        d[r] = INFINITY;
+        q[r] = 0;
+      }
+      if (r0 * 64 < m) {
+        double4 x[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+          const int g = min((r0 + u) * 64 + lane, m - 1);
+          int s = shift[0];
+#pragma unroll
+          for (int r = 1; r < 9; ++r) s = g >= first[r] ? shift[r] : s;
+          q[r0 + u] = g + s;
+          x[u] = cells.pos[q[r0 + u]];
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)
+          if ((r0 + u) * 64 + lane < m) d[r0 + u] = dist2_rn(xi - x[u].x, yi - x[u].y, zi - x[u].z);
+      }
+    }
     // cells are at least r_c wide: (2 cells)² bounds what the bisection starts from
     const double top = 12.0 / (cells.inv * cells.inv);
     double t = m <= 64 ? INFINITY : top, tl = 0.0, th = INFINITY;
@@ -168,12 +188,7 @@ __global__ void __launch_bounds__(64 * kKnnWaves) k_knn(int n, BandDev b, CellsD
       else break;
     }
     if (cnt <= 64 && (cnt >= kSlots || m <= 64)) {
-      // compact the survivors into the first cnt LDS slots; a survivor's place is never beyond
-      // its own, and every lane holds its distances in registers, its q is read before any write
-      int q[kRows];
-#pragma unroll
-      for (int r = 0; r < kRows; ++r) q[r] = r * 64 + lane < m ? sq[w][r * 64 + lane] : 0;
-      lds_order();
+      // compact the survivors, at most 64, into the wave's LDS slots
       int base = 0;
 #pragma unroll
       for (int r = 0; r < kRows; ++r)
@@ -203,33 +218,36 @@ __global__ void __launch_bounds__(64 * kKnnWaves) k_knn(int n, BandDev b, CellsD
     }
   }
   if (done) return;
-  // the general case: lane r < 9's range bounds are needed by lane 0, so every lane takes part in
-  // the reads of them
-  double bd[kSlots];
-  int bi[kSlots];
-  for (int s = 0; s < kSlots; ++s) {
-    bd[s] = INFINITY;
-    bi[s] = i;
-  }
-  for (int r = 0; r < 9; ++r) {
-    const int a = __builtin_amdgcn_readlane(lo, r), e = __builtin_amdgcn_readlane(hi, r);
-    for (int q = a; q < e; ++q) {
-      const double4 x = cells.pos[q];
-      const int j = cells.nodes[q];
+  // the general case: slot by slot, the least (distance, index) after the last one's
+  double ld = -1.0;
+  int lj = -1;
+  for (int t = 0; t < kSlots; ++t) {
+    double bd = INFINITY;
+    int bj = INT_MAX;
+    for (int g = lane; g < m; g += 64) {
+      int s = shift[0];
+#pragma unroll
+      for (int r = 1; r < 9; ++r) s = g >= first[r] ? shift[r] : s;
+      const double4 x = cells.pos[g + s];
+      const int j = cells.nodes[g + s];
       const double d2 = dist2_rn(xi - x.x, yi - x.y, zi - x.z);
-      if (d2 > bd[kSlots - 1] || (d2 == bd[kSlots - 1] && j >= bi[kSlots - 1])) continue;
-      int s = kSlots - 1;
-      while (s > 0 && (bd[s - 1] > d2 || (bd[s - 1] == d2 && bi[s - 1] > j))) {
-        bd[s] = bd[s - 1];
-        bi[s] = bi[s - 1];
-        --s;
+      if ((d2 > ld || (d2 == ld && j > lj)) && (d2 < bd || (d2 == bd && j < bj))) {
+        bd = d2;
+        bj = j;
       }
-      bd[s] = d2;
-      bi[s] = j;
     }
+    for (int off = 32; off > 0; off >>= 1) {
+      const double od = __shfl_xor(bd, off);
+      const int oj = __shfl_xor(bj, off);
+      if (od < bd || (od == bd && oj < bj)) {
+        bd = od;
+        bj = oj;
+      }
+    }
+    if (lane == 0) out[t] = bd < INFINITY ? bj : i;
+    ld = bd;
+    lj = bj;
   }
-  if (lane == 0)
-    for (int s = 0; s < kSlots; ++s) out[s] = bd[s] < INFINITY ? bi[s] : i;
 }
 
 // Per-node geometry features: φ/ε, n (3), H·ε with H = (2/m) Σ_{j≠i} (n_j − n_i)·(x_j − x_i)/|x_j − x_i|².
