@@ -323,19 +323,34 @@ static __global__ void __attribute__((unused)) __launch_bounds__(kBlock) k_p2p_f
   far64_tile_loop<kBlock>(b, wpsi, wpsn, t0, n, j0, j1, kp, smem, out + t0, out + n + t0);
 }
 
-// y = Λp + Σ_chunks partial (+ near), in a fixed order.
+// y = Λp + Σ_chunks partial (+ near), in a fixed order: eight sums over every eighth chunk, then those
+// pairwise. One sum over all chunks, up to 256 of them, would round that often at the size of the result: on a
+// sphere of 45,818 nodes with a smooth density (179 chunks) the two halves of the FP64 operator have a relative
+// error of 0.7e-16 and 1.5e-16, with one sum 2.3e-16 and 2.8e-16. Bound by the reads of the partial sums, eight in
+// flight a thread.
 static __global__ void __attribute__((unused)) __launch_bounds__(kBlock) k_reduce(int n, int n_chunks, const double* __restrict__ partial,
                                                           const double* __restrict__ near,
                                                           const double* __restrict__ p, double lam1, double lam2,
                                                           double* __restrict__ y) {
+  constexpr int kSums = 8;
   int e = blockIdx.x * kBlock + threadIdx.x;
   if (e >= 2 * n) return;
-  double s = 0.0;
-  // unrolled so that eight loads are in flight; the sum keeps its chunk order
-#pragma unroll 8
-  for (int c = 0; c < n_chunks; ++c) s += partial[(size_t)c * 2 * n + e];
-  if (near) s += near[e];
-  y[e] = (e < n ? lam1 : lam2) * p[e] + s;
+  double s[kSums] = {}, v[kSums];
+  int c = 0;
+  for (; c + kSums <= n_chunks; c += kSums)
+#pragma unroll
+    for (int u = 0; u < kSums; ++u) s[u] += partial[(size_t)(c + u) * 2 * n + e];
+  // the rest, all read before any is added
+#pragma unroll
+  for (int u = 0; u < kSums; ++u) v[u] = c + u < n_chunks ? partial[(size_t)(c + u) * 2 * n + e] : 0.0;
+#pragma unroll
+  for (int u = 0; u < kSums; ++u) s[u] += v[u];
+#pragma unroll
+  for (int k = kSums / 2; k > 0; k /= 2)
+#pragma unroll
+    for (int u = 0; u < k; ++u) s[u] += s[u + k];
+  if (near) s[0] += near[e];
+  y[e] = (e < n ? lam1 : lam2) * p[e] + s[0];
 }
 
 // FP32 records of a band (layout above); with p == nullptr only the geometry is written
