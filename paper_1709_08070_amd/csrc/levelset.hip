@@ -267,7 +267,7 @@ __global__ void __launch_bounds__(kBlock) k_rk_node(GridDev g, const double* __r
   out[uid] = stage_value<MODE>(acc, c, s, f[2][3], dt, stage > 0 ? phi_n[uid] : 0.0, stage);
 }
 
-// The stage on large grids: a thread takes two nodes consecutive in k (16-byte loads, 8-byte aligned
+// The stage on large grids (stage_marches): a thread takes two nodes consecutive in k (16-byte loads, 8-byte aligned
 // only: rows may be odd) and marches len nodes in i with the seven x values of both in registers, a
 // block a tile of 32 (k) × 16 (j) columns: 11 loads for two nodes and a step instead of 38, and the
 // loads from far away (next x plane, S, φ_n) are issued a step ahead. Tiles go to the XCDs in
@@ -361,12 +361,18 @@ __global__ void __launch_bounds__(kBlock) k_rk_march(GridDev g, const double* __
   }
 }
 
-// Whether a grid of so many nodes marches, and how far a thread then goes.
+// Whether a grid marches, and how far a thread then goes.
 // Marching pays once it has some 1300 blocks; below that too few waves are in flight: 161 × 145 × 127
-// nodes (2.97M) 6.95 ms marching, 7.15 ms by nodes; 137 × 120 × 103 (1.69M) 5.00 and 4.18 ms. A longer
+// nodes (2.97M) 6.95 ms marching, 7.15 ms by nodes; 137 × 120 × 103 (1.69M) 5.00 and 4.18 ms. And its tiles of columns
+// have to be filled, 85% of them: 140 × 140 × 140 (2.7M, 85%) 6.24 ms marching, 6.12 by nodes; 180 × 170 × 90 (91%)
+// 5.67 and 6.13; 300 × 200 × 103 (6.2M, 77%) 13.9 and 13.0; 340 × 330 × 140 (15.7M, 86%) 31.8 and 34.9. On flat grids most
+// lanes would idle: 620 × 610 × 7 (21%) 18.9 and 5.8 ms, 300 × 260 × 34 (51%) 8.6 and 5.8. A longer
 // march loads the seven starting planes less often but needs a larger grid for as many blocks: 4, 8 and 16
 // nodes take 12.4, 12.8, 13.6 ms at 6.1M nodes and 35.5, 34.2, 33.7 ms at 15.7M.
-bool stage_marches(int64_t total) { return total >= (int64_t)5 << 19; }
+bool stage_marches(const GridDev& g) {
+  const int64_t cols = (int64_t)g.ny * g.nz, tiles = (int64_t)((g.ny + kStageJ - 1) / kStageJ) * ((g.nz + kStageK - 1) / kStageK);
+  return cols * g.nx >= (int64_t)5 << 19 && 100 * cols >= 85 * tiles * (kStageJ * kStageK);
+}
 int march_len(int64_t total) { return (int)std::min<int64_t>(std::max<int64_t>(total >> 20, 4), 16); }
 
 __global__ void __launch_bounds__(kBlock) k_sign(int64_t total, const double* __restrict__ phi, double h,
@@ -563,7 +569,7 @@ pb_status tvd_rk3(pb_ctx* ctx, const GridDev& g, double*& cur, double*& spare, d
                   int steps, double dt) {
   const int64_t total = (int64_t)g.nx * g.ny * g.nz;
   const double e = 4.0 * g.h * g.h * kWenoEps, c = 1.0 / (6.0 * g.h);
-  const bool march = stage_marches(total);
+  const bool march = stage_marches(g);
   const int len = march_len(total), nkt = (g.nz + kStageK - 1) / kStageK, njt = (g.ny + kStageJ - 1) / kStageJ,
             nic = (g.nx + len - 1) / len, nb = nkt * njt * nic;
   const unsigned blocks = kXcds * (march ? (unsigned)((nb + kXcds - 1) / kXcds)
