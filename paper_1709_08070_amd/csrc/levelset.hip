@@ -224,23 +224,40 @@ __device__ __forceinline__ unsigned div_u32(unsigned t, Div m) {
 
 // The stage with one thread per node: e = 4h²ε and c = 1/(6h) undo the scaling of godunov_axis. 32-bit
 // node indexing (grids hold fewer than 2^31 nodes). The XCDs take slabs of ny/8 rows, so that the
-// planes of a node's x neighbours lie in the L2 of its own XCD.
+// planes of a node's x neighbours lie in the L2 of its own XCD; on grids of less than 32 rows (kRows = false),
+// where one XCD would have up to twice the rows of another, slabs of an eighth of the (y, z) columns instead
+// (300 × 9 × 300 nodes 3.23 ms by rows, 2.21 by columns; from 32 rows on either is ahead, by up to 3 or 10%
+// as the shape has it).
 // Small grids wait on launches (an empty one takes 4 µs, a stage here under 6) and on one chain of index
 // arithmetic, loads and FP64 work (two waves per SIMD at 135,000 nodes): no divisions, no branch that a wave
 // takes both ways, 250 FP64 instructions a node. Level set of 54 × 51 × 49 nodes (150 stages; cavities
 // included) 1270 → 900 µs, of 85 × 79 × 70 2.11 → 1.56 ms, of 117 × 106 × 93 3.9 → 2.9 ms.
-template <int MODE>
+template <int MODE, bool kRows>
 __global__ void __launch_bounds__(kBlock) k_rk_node(GridDev g, const double* __restrict__ phi_in,
                                                     const double* __restrict__ phi_n, const double* __restrict__ S,
                                                     double* __restrict__ out, int stage, double dt, double e,
                                                     double c, Div by_less, Div by_more, Div by_nz) {
   const unsigned xcd = blockIdx.x % kXcds, t = blockIdx.x / kXcds * kBlock + threadIdx.x;
-  const unsigned j0 = (unsigned)g.ny * xcd / kXcds, j1 = (unsigned)g.ny * (xcd + 1) / kXcds;
-  const unsigned plane = (j1 - j0) * (unsigned)g.nz;
-  if (plane == 0 || t >= plane * (unsigned)g.nx) return;
-  const int i = (int)div_u32(t, j1 - j0 == (unsigned)g.ny / kXcds ? by_less : by_more), r = (int)(t - i * plane);
-  const int row = (int)div_u32((unsigned)r, by_nz), j = (int)j0 + row, k = r - row * g.nz;
-  const unsigned uid = ((unsigned)i * g.ny + j) * g.nz + k;
+  int i, j, k;
+  unsigned uid;
+  if (kRows) {
+    const unsigned j0 = (unsigned)g.ny * xcd / kXcds, j1 = (unsigned)g.ny * (xcd + 1) / kXcds;
+    const unsigned slab = (j1 - j0) * (unsigned)g.nz;
+    if (t >= slab * (unsigned)g.nx) return;
+    i = (int)div_u32(t, j1 - j0 == (unsigned)g.ny / kXcds ? by_less : by_more);
+    const int r = (int)(t - i * slab), row = (int)div_u32((unsigned)r, by_nz);
+    j = (int)j0 + row;
+    k = r - row * g.nz;
+    uid = ((unsigned)i * g.ny + j) * g.nz + k;
+  } else {
+    const unsigned plane = (unsigned)g.ny * g.nz, c0 = plane * xcd / kXcds, slab = plane * (xcd + 1) / kXcds - c0;
+    if (t >= slab * (unsigned)g.nx) return;
+    i = (int)div_u32(t, slab == plane / kXcds ? by_less : by_more);
+    const unsigned col = c0 + (t - i * slab);
+    j = (int)div_u32(col, by_nz);
+    k = (int)col - j * g.nz;
+    uid = i * plane + col;
+  }
   const double* __restrict__ p = phi_in + uid;
   const double s = MODE == 1 ? S[uid] : -1.0;
   const double sg = s >= 0.0 ? 1.0 : -1.0;
@@ -567,22 +584,25 @@ bool vdw_two_levels(int64_t total, int n_atoms) { return total >= (int64_t)1 << 
 // first stage used, which then holds φ: the two swap every step.
 pb_status tvd_rk3(pb_ctx* ctx, const GridDev& g, double*& cur, double*& spare, double* p2, const double* S, int mode,
                   int steps, double dt) {
-  const int64_t total = (int64_t)g.nx * g.ny * g.nz;
+  const int64_t plane = (int64_t)g.ny * g.nz, total = plane * g.nx;
   const double e = 4.0 * g.h * g.h * kWenoEps, c = 1.0 / (6.0 * g.h);
   const bool march = stage_marches(g);
+  const bool rows = g.ny >= 32;
+  const int64_t unit = rows ? g.nz : 1;  // what k_rk_node deals out to the XCDs: rows or columns, at least four each
   const int len = march_len(total), nkt = (g.nz + kStageK - 1) / kStageK, njt = (g.ny + kStageJ - 1) / kStageJ,
             nic = (g.nx + len - 1) / len, nb = nkt * njt * nic;
   const unsigned blocks = kXcds * (march ? (unsigned)((nb + kXcds - 1) / kXcds)
-                                         : blocks_for((int64_t)((g.ny + kXcds - 1) / kXcds) * g.nz * g.nx));
-  const uint64_t rows = (uint64_t)(g.ny / kXcds);  // or one more, of an XCD's slab in k_rk_node
-  const Div by_less = div_by(std::max<uint64_t>(rows, 1) * g.nz), by_more = div_by((rows + 1) * g.nz), by_nz = div_by(g.nz);
+                                         : blocks_for((plane / unit + kXcds - 1) / kXcds * unit * g.nx));
+  const int64_t own = plane / unit / kXcds;  // an XCD's units, or one more
+  const Div by_less = div_by(own * unit), by_more = div_by((own + 1) * unit), by_nz = div_by(g.nz);
   auto stage = [&](const double* in, const double* phi_n, double* out, int st) {
     if (march)
       (mode == 0 ? k_rk_march<0> : k_rk_march<1>)<<<blocks, kBlock, 0, ctx->stream>>>(g, in, phi_n, S, out, st, dt, e,
                                                                                      c, len, nkt, nic, nb);
     else
-      (mode == 0 ? k_rk_node<0> : k_rk_node<1>)<<<blocks, kBlock, 0, ctx->stream>>>(g, in, phi_n, S, out, st, dt, e, c,
-                                                                                  by_less, by_more, by_nz);
+      (rows ? mode == 0 ? k_rk_node<0, true> : k_rk_node<1, true>
+            : mode == 0 ? k_rk_node<0, false> : k_rk_node<1, false>)<<<blocks, kBlock, 0, ctx->stream>>>(
+          g, in, phi_n, S, out, st, dt, e, c, by_less, by_more, by_nz);
   };
   for (int s = 0; s < steps; ++s) {
     Scope t(ctx, "levelset");

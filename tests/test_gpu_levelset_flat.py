@@ -41,7 +41,8 @@ def _time_per_node(env, dims):
     return best / np.prod(dims)
 
 
-@pytest.mark.parametrize("flat,compact", [((620, 610, 7), (16, 410, 400)), ((300, 260, 34), (16, 410, 400))],
+@pytest.mark.parametrize("flat,compact", [((620, 610, 7), (16, 410, 400)), ((300, 260, 34), (16, 410, 400)),
+                                          ((300, 9, 300), (300, 300, 9))],
                          ids=str)
 def test_flat_grids(env, flat, compact):
     print("case: level set times", flat, compact, flush=True)
