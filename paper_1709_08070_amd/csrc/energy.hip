@@ -29,31 +29,34 @@ constexpr int kMaxDevices = 64;
 double* scratch_dev[kMaxDevices];  // device address of `scratch` per device ordinal
 std::mutex scratch_mu;
 
-// A block takes 64 nodes; its kRhsWaves waves share the atoms of each LDS tile out among themselves and
-// add their sums up at the end in wave order. Bound by FP64 issue (some 20 instructions
-// and a reciprocal square root a pair); by nodes alone the 1343 waves of 85,870 nodes leave SIMDs idle:
-// 1991 atoms 213 → 153 µs with the call, 500 atoms on 35,214 nodes 46 → 35.
-constexpr int kRhsWaves = 8, kRhsTile = 64 * kRhsWaves;
-
-__global__ void __launch_bounds__(kRhsTile) k_rhs(int n, const double* __restrict__ px, const double* __restrict__ py,
-                                                  const double* __restrict__ pz, const double* __restrict__ nx,
-                                                  const double* __restrict__ ny, const double* __restrict__ nz,
-                                                  const double* __restrict__ atoms, int n_atoms, double eps_in,
-                                                  double* __restrict__ g) {
-  __shared__ double4 tile[kRhsTile];
-  __shared__ double part[2][kRhsWaves][64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i = blockIdx.x * 64 + lane, r = min(i, n - 1);
+// A block takes 64·NW nodes; AW waves share the atoms of each LDS tile out among themselves and add their
+// sums up at the end in wave order. Bound by FP64 issue (some 20 instructions and a reciprocal square root a
+// pair): by nodes alone the 1343 waves of 85,870 nodes leave SIMDs idle, so eight waves share the
+// atoms of 64 nodes (1991 atoms 213 → 153 µs with the call, 500 atoms on 35,214 nodes 46 → 35). Few atoms do not
+// pay for that many waves' set-up (rhs_splits).
+template <int NW, int AW>
+__global__ void __launch_bounds__(64 * NW * AW) k_rhs(int n, const double* __restrict__ px, const double* __restrict__ py,
+                                                      const double* __restrict__ pz, const double* __restrict__ nx,
+                                                      const double* __restrict__ ny, const double* __restrict__ nz,
+                                                      const double* __restrict__ atoms, int n_atoms, double eps_in,
+                                                      double* __restrict__ g) {
+  static_assert(NW == 1 || AW == 1, "waves share out the nodes or the atoms");
+  constexpr int kTile = 64 * NW * AW;
+  __shared__ double4 tile[kTile];
+  __shared__ double part[2][AW > 1 ? AW : 1][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wa = AW > 1 ? wave : 0;
+  const int i = (AW > 1 ? blockIdx.x : blockIdx.x * NW + wave) * 64 + lane, r = min(i, n - 1);
   const double x = px[r], y = py[r], z = pz[r], a = nx[r], b = ny[r], c = nz[r];
   double s1 = 0.0, s2 = 0.0;
   const double c4 = 1.0 / (4.0 * kPi);
-  for (int base = 0; base < n_atoms; base += kRhsTile) {
-    const int k = base + (int)threadIdx.x, m = min(kRhsTile, n_atoms - base);
+  for (int base = 0; base < n_atoms; base += kTile) {
+    const int k = base + (int)threadIdx.x, m = min(kTile, n_atoms - base);
     // the charge enters as q/ε_I/(4π), formed once per atom (the same operations, hoisted)
     if (k < n_atoms)
       tile[threadIdx.x] = make_double4(atoms[5 * k], atoms[5 * k + 1], atoms[5 * k + 2], atoms[5 * k + 4] / eps_in * c4);
     __syncthreads();
 #pragma unroll 4
-    for (int q = wave; q < m; q += kRhsWaves) {
+    for (int q = wa; q < m; q += AW) {
       const double4 at = tile[q];
       const double dx = x - at.x, dy = y - at.y, dz = z - at.z;
       const double r2 = dx * dx + dy * dy + dz * dz;
@@ -65,12 +68,19 @@ __global__ void __launch_bounds__(kRhsTile) k_rhs(int n, const double* __restric
     }
     __syncthreads();
   }
-  part[0][wave][lane] = s1;
-  part[1][wave][lane] = s2;
+  if (AW == 1) {
+    if (i < n) {
+      g[i] = s1;
+      g[(int64_t)n + i] = s2;
+    }
+    return;
+  }
+  part[0][wa][lane] = s1;
+  part[1][wa][lane] = s2;
   __syncthreads();
   if (wave < 2 && i < n) {
     double s = 0.0;
-    for (int w = 0; w < kRhsWaves; ++w) s += part[wave][w][lane];
+    for (int w = 0; w < AW; ++w) s += part[wave][w][lane];
     g[(int64_t)wave * n + i] = s;
   }
 }
@@ -203,11 +213,17 @@ pb_status noalloc_init(pb_ctx* ctx) {
   return PB_OK;
 }
 
+// Whether eight waves share the atoms of 64 nodes: where the nodes alone give few waves and the atoms are enough to
+// share. The two cross at about 8 atoms up to 16,000 nodes, 64 at 105,366 (24.1 µs both with the call), 90 at 169,205 and
+// 200 at 371,268 (68.3); one atom on 724,665 nodes takes 37.9 µs split and 22.6 not, 1000 on 105,366 96 and 110.
+static bool rhs_splits(int n, int n_atoms) { return n_atoms >= 8 && n_atoms >= n / 2048; }
+
 pb_status rhs(pb_ctx* ctx, const pb_band* band, const double* atoms, int n_atoms, const Derived& d, double* g) {
   const int n = (int)band->n;
   Scope t(ctx, "rhs");
-  k_rhs<<<(unsigned)((n + 63) / 64), kRhsTile, 0, ctx->stream>>>(n, band->px, band->py, band->pz, band->nx, band->ny,
-                                                                 band->nz, atoms, n_atoms, d.eps_in, g);
+  const int nodes = rhs_splits(n, n_atoms) ? 64 : 256;
+  (nodes == 64 ? k_rhs<1, 8> : k_rhs<4, 1>)<<<(unsigned)((n + nodes - 1) / nodes), nodes == 64 ? 512 : 256, 0, ctx->stream>>>(
+      n, band->px, band->py, band->pz, band->nx, band->ny, band->nz, atoms, n_atoms, d.eps_in, g);
   return launch_ok(ctx, "rhs");
 }
 
