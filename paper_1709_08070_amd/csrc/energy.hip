@@ -85,42 +85,56 @@ __global__ void __launch_bounds__(64 * NW * AW) k_rhs(int n, const double* __res
   }
 }
 
-constexpr int kPsiBlock = 1024;
+constexpr int kPsiBlock = 1024, kPsiHalf = 512;
 
-// The sum of v over the block in a fixed order, in thread 0. red: one double per wave.
-__device__ __forceinline__ double block_sum(double v, double* red) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off);
-  __syncthreads();  // red may hold an earlier sum
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+// The sums of A values over a block of B threads in a fixed order: thread a < A gets that of v[a]. red: A doubles per
+// wave, not in use by the block.
+template <int B, int A>
+__device__ __forceinline__ double block_sums(double (&v)[A], double (&red)[B / 64][A]) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  // the halvings leave lane l with value l & (A − 1) summed over its group of A lanes
+#pragma unroll
+  for (int len = A / 2; len > 0; len /= 2) {
+    const bool up = lane & len;
+#pragma unroll
+    for (int u = 0; u < len; ++u) v[u] = (up ? v[len + u] : v[u]) + __shfl_xor(up ? v[u] : v[len + u], len);
+  }
+  double s = v[0];
+  for (int off = A; off < 64; off <<= 1) s += __shfl_xor(s, off);
+  if (lane < A) red[wave][lane] = s;
   __syncthreads();
-  if (threadIdx.x == 0)
-    for (int w = 1; w < kPsiBlock / 64; ++w) v += red[w];
-  return v;
+  s = 0.0;
+  if (wave == 0) {
+    for (int w = lane / A; w < B / 64; w += 64 / A) s += red[w][lane & (A - 1)];
+    for (int off = A; off < 64; off <<= 1) s += __shfl_xor(s, off);
+  }
+  return s;
 }
 
 // ψ_rxn of A atoms per block: every thread reads the data of each of its nodes once and adds that
-// node's term to the sums of all the block's atoms, then one fixed-order block reduction per atom.
+// node's term to the sums of all the block's atoms, then one fixed-order block reduction of them all (one per
+// atom, of two barriers and a serial sum each, took a fifth of the time of 20,000 atoms on 2924 nodes).
 // 1/ρ is rsqrt_f64 and e^{−κρ} exp_neg_f64 (fp64_math.hpp). Per pair, times 4π:
 // (s(θ1 E(1 + κρ) − 1)/ρ² · ψ̄_j + (1 − E) · ψ̄n_j)/ρ, with the weight h³ω_j/4π, ψ̄_j's in the normal. Block 0 sums the area
 // h³ Σ_j ω_j instead. Bound by FP64 issue (about 40 instructions a
-// pair); blocks of 512 threads left a CU two waves per SIMD to hide the loads of a node behind, and the area,
+// pair); one block of 512 threads per CU left two waves per SIMD to hide the loads of a node behind, and the area,
 // summed afterwards by one block, took 76 µs of its own: 1991 atoms on 85,870 nodes 414 → 306 µs with
 // the call.
-template <int A>
-__global__ void __launch_bounds__(kPsiBlock) k_psi_rxn(int n, const double* __restrict__ px, const double* __restrict__ py,
+template <int B, int A>
+__global__ void __launch_bounds__(B) k_psi_rxn(int n, const double* __restrict__ px, const double* __restrict__ py,
                                                     const double* __restrict__ pz, const double* __restrict__ nx,
                                                     const double* __restrict__ ny, const double* __restrict__ nz,
                                                     const double* __restrict__ w, const double* __restrict__ p,
                                                     const double* __restrict__ atoms, int n_atoms, double th1,
                                                     double kappa, double h3, double* __restrict__ psi,
                                                     double* __restrict__ area) {
-  __shared__ double red[kPsiBlock / 64];
+  __shared__ double red[B / 64][A], red1[B / 64][1];
   if (blockIdx.x == 0) {
-    double s = 0.0;
+    double s[1] = {0.0};
 #pragma unroll 8
-    for (int j = threadIdx.x; j < n; j += kPsiBlock) s += w[j];
-    s = block_sum(s, red);
-    if (threadIdx.x == 0) *area = h3 * s;
+    for (int j = threadIdx.x; j < n; j += B) s[0] += w[j];
+    const double t = block_sums<B>(s, red1);
+    if (threadIdx.x == 0) *area = h3 * t;
     return;
   }
   const int k0 = (blockIdx.x - 1) * A;
@@ -133,7 +147,7 @@ __global__ void __launch_bounds__(kPsiBlock) k_psi_rxn(int n, const double* __re
   double acc[A];
 #pragma unroll
   for (int a = 0; a < A; ++a) acc[a] = 0.0;
-  for (int j = threadIdx.x; j < n; j += kPsiBlock) {
+  for (int j = threadIdx.x; j < n; j += B) {
     const double yx = px[j], yy = py[j], yz = pz[j];
     const double ww = c4 * w[j];
     const double w1 = ww * p[j], w2 = ww * p[n + j];
@@ -150,23 +164,20 @@ __global__ void __launch_bounds__(kPsiBlock) k_psi_rxn(int n, const double* __re
       acc[a] = fma(rinv, t, acc[a]);
     }
   }
-#pragma unroll
-  for (int a = 0; a < A; ++a) {
-    const double s = block_sum(acc[a], red);
-    if (threadIdx.x == 0 && k0 + a < n_atoms) psi[k0 + a] = s;
-  }
+  const double s = block_sums<B>(acc, red);
+  if (threadIdx.x < A && k0 + (int)threadIdx.x < n_atoms) psi[k0 + threadIdx.x] = s;
 }
 
 // The fields of pb_energy in order: out[0] = G_pol = ½ Σ_k q_k ψ_k, out[1] = G_pol in kcal/mol (one
 // block, fixed order); out[2], the area, is k_psi_rxn's.
 __global__ void __launch_bounds__(kPsiBlock) k_finish(int n_atoms, const double* __restrict__ atoms,
                                                    const double* __restrict__ psi, double* __restrict__ out) {
-  __shared__ double red[kPsiBlock / 64];
-  double a = 0.0;
-  for (int k = threadIdx.x; k < n_atoms; k += kPsiBlock) a += atoms[5 * k + 4] * psi[k];
-  a = block_sum(a, red);
+  __shared__ double red[kPsiBlock / 64][1];
+  double a[1] = {0.0};
+  for (int k = threadIdx.x; k < n_atoms; k += kPsiBlock) a[0] += atoms[5 * k + 4] * psi[k];
+  const double t = block_sums<kPsiBlock>(a, red);
   if (threadIdx.x == 0) {
-    const double gpol = 0.5 * a;
+    const double gpol = 0.5 * t;
     out[0] = gpol;
     out[1] = gpol * 4.0 * kPi * 332.0637;
   }
@@ -176,13 +187,13 @@ __global__ void __launch_bounds__(kPsiBlock) k_finish(int n_atoms, const double*
 void energy_launch(pb_ctx* ctx, const pb_band* band, const double* atoms, int n_atoms, const Derived& d,
                    const double* p, double* psi, double* out) {
   const int n = (int)band->n;
-  auto launch = [&](auto kernel, int A) {
-    kernel<<<1 + (n_atoms + A - 1) / A, kPsiBlock, 0, ctx->stream>>>(n, band->px, band->py, band->pz, band->nx, band->ny,
+  auto launch = [&](auto kernel, int A, int threads) {
+    kernel<<<1 + (n_atoms + A - 1) / A, threads, 0, ctx->stream>>>(n, band->px, band->py, band->pz, band->nx, band->ny,
                                                                      band->nz, band->w, p, atoms, n_atoms, d.th1,
                                                                      d.kappa, d.h3, psi, out + 2);
   };
-  // One block fits a CU at a time; a turn over the nodes costs about its atoms and two thirds (the loads).
-  // So the atoms per block that need the least in turns of all CUs: for 1000 atoms 4 (121 µs; 8: 194,
+  // One block of 1024 threads fits a CU at a time; a turn over the nodes costs about its atoms and two thirds (the
+  // loads). So the atoms per block that need the least in turns of all CUs: for 1000 atoms 4 (121 µs; 8: 194,
   // 2: 152), for 1991 8 (306; 4: 329), for 5000 4 (1382; 8: 1505), for 500 2 (69; 4: 84, 8: 136).
   int best = 8;
   double cost = INFINITY;
@@ -190,10 +201,14 @@ void energy_launch(pb_ctx* ctx, const pb_band* band, const double* atoms, int n_
     const double c = (double)(((n_atoms + A - 1) / A + ctx->n_cu - 1) / ctx->n_cu) * (A + 2.0 / 3.0);
     if (c < cost) cost = c, best = A;
   }
-  if (best == 8) launch(k_psi_rxn<8>, 8);
-  else if (best == 4) launch(k_psi_rxn<4>, 4);
-  else if (best == 2) launch(k_psi_rxn<2>, 2);
-  else launch(k_psi_rxn<1>, 1);
+  // More than a block per CU: half the threads, so that a block's set-up and sums run beside another's pairs. 20,000 atoms
+  // on 492, 2924, 13,628 and 105,366 nodes 66, 136, 427 and 2975 µs with the call; 82, 171, 495 and 3374 in blocks of 1024. With
+  // a block per CU or fewer the half would leave the CU two waves per SIMD: 1000 atoms on 105,366 nodes 240 and 215.
+  const bool half = (n_atoms + best - 1) / best > ctx->n_cu;
+  if (best == 8) half ? launch(k_psi_rxn<kPsiHalf, 8>, 8, kPsiHalf) : launch(k_psi_rxn<kPsiBlock, 8>, 8, kPsiBlock);
+  else if (best == 4) half ? launch(k_psi_rxn<kPsiHalf, 4>, 4, kPsiHalf) : launch(k_psi_rxn<kPsiBlock, 4>, 4, kPsiBlock);
+  else if (best == 2) half ? launch(k_psi_rxn<kPsiHalf, 2>, 2, kPsiHalf) : launch(k_psi_rxn<kPsiBlock, 2>, 2, kPsiBlock);
+  else launch(k_psi_rxn<kPsiBlock, 1>, 1, kPsiBlock);
   k_finish<<<1, kPsiBlock, 0, ctx->stream>>>(n_atoms, atoms, psi, out);
 }
 
