@@ -1031,7 +1031,13 @@ extern "C" pb_status pb_ibim_solve_batched(pb_ctx* ctx, int n_mol, const pb_band
 
   // far-field tile shape: autotuned once per batch shape
   {
-    const int64_t key = (int64_t)B.ntot * 4096 + n_mol;
+    std::vector<int> key{B.d.kappa > 0.0};
+    for (const MolDev& md : B.mols_h) key.push_back(md.n);
+    std::sort(key.begin() + 1, key.end());
+    if (ctx->batch_cfg.size() >= kBatchShapes) {
+      ctx->batch_cfg.clear();
+      ctx->batch_cfg64.clear();
+    }
     auto itc = ctx->batch_cfg.find(key);
     const char* env = std::getenv("PB_FAR_CFG");
     if (itc != ctx->batch_cfg.end()) {

@@ -38,6 +38,8 @@ struct Derived {
 
 Derived derive(const pb_params& p);
 
+constexpr size_t kBatchShapes = 1024;  // batch shapes whose kernel choice a context keeps
+
 // Growable device buffer owned by the context.
 struct DevBuf {
   void* ptr = nullptr;
@@ -143,8 +145,9 @@ struct pb_ctx {
     const int2* dev = nullptr;
   };
   std::map<int, SymList> sym_list;     // item lists of the symmetric kernels per tile size
-  std::map<int64_t, int> batch_cfg;    // autotuned far-field kernel for batches, per (nodes, molecules)
-  std::map<int64_t, int> batch_cfg64;  // FP64 operator kernel for batches (0 tiled, 1 symmetric)
+  // Autotuned kernels of batches, per batch shape (κ > 0 or not, then the molecules' sizes in increasing order): the far
+  // field, and the FP64 operator (0 tiled, 1 symmetric). Forgotten when kBatchShapes are kept.
+  std::map<std::vector<int>, int> batch_cfg, batch_cfg64;
   hipStream_t batch_stream = nullptr;  // capture stream of the batched solve
   const void* nn_key = nullptr;        // band prepared for the learned preconditioner
   int64_t nn_n = 0;
