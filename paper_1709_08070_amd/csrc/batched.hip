@@ -1034,17 +1034,15 @@ extern "C" pb_status pb_ibim_solve_batched(pb_ctx* ctx, int n_mol, const pb_band
     std::vector<int> key{B.d.kappa > 0.0};
     for (const MolDev& md : B.mols_h) key.push_back(md.n);
     std::sort(key.begin() + 1, key.end());
-    if (ctx->batch_cfg.size() >= kBatchShapes) {
-      ctx->batch_cfg.clear();
-      ctx->batch_cfg64.clear();
-    }
+    for (auto* kept : {&ctx->batch_cfg, &ctx->batch_cfg64})
+      if (kept->size() >= kBatchShapes) kept->clear();
+    // the environment's choice holds for its own call only
     auto itc = ctx->batch_cfg.find(key);
     const char* env = std::getenv("PB_FAR_CFG");
-    if (itc != ctx->batch_cfg.end()) {
-      B.cfg = itc->second;
-    } else if (env && std::atoi(env) >= 0 && std::atoi(env) < kNumCfgB) {
+    if (env && std::atoi(env) >= 0 && std::atoi(env) < kNumCfgB) {
       B.cfg = std::atoi(env);
-      ctx->batch_cfg[key] = B.cfg;
+    } else if (itc != ctx->batch_cfg.end()) {
+      B.cfg = itc->second;
     } else {
       k_pack_batch<<<nbn, kBlock, 0, B.st>>>(B.ntot, B.mol_of, B.mols, x, nullptr, 0, 0, B.d.h3 / (4.0 * kPi), B.sigma);
       hipEvent_t e0, e1;
@@ -1072,11 +1070,10 @@ extern "C" pb_status pb_ibim_solve_batched(pb_ctx* ctx, int n_mol, const pb_band
     // the FP64 operator's kernel, the same way (PB_F64_CFG=<0|1> fixes it)
     auto it64 = ctx->batch_cfg64.find(key);
     const char* env64 = std::getenv("PB_F64_CFG");
-    if (it64 != ctx->batch_cfg64.end()) {
-      B.cfg64 = it64->second;
-    } else if (env64 && (std::atoi(env64) == 0 || std::atoi(env64) == 1)) {
+    if (env64 && (std::atoi(env64) == 0 || std::atoi(env64) == 1)) {
       B.cfg64 = std::atoi(env64);
-      ctx->batch_cfg64[key] = B.cfg64;
+    } else if (it64 != ctx->batch_cfg64.end()) {
+      B.cfg64 = it64->second;
     } else {
       k_weights_batch<<<nbn, kBlock, 0, B.st>>>(B.ntot, B.mol_of, B.mols, x, B.d.h3 / (4.0 * kPi), B.wpsi, B.wpsn);
       hipEvent_t e0, e1;

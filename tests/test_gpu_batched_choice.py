@@ -56,3 +56,16 @@ def test_other_batches_choose_for_themselves(env, sizes, kappa):
     assert first.far_symmetric == 0 and first.far_tile == 256 and first.far_tpl == 2
     assert solve(ctx, sizes, kappa).far_symmetric == 1
     ctx.close()
+
+
+def test_environment_holds_for_its_call(env):
+    pb, solve = env
+    print("case: batch choice by the environment", flush=True)
+    ctx = pb.Context(0)
+    sizes = (40000, 30000)
+    assert solve(ctx, sizes, 0.1257).far_symmetric == 1
+    second = solve(ctx, sizes, 0.1257, "2")
+    assert second.far_symmetric == 0 and second.far_tile == 256 and second.far_tpl == 2
+    assert solve(ctx, sizes, 0.1257, "4").far_symmetric == 1
+    assert solve(ctx, sizes, 0.1257).far_symmetric == 1
+    ctx.close()
