@@ -321,14 +321,22 @@ pb_status exclusive_scan_i64(pb_ctx* ctx, int64_t* data, int64_t n, int64_t* tot
 
 pb_status exclusive_scan_i32(pb_ctx* ctx, int* data, int64_t n) { return scan<int>(ctx, data, n, nullptr); }
 
+pb_status host_mapped(pb_ctx* ctx, size_t bytes, void** host, void** dev) {
+  void *h = nullptr, *d = nullptr;
+  PB_HIP(ctx, hipHostMalloc(&h, bytes, hipHostMallocCoherent | hipHostMallocMapped));
+  const hipError_t e = hipHostGetDevicePointer(&d, h, 0);
+  if (e != hipSuccess) {
+    (void)hipHostFree(h);
+    return ctx->fail(PB_EDEVICE, "device address of pinned memory: %s", hipGetErrorString(e));
+  }
+  *host = h;
+  *dev = d;
+  return PB_OK;
+}
+
 pb_status host_pin(pb_ctx* ctx) {
   if (ctx->host_pin) return PB_OK;
-  void *h = nullptr, *dev = nullptr;
-  PB_HIP(ctx, hipHostMalloc(&h, sizeof(double) * kHostPin, hipHostMallocCoherent | hipHostMallocMapped));
-  ctx->host_pin = (double*)h;
-  PB_HIP(ctx, hipHostGetDevicePointer(&dev, h, 0));
-  ctx->host_pin_dev = (double*)dev;
-  return PB_OK;
+  return host_mapped(ctx, sizeof(double) * kHostPin, (void**)&ctx->host_pin, (void**)&ctx->host_pin_dev);
 }
 
 }  // namespace pb

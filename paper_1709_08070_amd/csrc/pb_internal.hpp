@@ -205,6 +205,8 @@ pb_status exclusive_scan_i32(pb_ctx* ctx, int* data, int64_t n);
 // copy: written by kernels, read after a stream synchronization. Allocated on first use.
 constexpr int kHostPin = 2048;
 pb_status host_pin(pb_ctx* ctx);
+// Allocates coherent pinned host memory and its device address: both, or neither and an error.
+pb_status host_mapped(pb_ctx* ctx, size_t bytes, void** host, void** dev);
 
 // Operator internals used by the solver.
 pb_status matvec_fp64(pb_ctx* ctx, const pb_band* band, const Derived& d, const double* p, double* y);

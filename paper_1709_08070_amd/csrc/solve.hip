@@ -278,16 +278,9 @@ pb_status norm2(pb_ctx* ctx, Krylov& K, const double* v, double* out) {
 
 // Sets up the pinned host slots through which GMRES reads each step's state.
 pb_status step_sync_init(pb_ctx* ctx) {
-  if (!ctx->host_state) {
-    void* h = nullptr;
-    // coherent and mapped: the Givens step writes each step's state straight into it
-    PB_HIP(ctx, hipHostMalloc(&h, sizeof(int) * 2 * kMaxRestart, hipHostMallocCoherent | hipHostMallocMapped));
-    ctx->host_state = (int*)h;
-    void* d = nullptr;
-    PB_HIP(ctx, hipHostGetDevicePointer(&d, h, 0));
-    ctx->host_state_dev = (int*)d;
-  }
-  return PB_OK;
+  if (ctx->host_state) return PB_OK;
+  // coherent and mapped: the Givens step writes each step's state straight into it
+  return host_mapped(ctx, sizeof(int) * 2 * kMaxRestart, (void**)&ctx->host_state, (void**)&ctx->host_state_dev);
 }
 
 // Waits until the Givens step of Arnoldi step k has written its slot (the host set it to −1
