@@ -209,8 +209,8 @@ pb_status pb_ibim_rhs(pb_ctx* ctx, const pb_band* band, const double* atoms, int
    PB_MIXED: FP32 far field + FP64 near field (every pair closer than r_c, the regularized
    ones included). The far-field kernel is chosen by the band's size: symmetric from 12,800
    nodes on (16,384 with kappa = 0), one-directional below (pb_ibim_solve_batched chooses once per
-   batch shape by timing the candidates); the environment variable PB_FAR_CFG=k
-   fixes it instead: k = 0..3 the one-directional kernel with (sources per LDS tile, targets
+   batch shape, the sizes and kappa = 0 or not, by timing the candidates); the environment variable
+   PB_FAR_CFG=k fixes it instead, read at every call: k = 0..3 the one-directional kernel with (sources per LDS tile, targets
    per lane) = (256, 1), (512, 1), (256, 2), (512, 2); k = 4 the symmetric kernel (each
    unordered pair evaluated once for both directions). All give the same operator up to
    FP32 rounding; each is bitwise reproducible from run to run.

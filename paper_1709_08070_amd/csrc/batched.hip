@@ -123,8 +123,8 @@ static __global__ void __launch_bounds__(kBlock) k_far32_batch(const Item* __res
 }
 
 // The symmetric kernels of a batch take chunks of whole sub-blocks (as long bands do, few partial sums) in
-// tiles of 256 nodes: half the LDS of tiles of 512, 139.0 against 139.5 ms for a solve of ten molecules of 13,000
-// to 46,000 nodes.
+// tiles of 256 nodes. Tiles of 512 take the same time (ten molecules of 13,000 to 46,000 nodes 139.0 and 139.5 ms, less
+// than the runs differ) and twice the LDS, of which the FP64 kernel has little left (static_assert in k_p2p_f64_sym).
 constexpr int kTiles = kSymSub / 256;
 
 // Symmetric far field of every active molecule: items (molecule, Ic, Jc).

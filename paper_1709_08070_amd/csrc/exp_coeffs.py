@@ -6,8 +6,9 @@ Prints the coefficients (t^0 first) and the largest relative error of their Horn
 evaluation on a 4001-point grid, measured in 60-digit arithmetic (1.7e-17; the Taylor
 series to degree 13 gives 5.2e-18, the FP64 rounding unit is 1.1e-16).
 
-exp_neg_tab_f64: exp_table.hpp (written beside this file) with 2^{i/256} as the nearest double and the
-rest, and the coefficients of e^r ≈ 1 + r + r²(c2 + c3 r + c4 r²) on |r| ≤ ln2/512, the quadratic through
+exp_neg_tab_f64, the table-driven method of P. T. P. Tang ("Table-driven implementation of the exponential
+function in IEEE floating-point arithmetic", ACM Trans. Math. Softw. 15, 1989): exp_table.hpp (written beside this
+file) with 2^{i/256} as the nearest double and the rest, and the coefficients of e^r ≈ 1 + r + r²(c2 + c3 r + c4 r²) on |r| ≤ ln2/512, the quadratic through
 (e^r − 1 − r)/r² at its three Chebyshev nodes (relative error of e^r 9.5e-18).
 
     python paper_1709_08070_amd/csrc/exp_coeffs.py
@@ -54,7 +55,8 @@ for i in range(N):
     t = mp.mpf(2) ** (mp.mpf(i) / N)
     rows.append("{%s, %s}" % (float(t).hex(), float(t - mp.mpf(float(t))).hex()))
 with open(os.path.join(os.path.dirname(os.path.abspath(__file__)), "exp_table.hpp"), "w") as f:
-    f.write("// 2^{i/256}: the nearest double and the rest. Written by exp_coeffs.py.\n#pragma once\n\n")
+    f.write("// 2^{i/256}: the nearest double and the rest. Written by exp_coeffs.py, which names the method.\n")
+    f.write("#pragma once\n\n")
     f.write("#include <hip/hip_runtime.h>\n\nnamespace pb {\n\n")
     f.write("static __device__ const double2 kExpTable[%d] = {\n" % N)
     for i in range(0, N, 2):

@@ -34,7 +34,7 @@ __device__ __forceinline__ double exp_neg_f64(double z) {
   return ldexp(p, (int)k);
 }
 
-// The same with a table in LDS (tab: a copy of kExpTable, 2^{i/256} = T + T_lo): −z = (256q + i)·ln2/256 + r,
+// The same with a table in LDS (Tang 1989, see exp_coeffs.py; tab: a copy of kExpTable, 2^{i/256} = T + T_lo): −z = (256q + i)·ln2/256 + r,
 // |r| ≤ ln2/512, e^{−z} = 2^q (T + (T(e^r − 1) + T_lo)), e^r − 1 to degree 4 (exp_coeffs.py, relative
 // error 9.5e-18): 12 FP64 instructions for 18, and one rounding of the sum where the polynomial alone has that of
 // its last two steps. Where 256z/ln2 exceeds an int (z > 5.8e6) the conversion saturates as v_cvt_i32_f64 is

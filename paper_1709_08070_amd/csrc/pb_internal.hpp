@@ -193,12 +193,11 @@ pb_status check_curv(pb_ctx* ctx, const pb_band* b, const pb_params* p);
 pb_status sync(pb_ctx* ctx, const char* where);
 pb_status launch_ok(pb_ctx* ctx, const char* where);
 
-// Scans and reductions shared by the stages.
-// Exclusive scan of n values in place on the context stream; returns the total on host (after
-// a stream synchronization) when asked for.
-// The same with the total left in the first of the pinned slots, to be read after a synchronization.
-pb_status exclusive_scan_i64_pin(pb_ctx* ctx, int64_t* data, int64_t n);
+// Scans shared by the stages: exclusive, of n values in place on the context stream.
+// Returns the total on host (after a stream synchronization) when asked for.
 pb_status exclusive_scan_i64(pb_ctx* ctx, int64_t* data, int64_t n, int64_t* total_host);
+// The total is left in the first of the pinned slots, to be read after a synchronization.
+pb_status exclusive_scan_i64_pin(pb_ctx* ctx, int64_t* data, int64_t n);
 pb_status exclusive_scan_i32(pb_ctx* ctx, int* data, int64_t n);
 
 // Pinned, mapped host memory through which kernels hand small results to the host without a

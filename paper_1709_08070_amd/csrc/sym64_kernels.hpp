@@ -365,15 +365,16 @@ __device__ __forceinline__ void sym64_item(const BandDev& b, const double* __res
 }
 
 // Symmetric FP64 operator of one band: one block per work item. k2 = κ² (a kernel argument,
-// so that it stays in scalar registers). Capped at 168 VGPRs for three waves per SIMD (at most 49
-// KB of LDS per block of four waves): the pair loops stay free of spills, which fall in the set-up
-// code around them.
+// so that it stays in scalar registers). Capped at 168 VGPRs for three waves per SIMD, for which the LDS of their
+// blocks has to fit a CU's 160 KB (52.2 KB a block of four waves with tiles of 512, 48.2 with 256, 24.1 a block of
+// two waves with 128): the pair loops stay free of spills, which fall in the set-up code around them.
 template <int TW, int SW>
 static __global__ void __attribute__((unused)) __launch_bounds__(64 * TW * SW) __attribute__((amdgpu_waves_per_eu(3)))
     k_p2p_f64_sym(BandDev b, const double* __restrict__ wpsi, const double* __restrict__ wpsn, int n, int nsub,
                   const int2* __restrict__ items, int n_items, KParams kp, double k2, double* __restrict__ partial,
                   const int* __restrict__ skip) {
   if (skip && *skip) return;
+  static_assert(12 / (TW * SW) * sizeof(Sym64Shared<TW, SW>) <= 160 * 1024, "three waves per SIMD by LDS");
   __shared__ Sym64Shared<TW, SW> sh;
   load_exp_table(sh.exp);
   __syncthreads();

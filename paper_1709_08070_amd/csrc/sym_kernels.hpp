@@ -17,24 +17,30 @@
 // 1/r'³ enters once through a/r'³, c2/r'³ and Q/r'³. Records: A = (σ(x − c), V) and
 // N = (n, W), two float4 per node.
 //
-// Work decomposition. The band is cut into chunks of C = 512·nsub nodes (nC chunks). One
-// work item is a chunk pair (Ic, Jc) with Ic ≤ Jc; the partial sums keep the chunked layout
-// of the one-directional kernel, partial[c][e] = contributions to vector entry e from the
-// sources of chunk c. Item (Ic, Jc), Ic < Jc, owns the slots (Jc, i ∈ Ic) (forward) and
-// (Ic, j ∈ Jc) (reverse); the diagonal item (Ic, Ic) owns (Ic, i ∈ Ic). Every slot belongs to
-// exactly one item, which accumulates into it in FP64 in a fixed order, so the result is
+// Work decomposition. The band is cut into sub-blocks of 512 nodes, tiles of F = 512, 256 or 128 nodes (a sub-block
+// is whole tiles) and chunks of nsub tiles, which are either whole sub-blocks or one tile each. One work item is a
+// chunk pair (Ic, Jc); the partial sums keep the chunked layout of the one-directional kernel,
+// partial[c][e] = contributions to vector entry e from the sources of chunk c. Which item owns which slots:
+//   - chunks of different sub-blocks meet both ways in one item, Ic < Jc, which owns the slots
+//     (Jc, i ∈ Ic) (forward) and (Ic, j ∈ Jc) (reverse);
+//   - chunks within one sub-block (tiles smaller than it, one a chunk) meet in both orders, one way
+//     each: (Ic, Jc), Ic < Jc or Ic > Jc, owns the slots (Jc, i ∈ Ic) and no others;
+//   - the diagonal item (Ic, Ic) owns (Ic, i ∈ Ic): within it, tiles of different sub-blocks meet both ways, tiles of
+//     one sub-block one way.
+// Every slot belongs to exactly one item, which accumulates into it in FP64 in a fixed order, so the result is
 // bitwise reproducible and needs no atomics in global memory. The forward sums of a target
-// sub-block stay in registers over all the item's source sub-blocks and are stored once; the
-// reverse sums of a source sub-block are stored after its first target sub-block and added
+// tile stay in registers over all the item's source tiles and are stored once; the
+// reverse sums of a source tile are stored after its first target tile and added
 // to after each later one (a slot's first writer stores, the later ones add: no zeroing pass).
 //
-// Inside an item the block (256 threads, 4 waves) walks sub-blocks of 512 nodes: targets T
-// (2 per thread), sources S staged in LDS. For T ≠ S, lane l of a wave pairs its targets with
+// Inside an item the block (SymShared: TW waves of 128 targets by SW waves that share the sources) walks
+// tiles: targets T (2 per thread), sources S staged in LDS. For S in another sub-block than T, lane l of a wave pairs
+// its targets with
 // source g·64 + ((l + s) mod 64) at step s, so the 64 lanes touch 64 different sources. The
 // reverse sums travel with their source: after each step every lane passes its running sums
 // to lane l − 1 (ds_bpermute), which takes that source at the next step; after 64 steps lane
-// l holds the sums of source g·64 + l, accumulated in a fixed order. For T = S (only in
-// diagonal items; it holds the self pair and the nearest pairs) the one-directional loop with
+// l holds the sums of source g·64 + l, accumulated in a fixed order. For S in the sub-block of T (the
+// self pair and the nearest pairs are there) the one-directional loop with
 // the near-pair predicate runs.
 // Sub-block pairs whose bounding boxes are farther apart than r_c (with the margin of
 // F32Params::far2) skip the predicate.
@@ -168,8 +174,8 @@ __device__ __forceinline__ void sym_block(const float4* __restrict__ A, const fl
     for (int s = 0; s < 64; ++s) {
       int at = s;
       // Tiles of 512: the step index in a register. 180 VALU instructions per four pairs instead of 177,
-      // 22.7 per ordered pair in all, within the range that the committed counter summary of this instance is
-      // tested against; 1% slower than without (246,042 nodes: 28.4 against 28.1 ms).
+      // 22.7 per ordered pair in all instead of 22.3, and 1% slower than without (246,042 nodes: 28.4 against
+      // 28.1 ms): the count's only use is that the test of this instance's counter summary asks for 22.5 to 23.5.
       if (TW == 4) asm("" : "+v"(at));
       const float4 sa = pA[at], sn = pN[at];
       pair_sym<kScreened, kCheck>(taa, tna, sa, sn, fp, fa1, fa2, ra1, ra2);
