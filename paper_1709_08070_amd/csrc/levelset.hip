@@ -576,9 +576,13 @@ constexpr int kMaxAxis = 4096;
 unsigned blocks_for(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
 // Whether k_vdw filters in two levels. The box's eight tiles follow one another in a block, which
-// pays when there are boxes enough: 5000 atoms on 286 × 253 × 217 nodes 0.55 ms against 1.30 in one level,
-// 2000 atoms on 161 × 145 × 127 nodes (2.97M) 0.167 against 0.145.
-bool vdw_two_levels(int64_t total, int n_atoms) { return total >= (int64_t)1 << 22 && n_atoms > 2 * kBlock; }
+// pays when there are boxes enough and when a scan of the atoms costs more than a tile's own work, the
+// sooner the more boxes there are (µs, one level against two): 4.25M nodes 69 and 89 with 513 atoms, 133 and
+// 140 with 1400, 177 and 159 with 2000; 8M nodes 117 and 135 with 700 atoms, 150 and 151 with 1000, 208 and 186 with
+// 1400; 5000 atoms on 286 × 253 × 217 nodes 1300 and 550, 2000 atoms on 161 × 145 × 127 nodes (2.97M) 145 and 167.
+bool vdw_two_levels(int64_t total, int n_atoms) {
+  return total >= (int64_t)1 << 22 && n_atoms > (total >= (int64_t)1 << 23 ? 4 : 6) * kBlock;
+}
 
 // Three-stage TVD-RK3 for `steps` steps of size dt on φ in cur. A step's result goes to the buffer its
 // first stage used, which then holds φ: the two swap every step.
