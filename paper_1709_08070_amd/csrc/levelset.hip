@@ -59,8 +59,10 @@ __device__ __forceinline__ void vdw_update(double x, double y, double z, const d
 }
 
 // The atoms of src(0..m−1) that can attain F within R of c, appended to list (the first cap of them);
-// returns how many there are. Called by the whole block; red and count are its scratch.
-template <class Src>
+// returns how many there are. Called by the whole block; red and count are its scratch. The minimum's
+// exchange is by one wave (kOneWave), which leaves the LDS to the other blocks, or, with one barrier less,
+// by each wave: 200³ nodes with 300 atoms 72 and 78 µs in one level, 107 and 104 in two.
+template <bool kOneWave, class Src>
 __device__ __forceinline__ int vdw_filter(const Src& src, int m, double cx, double cy, double cz, double R, double h,
                                           double4* list, int cap, double* red, int* count) {
   const int t = threadIdx.x;
@@ -70,11 +72,23 @@ __device__ __forceinline__ int vdw_filter(const Src& src, int m, double cx, doub
     const double dc = sqrt((sq(cx - q.x) + sq(cy - q.y)) + sq(cz - q.z)) - q.w;
     u = dc < u ? dc : u;
   }
-  for (int off = 32; off > 0; off >>= 1) u = fmin(u, __shfl_xor(u, off));
-  if ((t & 63) == 0) red[t >> 6] = u;
   if (t == 0) *count = 0;
-  __syncthreads();
-  for (int w = 0; w < kBlock / 64; ++w) u = fmin(u, red[w]);
+  if (kOneWave) {
+    red[t] = u;
+    __syncthreads();
+    if (t < 64) {
+      for (int w = 1; w < kBlock / 64; ++w) u = fmin(u, red[t + 64 * w]);
+      for (int off = 32; off > 0; off >>= 1) u = fmin(u, __shfl_xor(u, off));
+      if (t == 0) red[0] = u;
+    }
+    __syncthreads();
+    u = red[0];
+  } else {
+    for (int off = 32; off > 0; off >>= 1) u = fmin(u, __shfl_xor(u, off));
+    if ((t & 63) == 0) red[t >> 6] = u;
+    __syncthreads();
+    for (int w = 0; w < kBlock / 64; ++w) u = fmin(u, red[w]);
+  }
   const double reach = u + 2.0 * R;  // an atom matters only within reach + r of c
   for (int a = t; a < m; a += kBlock) {
     const double4 q = src(a);
@@ -94,7 +108,7 @@ template <bool TWO>
 __global__ void __launch_bounds__(kBlock) k_vdw(GridDev g, const double* __restrict__ atoms, int n_atoms,
                                                 double shift, double* __restrict__ phi) {
   __shared__ double4 box[TWO ? kVdwBox : 1], list[kVdwList];
-  __shared__ double red[kBlock / 64];
+  __shared__ double red[TWO ? kBlock / 64 : kBlock];
   __shared__ int count;
   constexpr int T = TWO ? 2 : 1;  // tiles per axis
   const int nbk = (g.nz + T * kTK - 1) / (T * kTK), nbj = (g.ny + T * kTJ - 1) / (T * kTJ);
@@ -108,7 +122,7 @@ __global__ void __launch_bounds__(kBlock) k_vdw(GridDev g, const double* __restr
   };
   int mb = kVdwBox + 1;
   if (TWO)
-    mb = vdw_filter(global, n_atoms, centre(g.ox, bi * T * kTI, T * kTI), centre(g.oy, bj * T * kTJ, T * kTJ),
+    mb = vdw_filter<false>(global, n_atoms, centre(g.ox, bi * T * kTI, T * kTI), centre(g.oy, bj * T * kTJ, T * kTJ),
                     centre(g.oz, bk * T * kTK, T * kTK), radius(T * kTI, T * kTJ, T * kTK), g.h, box, kVdwBox, red,
                     &count);
   const int t = threadIdx.x;
@@ -117,8 +131,9 @@ __global__ void __launch_bounds__(kBlock) k_vdw(GridDev g, const double* __restr
     if (i0 >= g.nx || j0 >= g.ny || k0 >= g.nz) continue;  // the whole block
     const double cx = centre(g.ox, i0, kTI), cy = centre(g.oy, j0, kTJ), cz = centre(g.oz, k0, kTK),
                  R = radius(kTI, kTJ, kTK);
-    const int m = TWO && mb <= kVdwBox ? vdw_filter(local, mb, cx, cy, cz, R, g.h, list, kVdwList, red, &count)
-                                       : vdw_filter(global, n_atoms, cx, cy, cz, R, g.h, list, kVdwList, red, &count);
+    const int m = TWO && mb <= kVdwBox
+                      ? vdw_filter<!TWO>(local, mb, cx, cy, cz, R, g.h, list, kVdwList, red, &count)
+                      : vdw_filter<!TWO>(global, n_atoms, cx, cy, cz, R, g.h, list, kVdwList, red, &count);
     const int i = i0 + t / (kTJ * kTK), j = j0 + (t / kTK) % kTJ, k = k0 + t % kTK;
     const double x = g.ox + g.h * (double)i, y = g.oy + g.h * (double)j, z = g.oz + g.h * (double)k;
     double best = INFINITY;
@@ -577,8 +592,8 @@ unsigned blocks_for(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
 // Whether k_vdw filters in two levels. The box's eight tiles follow one another in a block, which
 // pays when there are boxes enough and when a scan of the atoms costs more than a tile's own work, the
-// sooner the more boxes there are (µs, one level against two): 4.25M nodes 69 and 89 with 513 atoms, 133 and
-// 140 with 1400, 177 and 159 with 2000; 8M nodes 117 and 135 with 700 atoms, 150 and 151 with 1000, 208 and 186 with
+// sooner the more boxes there are (µs, one level against two): 4.25M nodes 66 and 89 with 513 atoms, 135 and
+// 143 with 1400, 179 and 160 with 2000; 8M nodes 111 and 132 with 700 atoms, 144 and 146 with 1000, 205 and 181 with
 // 1400; 5000 atoms on 286 × 253 × 217 nodes 1300 and 550, 2000 atoms on 161 × 145 × 127 nodes (2.97M) 145 and 167.
 bool vdw_two_levels(int64_t total, int n_atoms) {
   return total >= (int64_t)1 << 22 && n_atoms > (total >= (int64_t)1 << 23 ? 4 : 6) * kBlock;
